@@ -76,6 +76,51 @@ int chunk(int planes, int xy_tiles, int cap, int target = kTargetGroups)
     return (int)std::max(1L, std::min((long)cap, want));
 }
 
+// Tiling of a two-sweep launch over an n[0] x n[1] x n[2] level, chosen by an
+// estimate of its time.
+PairTiling pair_tiling(const int n[3], int path, bool zero_in, bool batched)
+{
+    const int V = path == kF64 ? kPairV64 : kPairV32;
+    int lgx = 0;
+    while (lgx < 6 && (V << lgx) < n[0] - 1) ++lgx;
+    const int wx = V << lgx;
+    PairTiling best;
+    best.lgx = lgx;
+    double tbest = 0.0;
+    for (int q = 0; q < kPairNVariants; ++q) {
+        const PairVariant &pv = kPairVariants[q];
+        // sixteen waves leave 128 registers per lane, twelve 168: enough for
+        // FP32 (sixteen only from a zero guess)
+        if (pv.waves >= 12 && (path == kF64 || (pv.waves == 16 && !zero_in))) continue;
+        const int wy = 2 * pv.waves * (64 >> lgx);
+        if (wy <= 8 && wy < n[1] - 1) continue;
+        const int ntx = wx >= n[0] - 1 ? 1 : 1 + ceil_div(n[0] - 1 - wx, wx - 8);
+        const int nty = wy >= n[1] - 1 ? 1 : 1 + ceil_div(n[1] - 1 - wy, wy - 8);
+        const int ns = 5 + pv.depth;
+        const int regs = pv.waves == 16 ? 128 : pv.depth == 1 ? 168 : zero_in ? 128 : 256;
+        const int resident = std::max(1, (512 / regs) * 4 / pv.waves);
+        for (int kz = ns == 8 ? 2 : 6; kz <= kPairMaxKz; kz += ns) {
+            const int ntz = ceil_div(n[2] - 2, kz);
+            const double nwg = (double)ntx * nty * ntz * (batched ? 8.0 : 1.0);
+            const double steps = std::min(kz, n[2] - 2) + 6 + 3;
+            const double per_cu = std::min((double)resident, std::ceil(nwg / 256.0));
+            const double rounds = std::ceil(nwg / (256.0 * per_cu));
+            const double step = std::max(0.45, per_cu * pv.waves / 4.0 * 0.33);
+            const double tm = rounds * steps * step;
+            if (best.var < 0 || tm < tbest) {
+                tbest = tm;
+                best.var = q;
+                best.nt[0] = ntx;
+                best.nt[1] = nty;
+                best.nt[2] = ntz;
+                best.kz = kz;
+            }
+            if (kz >= n[2] - 2) break;
+        }
+    }
+    return best;
+}
+
 bool valid_axis(int n)
 {
     if (n < 5) return false;
@@ -182,6 +227,7 @@ int build_geometry(Hierarchy &h, const int n0[3], const double len[3], bool plan
             lv.st[2] = ceil_div(lv.n[2] - 2, lv.kz);
             lv.kz_b = l == 0 ? lv.kz : chunk(lv.n[2] - 2, lv.st[0] * lv.ity, kKZ, kBatchCoarseTargetGroups);
             lv.stz_b = ceil_div(lv.n[2] - 2, lv.kz_b);
+            for (int q = 0; q < 8; ++q) lv.pair[q >> 2][(q >> 1) & 1][q & 1] = pair_tiling(lv.n, q >> 2, (q >> 1) & 1, q & 1);
         }
         if (l + 1 < L) {
             const Level &c2 = h.lv[l + 1];
@@ -660,11 +706,15 @@ LevelItem level_item(const Hierarchy &h, int l, int path)
     return it;
 }
 
+// Whether sweeps s and s + 1 of a level go into one launch.
+bool pairs(const Hierarchy &h, const void *f) { return h.planar || f; }
+
 void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, const void *uin, void *uout,
                const void *f, const void *ec, int flags, SolveState *state, double *partials)
 {
     LevelItem it = level_item(h, l, path);
     const Level &lv = h.lv[l];
+    const bool pair3 = !h.planar && (flags & kTwoSweeps);
     it.u_in = uin;
     it.u_out = uout;
     it.f = f;
@@ -678,6 +728,14 @@ void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, co
     it.nty = lv.st[1];
     it.ntz = bt ? lv.stz_b : lv.st[2];
     it.kz = bt ? lv.kz_b : lv.kz;
+    const PairTiling &pt = lv.pair[path][(flags & kZeroIn) ? 1 : 0][h.batched ? 1 : 0];
+    if (pair3) {
+        it.lgx = pt.lgx;
+        it.ntx = pt.nt[0];
+        it.nty = pt.nt[1];
+        it.ntz = pt.nt[2];
+        it.kz = pt.kz;
+    }
     it.tile_base = 0;
     const LevelItem *d = st.put(it);
     if (!d) {
@@ -685,8 +743,12 @@ void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, co
         return;
     }
     Launch L{};
-    L.kind = h.planar ? Launch::kSweep2 : Launch::kSweep3;
+    L.kind = h.planar ? Launch::kSweep2 : pair3 ? Launch::kPair3 : Launch::kSweep3;
     L.flags = flags | (f ? kHasF : 0);
+    if (pair3) {
+        if ((flags & kProlong) && lv.keepz) L.flags |= kPairKeepZ;
+        L.flags |= pt.var << kPairVariantShift;
+    }
     L.dbl = path == kF64;
     L.items = d;
     L.nitems = 1;
@@ -865,19 +927,19 @@ void *add_cycle(Program &pg, Staging &st, const Hierarchy &h, int path, void *a0
     const int b = h.b;
     void *cur = a0, *oth = b0;
     // sweeps s0 .. n-1 of level l after the first, ping-pong between c and
-    // o; on the 2D hierarchy two per launch (the launch-bound small planes)
+    // o, two per launch
     auto more = [&](int l, void *&c, void *&o, const void *f, int s0, int n) {
         for (int s = s0; s < n;) {
-            const bool pair = h.planar && s + 1 < n;
+            const bool pair = pairs(h, f) && s + 1 < n;
             add_sweep(pg, st, h, l, path, c, o, f, nullptr, pair ? kTwoSweeps : 0, state, nullptr);
             std::swap(c, o);
             s += pair ? 2 : 1;
         }
     };
-    // the first sweep (flags) and, on the 2D hierarchy, the second with it
-    auto pair_first = [&](int n) { return h.planar && n >= 2 ? kTwoSweeps : 0; };
+    // the first sweep (flags) and the second with it
+    auto pair_first = [&](int n, const void *f) { return pairs(h, f) && n >= 2 ? kTwoSweeps : 0; };
     {
-        int flags = pair_first(nu1);
+        int flags = pair_first(nu1, f0);
         if (first_zero) flags |= kZeroIn;
         if (first_norm) flags |= kNorm;
         add_sweep(pg, st, h, 0, path, cur, oth, f0, nullptr, flags, state, h.partials);
@@ -891,7 +953,7 @@ void *add_cycle(Program &pg, Staging &st, const Hierarchy &h, int path, void *a0
         const Level &lv = h.lv[l];
         void *c = lv.u[path], *o = lv.t[path];
         // first sweep from a zero guess writes lv.u
-        const int fl = kZeroIn | pair_first(nu1);
+        const int fl = kZeroIn | pair_first(nu1, lv.f[path]);
         add_sweep(pg, st, h, l, path, nullptr, c, lv.f[path], nullptr, fl, state, nullptr);
         more(l, c, o, lv.f[path], (fl & kTwoSweeps) ? 2 : 1, nu1);
         lcur[l] = c;
@@ -903,14 +965,14 @@ void *add_cycle(Program &pg, Staging &st, const Hierarchy &h, int path, void *a0
         const Level &lv = h.lv[l];
         void *c = lcur[l];
         void *o = (c == lv.u[path]) ? lv.t[path] : lv.u[path];
-        const int fl = pair_first(nu2);
+        const int fl = pair_first(nu2, lv.f[path]);
         add_correct_sweep(pg, st, h, l, path, c, o, lv.f[path], ec, state, fl);
         std::swap(c, o);
         more(l, c, o, lv.f[path], fl ? 2 : 1, nu2);
         ec = c;
     }
     {
-        const int fl = pair_first(nu2);
+        const int fl = pair_first(nu2, f0);
         add_correct_sweep(pg, st, h, 0, path, cur, oth, f0, ec, state, fl);
         std::swap(cur, oth);
         more(0, cur, oth, f0, fl ? 2 : 1, nu2);
@@ -1054,6 +1116,9 @@ hipError_t exec_launch(const Launch &L, hipStream_t s)
     switch (L.kind) {
     case Launch::kSweep3:
         return launch_sweep3((const LevelItem *)L.items, L.nitems, L.ntiles, L.flags, L.dbl, s);
+    case Launch::kPair3:
+        return launch_pair3((const LevelItem *)L.items, L.nitems, L.ntiles, L.flags & (kPairVariantBit - 1) & ~kTwoSweeps,
+                            L.dbl, L.flags >> kPairVariantShift, s);
     case Launch::kSweep2:
         return launch_sweep2((const LevelItem *)L.items, L.nitems, L.ntiles, L.flags, L.dbl, s);
     case Launch::kRestrict3:
@@ -2045,10 +2110,11 @@ int mhs_stage_smooth(mhs_plan *p, const mhs_model *model, int32_t space, int32_t
     if ((st = begin_staging(p))) return st;
     Program pg;
     void *cur = d_u, *oth = tw;
-    // as in the cycles: on the 2D hierarchy two sweeps per launch
     for (int q = 0; q < nsweeps;) {
         const bool zero = q == 0 && zero_guess;
-        const bool pair = h->planar && q + 1 < nsweeps;
+        // as in the cycles two sweeps per launch (in 3D the kernel takes the
+        // boundary values as zero, which a caller guarantees from a zero guess)
+        const bool pair = (h->planar || zero) && q + 1 < nsweeps;
         add_sweep(pg, p->stage, *h, level, path, zero ? nullptr : cur, oth, d_f, nullptr,
                   (zero ? kZeroIn : 0) | (pair ? kTwoSweeps : 0), nullptr, nullptr);
         std::swap(cur, oth);

@@ -355,6 +355,7 @@ size_t item_size(Launch::Kind k)
 {
     switch (k) {
     case Launch::kSweep3:
+    case Launch::kPair3:
     case Launch::kSweep2:
     case Launch::kRestrict3:
     case Launch::kRestrict2:
@@ -412,6 +413,7 @@ bool merge(Staging &st, const std::vector<const Rec *> &grp, Launch *out)
         std::memcpy(dst, L.items, sz);
         switch (L.kind) {
         case Launch::kSweep3:
+        case Launch::kPair3:
         case Launch::kSweep2:
         case Launch::kRestrict3:
         case Launch::kRestrict2:
@@ -439,6 +441,7 @@ bool merge(Staging &st, const std::vector<const Rec *> &grp, Launch *out)
     }
     switch (first.kind) {
     case Launch::kSweep3:
+    case Launch::kPair3:
     case Launch::kSweep2:
     case Launch::kRestrict3:
     case Launch::kRestrict2:

@@ -112,6 +112,7 @@ struct LevelItem {
     int32_t ntx, nty, ntz; // tiles per axis
     int32_t tile_base;     // first global tile of this item in its launch
     int32_t kz;            // planes per workgroup (smoother: fine planes, restriction: coarse planes)
+    int32_t lgx;           // pair kernel: a row takes 2^lgx lanes of a wave
     int32_t spread;        // read on a launch's first item: 1 = its tiles go to the XCDs in turn
                            // (items of several shapes), 0 = in contiguous ranges per XCD
 };
@@ -215,7 +216,11 @@ enum SweepFlags : int {
     kZeroIn = 2,    // input iterate is zero (first sweep from a zero guess)
     kNorm = 4,      // also write per-tile ||f - A u_in||^2 partials
     kProlong = 8,   // add the interpolated coarse correction to u_in first
-    kTwoSweeps = 16, // two complete sweeps in one launch (2D only)
+    kTwoSweeps = 16, // two complete sweeps in one launch
+    kPairKeepZ = 32, // two sweeps in 3D: the step to the coarse level keeps z
+    // launch flags of the 3D two-sweep kernel carry its variant from this bit on
+    kPairVariantShift = 8,
+    kPairVariantBit = 1 << kPairVariantShift,
 };
 
 // Launch flags of the 3D restriction.
@@ -226,6 +231,17 @@ enum RestrictFlags : int {
 
 hipError_t launch_sweep3(const LevelItem *items, int nitems, int ntiles, int flags, bool dbl,
                          hipStream_t s);
+// Two sweeps per launch.  Variants: waves per workgroup and planes of loads in
+// flight; a thread owns kPairV64 (FP64) or kPairV32 (FP32) x nodes of two rows.
+constexpr int kPairV64 = 2, kPairV32 = 4;
+struct PairVariant {
+    int waves, depth;
+};
+constexpr PairVariant kPairVariants[] = {{12, 1}, {16, 1}, {4, 3}, {8, 3}};
+constexpr int kPairNVariants = 4;
+constexpr int kPairMaxKz = 44; // planes per workgroup (their coefficients sit one plane per lane)
+hipError_t launch_pair3(const LevelItem *items, int nitems, int ntiles, int flags, bool dbl, int variant,
+                        hipStream_t s);
 hipError_t launch_sweep2(const LevelItem *items, int nitems, int ntiles, int flags, bool dbl,
                          hipStream_t s);
 hipError_t launch_restrict3(const LevelItem *items, int nitems, int ntiles, bool has_f, bool keepz, bool dbl,

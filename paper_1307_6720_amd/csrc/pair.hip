@@ -1,0 +1,541 @@
+// Two complete red-black Gauss-Seidel sweeps of a 3D level in one pass over
+// memory.
+#include "device.h"
+
+// Products and sums are contracted within an expression only: a value that an
+// update stored and another one reads is rounded in between, as in memory.
+#pragma clang fp contract(on)
+
+namespace mhs {
+namespace {
+
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+// NW words of 32 bits from / to a plane; an offset at or past the plane's end
+// reads zeros and drops the store.
+template <int NWORD>
+__device__ __forceinline__ void bload_words(uint32_t (&w)[NWORD], __amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff)
+{
+    static_assert(NWORD >= 1 && NWORD <= 4, "at most 16 bytes per load");
+    if constexpr (NWORD == 1) {
+        w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0);
+    } else if constexpr (NWORD == 2) {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0);
+        w[0] = v.x, w[1] = v.y;
+    } else if constexpr (NWORD == 3) {
+        const u32x3 v = __builtin_amdgcn_raw_buffer_load_b96(r, off, soff, 0);
+        w[0] = v.x, w[1] = v.y, w[2] = v.z;
+    } else {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0);
+        w[0] = v.x, w[1] = v.y, w[2] = v.z, w[3] = v.w;
+    }
+}
+template <int N>
+__device__ __forceinline__ void bload_vec(float (&x)[N], __amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff)
+{
+    uint32_t w[N];
+    bload_words<N>(w, r, off, soff);
+#pragma unroll
+    for (int q = 0; q < N; ++q) x[q] = __builtin_bit_cast(float, w[q]);
+}
+template <int N>
+__device__ __forceinline__ void bload_vec(double (&x)[N], __amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff)
+{
+    uint32_t w[2 * N];
+    bload_words<2 * N>(w, r, off, soff);
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const u32x2 v = {w[2 * q], w[2 * q + 1]};
+        x[q] = __builtin_bit_cast(double, v);
+    }
+}
+__device__ __forceinline__ void bstore_vec(const float (&x)[4], __amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    const u32x4 v = {__builtin_bit_cast(uint32_t, x[0]), __builtin_bit_cast(uint32_t, x[1]),
+                     __builtin_bit_cast(uint32_t, x[2]), __builtin_bit_cast(uint32_t, x[3])};
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, 0);
+}
+__device__ __forceinline__ void bstore_vec(const float (&x)[2], __amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    const u32x2 v = {__builtin_bit_cast(uint32_t, x[0]), __builtin_bit_cast(uint32_t, x[1])};
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, 0);
+}
+__device__ __forceinline__ void bstore_vec(const double (&x)[2], __amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    const u32x2 a = __builtin_bit_cast(u32x2, x[0]), b = __builtin_bit_cast(u32x2, x[1]);
+    const u32x4 v = {a.x, a.y, b.x, b.y};
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, 0);
+}
+
+// The value of the lane below / above (0 past the wave's end).
+__device__ __forceinline__ uint32_t dpp_below(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138 /* wave_shr:1 */, 0xf, 0xf, true);
+}
+__device__ __forceinline__ uint32_t dpp_above(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130 /* wave_shl:1 */, 0xf, 0xf, true);
+}
+__device__ __forceinline__ float lane_below(float v)
+{
+    return __builtin_bit_cast(float, dpp_below(__builtin_bit_cast(uint32_t, v)));
+}
+__device__ __forceinline__ float lane_above(float v)
+{
+    return __builtin_bit_cast(float, dpp_above(__builtin_bit_cast(uint32_t, v)));
+}
+__device__ __forceinline__ double lane_below(double v)
+{
+    u32x2 w = __builtin_bit_cast(u32x2, v);
+    w.x = dpp_below(w.x), w.y = dpp_below(w.y);
+    return __builtin_bit_cast(double, w);
+}
+__device__ __forceinline__ double lane_above(double v)
+{
+    u32x2 w = __builtin_bit_cast(u32x2, v);
+    w.x = dpp_above(w.x), w.y = dpp_above(w.y);
+    return __builtin_bit_cast(double, w);
+}
+
+// ============================================================================
+// Two red-black sweeps, ping-pong (u_in -> u_out), columns in registers.
+//
+// A thread owns V consecutive x nodes of two consecutive rows and marches up
+// in z with the last planes of its columns in registers.  A wave covers
+// 64 / LX pairs of rows of LX * V nodes (LX = 2^lgx lanes per row), a
+// workgroup a window of NW * 64 / LX row pairs.  At step s it updates the red
+// nodes of plane s, the black nodes of plane s-1 (first sweep), the red
+// nodes of plane s-2 and the black nodes of plane s-3 (second sweep), then
+// writes plane s-3.  The z neighbours of an update are the thread's own
+// registers, its x neighbours its own or the next lane's (a lane shift), and
+// of its y neighbours one is its own other row: only the outer y neighbour
+// comes through LDS.  Every in-plane neighbour an update of step s reads was
+// final after step s-1 (the red nodes of plane s-1 for the black ones, and so
+// on; the z neighbour updated in the same step is the thread's own), so one
+// barrier per step suffices for the four updates, whose LDS reads are all
+// issued at its start; the published rows are double-buffered.
+//
+// A window not at the edge of the array is right only from its fourth node
+// inwards (each of the four updates moves one node in), so windows overlap by
+// eight nodes and write the part in between; at the edges of the array the
+// boundary nodes are fixed and nothing is lost.  A row of 2^lgx * V + 1 nodes
+// takes a single window in x: its last node, a boundary node, lies one past
+// the window and reads as zero (corrections vanish on the boundary).
+// In z a march starts three planes below the planes it writes and ends three
+// above.
+//
+// Old red values are never read (a Gauss-Seidel update does not use its own
+// old value), so the prolongation is interpolated at the black nodes only.
+//
+// Each value is computed by the same expression as in one sweep at a time
+// (k_sweep3), so the results are those of two launches of that kernel.
+//
+// Why: one sweep moves 12-12.5 bytes per node in FP32 and two launches twice
+// that; here a pair moves them once, and the registers carry what the LDS
+// windows of k_sweep3 carried (per node and sweep 1 LDS read and 1 write
+// instead of 7 and 2, one barrier per plane for both sweeps instead of four).
+// Measured on the two post-smoothing sweeps of a 257^3 level in FP32: 46.5
+// against 95 us for one request; twelve 257^3 equilibria served together take
+// 26.4 against 42.4 ms.  Merged it is bound by memory, alone by its
+// instructions: a window's halo and a march's first and last planes are
+// computed twice.
+// ============================================================================
+template <typename T, int V, int R, int NW, int D, int FLAGS>
+__global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__ items, int nitems)
+{
+    constexpr bool HAS_F = (FLAGS & kHasF) != 0;
+    constexpr bool ZERO_IN = (FLAGS & kZeroIn) != 0;
+    constexpr bool PROLONG = (FLAGS & kProlong) != 0;
+    constexpr bool KEEPZ = (FLAGS & kPairKeepZ) != 0;
+    constexpr int H = V / 2;
+    constexpr int RC = R / 2 + 1; // coarse rows under a thread's rows
+    constexpr int NS = 5 + D; // register slots: planes s-3 .. s+1+D
+    static_assert(NS % 2 == 0, "a round of NS steps keeps the plane's parity");
+    constexpr uint32_t es = sizeof(T);
+    // published rows: one colour of every row of the window (V/2 values per
+    // lane and row), a row of zeros below and above it; four sets (old black
+    // of plane s+1, red of s, black of s-1, red of s-2), two buffers
+    constexpr int kSet = (128 * NW + 128) * H;
+    static_assert(R == 2 || R == 4, "the correction's rows come in pairs");
+    __shared__ T S[8 * kSet];
+
+    const int tile = launch_tile(items, nitems);
+    const LevelItem *it = items + find_item(items, nitems, tile);
+    if (it->state && gin<SolveState>(it->state)->done) return;
+    const MHS_GLOBAL T *__restrict__ uin = gin<T>(it->u_in);
+    MHS_GLOBAL T *__restrict__ uout = gout<T>(it->u_out);
+    const MHS_GLOBAL T *__restrict__ fin = gin<T>(it->f);
+    const MHS_GLOBAL T *__restrict__ ec = gin<T>(it->ec);
+    const MHS_CONST T *__restrict__ coef = gconst<T>(it->coef);
+    const T cz = (T)it->cz;
+    const int nx = it->nx, ny = it->ny, nz = it->nz;
+    const int ncx = it->ncx, ncy = it->ncy, ncz = it->ncz;
+    const int kz = it->kz, lgx = it->lgx;
+    const int LX = 1 << lgx, WX = LX * V, WY = R * NW * (64 >> lgx);
+    int local = tile - it->tile_base;
+    const int tx = local % it->ntx;
+    local /= it->ntx;
+    const int ty = local % it->nty;
+    const int tz = local / it->nty;
+    const bool lastx = tx == it->ntx - 1, lasty = ty == it->nty - 1;
+    const int iw = lastx ? max(nx - 1 - WX, 0) : tx * (WX - 8); // window origin (even)
+    const int jw = lasty ? max(ny - 1 - WY, 0) : ty * (WY - 8);
+    const int xs = tx ? tx * (WX - 8) + 4 : 0, xe = lastx ? nx - 1 : (tx + 1) * (WX - 8) + 4; // nodes written
+    const int ys = ty ? ty * (WY - 8) + 4 : 0, ye = lasty ? ny - 1 : (ty + 1) * (WY - 8) + 4;
+    const int kb = 1 + tz * kz;
+    const int ke = min(kb + kz, nz - 1);
+    const size_t sxy = (size_t)nx * ny, csxy = (size_t)ncx * ncy;
+    const uint32_t plane_bytes = es * (uint32_t)sxy, cplane_bytes = es * (uint32_t)csxy;
+    const int tid = threadIdx.x, lane = tid & 63, lx = lane & (LX - 1);
+    const int t = ((tid >> 6) << (6 - lgx)) + (lane >> lgx); // row pair
+    const int i0 = iw + V * lx, j0 = jw + R * t;
+
+    // ---- per-thread geometry, the same on every plane ------------------------
+    // byte offset of the thread's first row in a plane (a row past the array
+    // lies past the plane's end: it reads as zero), rows are row_bytes apart
+    const uint32_t row_bytes = es * (uint32_t)nx, crow_bytes = es * (uint32_t)ncx;
+    const uint32_t og = es * (uint32_t)(i0 + nx * j0);
+    bool upd[R][2]; // [row][0: node 0 of the lane, 1: the others] interior
+    bool wr[R];     // row written
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int j = j0 + r;
+        upd[r][1] = j >= 1 && j <= ny - 2;
+        upd[r][0] = upd[r][1] && i0 > 0;
+        wr[r] = upd[r][1] && i0 >= xs && i0 < xe && j >= ys && j < ye;
+    }
+    // published rows: the row below the thread's, its first and last, the row
+    // above them, at a0 + 0 .. 3 times the row's length
+    const int LH = LX * H;
+    const int a0 = 2 * t * LH + lx * H;
+    // coarse rows from j0/2, columns i0/2 .. i0/2 + V/2
+    const uint32_t cg = es * (uint32_t)((i0 >> 1) + ncx * (j0 >> 1));
+    // the rows past the window's ends stay zero
+    for (int e = tid; e < 8 * LX * H; e += 64 * NW) {
+        const int set = e / (LX * H), q = e - set * (LX * H);
+        S[set * kSet + q] = (T)0;
+        S[set * kSet + (2 * NW * (64 >> lgx) + 1) * LX * H + q] = (T)0;
+    }
+
+    // planes s0-1 .. (at most 64): cx, cy, 1/d
+    const int s0 = max(kb - 3, 0) & ~1;
+    PlaneTab<T> tcx, tcy, tid_;
+    tcx.load(coef, s0 - 4, 0, nz);
+    tcy.load(coef, s0 - 4, 1, nz);
+    tid_.load(coef, s0 - 4, 3, nz);
+
+    T u[NS][R][V], f[NS][R][V];
+    T dr[R][H]; // red nodes of plane s-4
+    // prolongation: coarse rows interpolated to the thread's two rows, of the
+    // coarse plane below and above; the next coarse plane in flight
+    T ya[R][H + 1], yb[R][H + 1], raw[RC][H + 1];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+        for (int h = 0; h < H; ++h) dr[r][h] = (T)0;
+#pragma unroll
+        for (int q = 0; q < NS; ++q)
+#pragma unroll
+            for (int v = 0; v < V; ++v) u[q][r][v] = f[q][r][v] = (T)0;
+#pragma unroll
+        for (int h = 0; h <= H; ++h) ya[r][h] = yb[r][h] = raw[r / 2][h] = raw[RC - 1][h] = (T)0;
+    }
+
+    auto fetch_u = [&](int p, T(&dst)[R][V]) {
+        if constexpr (!ZERO_IN) {
+            const auto rs = plane_rsrc(uin + sxy * (size_t)min(max(p, 0), nz - 1), plane_bytes);
+#pragma unroll
+            for (int r = 0; r < R; ++r) bload_vec<V>(dst[r], rs, og, r * row_bytes);
+        }
+    };
+    auto fetch_f = [&](int p, T(&dst)[R][V]) {
+        if constexpr (HAS_F) {
+            const auto rs = plane_rsrc(fin + sxy * (size_t)min(max(p, 0), nz - 1), plane_bytes);
+#pragma unroll
+            for (int r = 0; r < R; ++r) bload_vec<V>(dst[r], rs, og, r * row_bytes);
+        }
+    };
+    auto fetch_c = [&](int P) {
+        if constexpr (PROLONG) {
+            const auto rs = plane_rsrc(ec + csxy * (size_t)min(max(P, 0), ncz - 1), cplane_bytes);
+#pragma unroll
+            for (int r = 0; r < RC; ++r) bload_vec<H + 1>(raw[r], rs, cg, r * crow_bytes);
+        }
+    };
+    // yb becomes the in-flight coarse plane, interpolated in y
+    auto take_c = [&]() {
+        if constexpr (PROLONG) {
+#pragma unroll
+            for (int h = 0; h <= H; ++h) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    ya[r][h] = yb[r][h];
+                    yb[r][h] = (r & 1) ? (T)0.5 * (raw[r / 2][h] + raw[r / 2 + 1][h]) : raw[r / 2][h];
+                }
+            }
+        }
+    };
+    // u += I(ec) at the black nodes of a plane of parity par (boundary nodes
+    // get the interpolation of the coarse boundary, zero)
+    auto correct = [&](int par, T(&up)[R][V]) {
+        if constexpr (PROLONG) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int v0 = (r + par + 1) & 1;
+                auto z = [&](int h) -> T {
+                    if (KEEPZ || !par) return yb[r][h];
+                    return (T)0.5 * (ya[r][h] + yb[r][h]);
+                };
+#pragma unroll
+                for (int m = 0; m < H; ++m) {
+                    const int v = v0 + 2 * m;
+                    const T c = v0 ? (T)0.5 * (z(m) + z(m + 1)) : z(m);
+                    up[r][v] += c;
+                }
+            }
+        }
+    };
+    // 1/d of plane p, 0 on the boundary planes: a node that is not updated is a
+    // boundary node, whose value (zero) comes out of the update as zero when
+    // its 1/d is zero
+    struct Coef {
+        T cx, cy, inv;
+    };
+    auto coef_of = [&](int p) {
+        const T cx = tcx(p), cy = tcy(p), inv = tid_(p);
+        return Coef{cx, cy, p >= 1 && p <= nz - 2 ? inv : (T)0};
+    };
+    Coef q[NS]; // of the planes in the slots
+#pragma unroll
+    for (int e = 0; e < NS; ++e) q[e] = Coef{(T)0, (T)0, (T)0};
+    // the outer y neighbours (row below the thread's first, above its last) of
+    // one colour
+    struct Rows {
+        T below[H], above[H];
+    };
+    auto outer = [&](const T *below, const T *above) {
+        Rows y;
+#pragma unroll
+        for (int m = 0; m < H; ++m) {
+            y.below[m] = below[m];
+            y.above[m] = above[m];
+        }
+        return y;
+    };
+    // one colour (0 red, 1 black) of a plane: k its coefficients, uc its columns, uu and ud those
+    // above and below, S rows at rd; par the plane's parity
+    auto colour = [&](const Coef &k, int par, int col, T(&uc)[R][V], const T(&uu)[R][V], const T(&dn)[R][V], const T(&fp)[R][V],
+                      const Rows &y) {
+        const T cx = k.cx, cy = k.cy, invd = k.inv;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int v0 = (r + par + col) & 1;
+            const T inv1 = upd[r][1] ? invd : (T)0, inv0 = v0 ? inv1 : upd[r][0] ? invd : (T)0;
+#pragma unroll
+            for (int m = 0; m < H; ++m) {
+                const int v = v0 + 2 * m;
+                const T e = v + 1 < V ? uc[r][(v + 1) % V] : lane_above(uc[r][0]);
+                const T w = v > 0 ? uc[r][(v + V - 1) % V] : lane_below(uc[r][V - 1]);
+                const T yn = r + 1 < R ? uc[(r + 1) % R][v] : y.above[m];
+                const T ys_ = r > 0 ? uc[(r + R - 1) % R][v] : y.below[m];
+                const T fv = HAS_F ? fp[r][v] : (T)0;
+                const T a = (fv - (cx * (e + w) + cy * (yn + ys_) + cz * (uu[r][v] + dn[r][v]))) * (v ? inv1 : inv0);
+                uc[r][v] = a;
+            }
+        }
+    };
+    auto publish = [&](int par, int col, const T(&uc)[R][V], T *first, T *last) {
+#pragma unroll
+        for (int r = 0; r < R; r += R - 1) {
+            const int v0 = (r + par + col) & 1;
+#pragma unroll
+            for (int m = 0; m < H; ++m) (r ? last : first)[m] = uc[r][v0 + 2 * m];
+        }
+    };
+
+    // one step at plane s; d: its position in the round of NS steps (s0 is
+    // even, so the plane's parity is d's).  Plane s + e lives in slot
+    // (d + e + 3) % NS.
+    auto step = [&](const int s, auto dc) {
+        constexpr int d = decltype(dc)::value;
+        constexpr int P = d & 1, Q = P ^ 1;
+        constexpr int cm3 = d % NS, cm2 = (d + 1) % NS, cm1 = (d + 2) % NS, c0 = (d + 3) % NS, cp1 = (d + 4) % NS;
+        constexpr int cnx = (d + 4 + D) % NS, cnf = (d + 3 + D) % NS;
+        // (the offsets of the two buffers stay in scalar registers: folded
+        // into the addresses they would take a vector register each)
+        int ro = Q * 4 * kSet, wo = P * 4 * kSet;
+        asm volatile("" : "+s"(ro), "+s"(wo));
+        const T *rb = S + (a0 + ro), *ra = S + (a0 + (ro + 3 * LH));
+        T *w0 = S + (a0 + (wo + LH)), *w1 = S + (a0 + (wo + 2 * LH));
+        fetch_u(s + 1 + D, u[cnx]);
+        fetch_f(s + D, f[cnf]);
+        __builtin_amdgcn_sched_barrier(0); // issued before the step's arithmetic
+        // plane s+1 gets its correction (coarse plane (s+2)/2 or, on a step
+        // that keeps z, s+1)
+        if constexpr (PROLONG) {
+            if (KEEPZ || Q) {
+                take_c();
+                fetch_c(KEEPZ ? s + 2 : (s + 4) >> 1);
+            }
+            correct(Q, u[cp1]);
+        }
+        Rows y0{};
+        if constexpr (!ZERO_IN) y0 = outer(rb, ra);
+        const Rows y1 = outer(rb + kSet, ra + kSet), y2 = outer(rb + 2 * kSet, ra + 2 * kSet), y3 = outer(rb + 3 * kSet, ra + 3 * kSet);
+        q[c0] = coef_of(s);
+        // first sweep
+        if constexpr (ZERO_IN) {
+            const T invd = q[c0].inv;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int v0 = (r + P) & 1;
+                const T inv1 = upd[r][1] ? invd : (T)0, inv0 = v0 ? inv1 : upd[r][0] ? invd : (T)0;
+#pragma unroll
+                for (int m = 0; m < H; ++m) {
+                    const int v = v0 + 2 * m;
+                    u[c0][r][v] = f[c0][r][v] * (v ? inv1 : inv0);
+                    // slots are reused: the plane's other nodes start from zero
+                    u[c0][r][v ^ 1] = (T)0;
+                }
+            }
+        } else {
+            colour(q[c0], P, 0, u[c0], u[cp1], u[cm1], f[c0], y0);
+        }
+        colour(q[cm1], Q, 1, u[cm1], u[c0], u[cm2], f[cm1], y1);
+        // second sweep
+        colour(q[cm2], P, 0, u[cm2], u[cm1], u[cm3], f[cm2], y2);
+        {
+            // below plane s-3 only its red nodes are needed, kept in dr
+            T dn[R][V];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int m = 0; m < H; ++m) {
+                    // red of plane s-4 (parity P) sits above / below the
+                    // black nodes of plane s-3 (parity Q): the same columns
+                    const int v = ((r + P) & 1) + 2 * m;
+                    dn[r][v] = dr[r][m];
+                    dn[r][v ^ 1] = (T)0;
+                }
+            colour(q[cm3], Q, 1, u[cm3], u[cm2], dn, f[cm3], y3);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int m = 0; m < H; ++m) dr[r][m] = u[cm3][r][((r + Q) & 1) + 2 * m];
+        }
+        if constexpr (!ZERO_IN) publish(Q, 1, u[cp1], w0, w1);
+        publish(P, 0, u[c0], w0 + kSet, w1 + kSet);
+        publish(Q, 1, u[cm1], w0 + 2 * kSet, w1 + 2 * kSet);
+        publish(P, 0, u[cm2], w0 + 3 * kSet, w1 + 3 * kSet);
+        const int m = s - 3;
+        // (outside the chunk the buffer is empty and drops the stores)
+        const auto rs = plane_rsrc(uout + sxy * (size_t)max(m, 0), m >= kb && m < ke ? plane_bytes : 0u);
+#pragma unroll
+        for (int r = 0; r < R; ++r) bstore_vec(u[cm3][r], rs, wr[r] ? og + r * row_bytes : plane_bytes);
+        lds_barrier();
+        __builtin_amdgcn_sched_barrier(0); // a step's loads stay in it
+    };
+
+    // planes s0-1 .. s0+D into their slots ((p - s0 + 3) % NS)
+#pragma unroll
+    for (int e = -1; e <= D; ++e) {
+        fetch_u(s0 + e, u[(e + 3) % NS]);
+        if (e < D) fetch_f(s0 + e, f[(e + 3) % NS]);
+    }
+    if constexpr (PROLONG) {
+        // coarse planes for s0-1 and s0; the one of s0+1 in flight
+        if constexpr (KEEPZ) {
+            fetch_c(s0 - 1);
+            take_c();
+            correct(1, u[2]);
+            fetch_c(s0);
+            take_c();
+            correct(0, u[3]);
+            fetch_c(s0 + 1);
+        } else {
+            fetch_c((s0 - 1) >> 1);
+            take_c();
+            fetch_c(s0 >> 1);
+            take_c();
+            correct(1, u[2]);
+            correct(0, u[3]);
+            fetch_c((s0 + 2) >> 1);
+        }
+    }
+    // rows that the first step reads before any step has published them must
+    // be finite (what it computes from them is not used, but a boundary node
+    // is kept by a factor of zero)
+#pragma unroll
+    for (int e = 5; e < 8; ++e)
+#pragma unroll
+        for (int m = 0; m < H; ++m) S[e * kSet + a0 + LH + m] = S[e * kSet + a0 + 2 * LH + m] = (T)0;
+    if constexpr (!ZERO_IN) publish(0, 1, u[3], S + 4 * kSet + a0 + LH, S + 4 * kSet + a0 + 2 * LH);
+    lds_barrier();
+    const int send = ke + 2; // the last step writes plane ke - 1
+    for (int s = s0; s <= send; s += NS) {
+        step(s, std::integral_constant<int, 0>{});
+        step(s + 1, std::integral_constant<int, 1>{});
+        step(s + 2, std::integral_constant<int, 2>{});
+        step(s + 3, std::integral_constant<int, 3>{});
+        step(s + 4, std::integral_constant<int, 4>{});
+        step(s + 5, std::integral_constant<int, 5>{});
+        if constexpr (NS == 8) {
+            step(s + 6, std::integral_constant<int, 6>{});
+            step(s + 7, std::integral_constant<int, 7>{});
+        }
+    }
+}
+
+template <typename T, int V, int R, int NW, int D>
+hipError_t pair_dispatch(const LevelItem *items, int nitems, int ntiles, int flags, hipStream_t s)
+{
+    dim3 grid(ntiles), block(64 * NW);
+    switch (flags) {
+#define MHS_CASE(F)                                                                           \
+    case F:                                                                                   \
+        hipLaunchKernelGGL((k_pair3<T, V, R, NW, D, F>), grid, block, 0, s, items, nitems);   \
+        break;
+        MHS_CASE(kHasF) MHS_CASE(kHasF | kProlong) MHS_CASE(kHasF | kProlong | kPairKeepZ) MHS_CASE(kHasF | kZeroIn)
+#undef MHS_CASE
+    default:
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+template <typename T, int V>
+hipError_t pair_variant(const LevelItem *items, int nitems, int ntiles, int flags, int variant, hipStream_t s)
+{
+    static_assert(kPairNVariants == 4, "one case per variant");
+    // instances the tiling does not choose (pair_fits) are not built
+    switch (variant) {
+    case 0:
+        if constexpr (sizeof(T) == 4)
+            return pair_dispatch<T, V, 2, kPairVariants[0].waves, kPairVariants[0].depth>(items, nitems, ntiles, flags, s);
+        break;
+    case 1:
+        if constexpr (sizeof(T) == 4) {
+            if (flags != (kHasF | kZeroIn)) break;
+            hipLaunchKernelGGL((k_pair3<T, V, 2, kPairVariants[1].waves, kPairVariants[1].depth, kHasF | kZeroIn>),
+                               dim3(ntiles), dim3(64 * kPairVariants[1].waves), 0, s, items, nitems);
+            return hipGetLastError();
+        }
+        break;
+    case 2: return pair_dispatch<T, V, 2, kPairVariants[2].waves, kPairVariants[2].depth>(items, nitems, ntiles, flags, s);
+    case 3: return pair_dispatch<T, V, 2, kPairVariants[3].waves, kPairVariants[3].depth>(items, nitems, ntiles, flags, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+} // namespace
+
+hipError_t launch_pair3(const LevelItem *items, int nitems, int ntiles, int flags, bool dbl, int variant, hipStream_t s)
+{
+    if (ntiles <= 0) return hipSuccess;
+    return dbl ? pair_variant<double, kPairV64>(items, nitems, ntiles, flags, variant, s)
+               : pair_variant<float, kPairV32>(items, nitems, ntiles, flags, variant, s);
+}
+
+} // namespace mhs

@@ -33,6 +33,16 @@ struct Carver {
     }
 };
 
+// Tiling of a two-sweep launch (k_pair3): the kernel's variant, 2^lgx lanes
+// per row, tiles per axis and planes per workgroup.
+struct PairTiling {
+    int var = -1; // -1: none
+    int lgx = 0;
+    int nt[3] = {0, 0, 0};
+    int kz = 0;
+    int tiles() const { return nt[0] * nt[1] * nt[2]; }
+};
+
 struct Level {
     int n[3] = {0, 0, 0}; // nx, ny, nz (nz = 1 for the 2D problem)
     double h[3] = {0, 0, 0};
@@ -54,6 +64,9 @@ struct Level {
     int zs = 0;            // xi of plane k is xi[k << zs] of the finest grid
     bool keepz = false;    // the step to level+1 halves x and y only
     bool keepxy = false;   // the step to level+1 halves z only
+    // two-sweep launches, per path, start (zero guess or not) and for a single
+    // request or a batch's merged launches
+    PairTiling pair[2][2][2];
     int ity = 0;           // refinement-step tiles in y (kTY rows; the smoother's are kSTY)
     int sweep_tiles() const { return st[0] * st[1] * st[2]; }
     int ir_tiles() const { return st[0] * ity * st[2]; }
@@ -78,7 +91,7 @@ struct Hierarchy {
 // One kernel launch of a program (the device item table is in the workspace).
 struct Launch {
     enum Kind {
-        kSweep3, kSweep2, kRestrict3, kRestrict2, kIr3, kBottom, kFinalize, kCopy, kFields, kPrep3, kPrep2,
+        kSweep3, kPair3, kSweep2, kRestrict3, kRestrict2, kIr3, kBottom, kFinalize, kCopy, kFields, kPrep3, kPrep2,
         kRestrict3Z, kProlong3Z,
         // the general operator (general.hip): items are GenItem
         kGenSweep, kGenResid, kGenRestrict, kGenProlong, kGenCoarsest, kZero
