@@ -78,26 +78,26 @@ int chunk(int planes, int xy_tiles, int cap, int target = kTargetGroups)
 
 // Tiling of a two-sweep launch over an n[0] x n[1] x n[2] level, chosen by an
 // estimate of its time.
-PairTiling pair_tiling(const int n[3], int path, bool zero_in, bool batched)
+PairTiling pair_tiling(const int n[3], int path, int kind, bool batched)
 {
     const int V = path == kF64 ? kPairV64 : kPairV32;
+    const int ext = kind == kPairDataFaces ? 2 : 0;
+    const int mx = n[0] - 1 + ext, my = n[1] - 1 + ext; // nodes the windows cover
     int lgx = 0;
-    while (lgx < 6 && (V << lgx) < n[0] - 1) ++lgx;
+    while (lgx < 6 && (V << lgx) < mx) ++lgx;
     const int wx = V << lgx;
     PairTiling best;
     best.lgx = lgx;
     double tbest = 0.0;
     for (int q = 0; q < kPairNVariants; ++q) {
         const PairVariant &pv = kPairVariants[q];
-        // sixteen waves leave 128 registers per lane, twelve 168: enough for
-        // FP32 (sixteen only from a zero guess)
-        if (pv.waves >= 12 && (path == kF64 || (pv.waves == 16 && !zero_in))) continue;
+        if (pv.waves == 16 && kind != kPairZero) continue; // not built
         const int wy = 2 * pv.waves * (64 >> lgx);
-        if (wy <= 8 && wy < n[1] - 1) continue;
-        const int ntx = wx >= n[0] - 1 ? 1 : 1 + ceil_div(n[0] - 1 - wx, wx - 8);
-        const int nty = wy >= n[1] - 1 ? 1 : 1 + ceil_div(n[1] - 1 - wy, wy - 8);
+        if (wy <= 8 && wy < my) continue;
+        const int ntx = wx >= mx ? 1 : 1 + ceil_div(mx - wx, wx - 8);
+        const int nty = wy >= my ? 1 : 1 + ceil_div(my - wy, wy - 8);
         const int ns = 5 + pv.depth;
-        const int regs = pv.waves == 16 ? 128 : pv.depth == 1 ? 168 : zero_in ? 128 : 256;
+        const int regs = pv.waves == 16 ? 128 : pv.depth == 1 ? 168 : kind == kPairZero ? 128 : 256;
         const int resident = std::max(1, (512 / regs) * 4 / pv.waves);
         for (int kz = ns == 8 ? 2 : 6; kz <= kPairMaxKz; kz += ns) {
             const int ntz = ceil_div(n[2] - 2, kz);
@@ -227,7 +227,9 @@ int build_geometry(Hierarchy &h, const int n0[3], const double len[3], bool plan
             lv.st[2] = ceil_div(lv.n[2] - 2, lv.kz);
             lv.kz_b = l == 0 ? lv.kz : chunk(lv.n[2] - 2, lv.st[0] * lv.ity, kKZ, kBatchCoarseTargetGroups);
             lv.stz_b = ceil_div(lv.n[2] - 2, lv.kz_b);
-            for (int q = 0; q < 8; ++q) lv.pair[q >> 2][(q >> 1) & 1][q & 1] = pair_tiling(lv.n, q >> 2, (q >> 1) & 1, q & 1);
+            for (int path = 0; path < 2; ++path)
+                for (int k = 0; k < kPairKinds; ++k)
+                    for (int bt = 0; bt < 2; ++bt) lv.pair[path][k][bt] = pair_tiling(lv.n, path, k, bt != 0);
         }
         if (l + 1 < L) {
             const Level &c2 = h.lv[l + 1];
@@ -282,6 +284,8 @@ void carve_hierarchy(Hierarchy &h, Carver &cv, int paths)
     }
     h.minv = cv.take<double>((size_t)h.mcap * h.mcap);
     h.npart = std::max(l0.sweep_tiles(), l0.ir_tiles());
+    if (!h.planar)
+        for (int k : {kPairData, kPairDataFaces}) h.npart = std::max(h.npart, l0.pair[kF64][k][0].tiles());
     h.partials = cv.take<double>(h.npart);
 }
 
@@ -706,9 +710,6 @@ LevelItem level_item(const Hierarchy &h, int l, int path)
     return it;
 }
 
-// Whether sweeps s and s + 1 of a level go into one launch.
-bool pairs(const Hierarchy &h, const void *f) { return h.planar || f; }
-
 void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, const void *uin, void *uout,
                const void *f, const void *ec, int flags, SolveState *state, double *partials)
 {
@@ -728,8 +729,11 @@ void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, co
     it.nty = lv.st[1];
     it.ntz = bt ? lv.stz_b : lv.st[2];
     it.kz = bt ? lv.kz_b : lv.kz;
-    const PairTiling &pt = lv.pair[path][(flags & kZeroIn) ? 1 : 0][h.batched ? 1 : 0];
+    // (the norm's partial sums depend on the tiling: the single request's)
+    const int kind = !f ? (h.faces ? kPairDataFaces : kPairData) : (flags & kZeroIn) ? kPairZero : kPairF;
+    const PairTiling &pt = lv.pair[path][kind][h.batched && !(flags & kNorm) ? 1 : 0];
     if (pair3) {
+        it.ext = kind == kPairDataFaces ? 2 : 0;
         it.lgx = pt.lgx;
         it.ntx = pt.nt[0];
         it.nty = pt.nt[1];
@@ -930,21 +934,21 @@ void *add_cycle(Program &pg, Staging &st, const Hierarchy &h, int path, void *a0
     // o, two per launch
     auto more = [&](int l, void *&c, void *&o, const void *f, int s0, int n) {
         for (int s = s0; s < n;) {
-            const bool pair = pairs(h, f) && s + 1 < n;
+            const bool pair = s + 1 < n;
             add_sweep(pg, st, h, l, path, c, o, f, nullptr, pair ? kTwoSweeps : 0, state, nullptr);
             std::swap(c, o);
             s += pair ? 2 : 1;
         }
     };
     // the first sweep (flags) and the second with it
-    auto pair_first = [&](int n, const void *f) { return pairs(h, f) && n >= 2 ? kTwoSweeps : 0; };
+    auto pair_first = [&](int n) { return n >= 2 ? kTwoSweeps : 0; };
     {
-        int flags = pair_first(nu1, f0);
+        int flags = pair_first(nu1);
         if (first_zero) flags |= kZeroIn;
         if (first_norm) flags |= kNorm;
         add_sweep(pg, st, h, 0, path, cur, oth, f0, nullptr, flags, state, h.partials);
         std::swap(cur, oth);
-        if (first_norm) add_finalize(pg, st, h.partials, h.lv[0].sweep_tiles(), state);
+        if (first_norm) add_finalize(pg, st, h.partials, pg.ok ? pg.launches.back().ntiles : 0, state);
         more(0, cur, oth, f0, (flags & kTwoSweeps) ? 2 : 1, nu1);
     }
     add_restrict(pg, st, h, 0, path, cur, f0, h.lv[1].f[path], state);
@@ -953,7 +957,7 @@ void *add_cycle(Program &pg, Staging &st, const Hierarchy &h, int path, void *a0
         const Level &lv = h.lv[l];
         void *c = lv.u[path], *o = lv.t[path];
         // first sweep from a zero guess writes lv.u
-        const int fl = kZeroIn | pair_first(nu1, lv.f[path]);
+        const int fl = kZeroIn | pair_first(nu1);
         add_sweep(pg, st, h, l, path, nullptr, c, lv.f[path], nullptr, fl, state, nullptr);
         more(l, c, o, lv.f[path], (fl & kTwoSweeps) ? 2 : 1, nu1);
         lcur[l] = c;
@@ -965,14 +969,14 @@ void *add_cycle(Program &pg, Staging &st, const Hierarchy &h, int path, void *a0
         const Level &lv = h.lv[l];
         void *c = lcur[l];
         void *o = (c == lv.u[path]) ? lv.t[path] : lv.u[path];
-        const int fl = pair_first(nu2, lv.f[path]);
+        const int fl = pair_first(nu2);
         add_correct_sweep(pg, st, h, l, path, c, o, lv.f[path], ec, state, fl);
         std::swap(c, o);
         more(l, c, o, lv.f[path], fl ? 2 : 1, nu2);
         ec = c;
     }
     {
-        const int fl = pair_first(nu2, f0);
+        const int fl = pair_first(nu2);
         add_correct_sweep(pg, st, h, 0, path, cur, oth, f0, ec, state, fl);
         std::swap(cur, oth);
         more(0, cur, oth, f0, fl ? 2 : 1, nu2);
@@ -1733,6 +1737,7 @@ int solve_interior_on(mhs_plan *p, const mhs_model *model, double *d_P, const mh
     if ((st = upload_model(p, model, s))) return st;
     if ((st = begin_staging(p))) return st;
     const bool mixed = o->precision == MHS_PREC_MIXED;
+    h.faces = o->faces == MHS_FACES_GIVEN;
     SolveState *d_state = (SolveState *)p->stage.put(initial_state(o->rtol, o->max_cycles));
     double *T0 = (double *)h.lv[0].t[kF64];
     const int64_t N = (int64_t)h.lv[0].N;
@@ -2110,11 +2115,13 @@ int mhs_stage_smooth(mhs_plan *p, const mhs_model *model, int32_t space, int32_t
     if ((st = begin_staging(p))) return st;
     Program pg;
     void *cur = d_u, *oth = tw;
+    h->faces = true; // u's boundary values are data
     for (int q = 0; q < nsweeps;) {
         const bool zero = q == 0 && zero_guess;
-        // as in the cycles two sweeps per launch (in 3D the kernel takes the
-        // boundary values as zero, which a caller guarantees from a zero guess)
-        const bool pair = (h->planar || zero) && q + 1 < nsweeps;
+        // as in the cycles two sweeps per launch (in 3D with a right-hand side
+        // the kernel takes the boundary values as zero, which a caller
+        // guarantees from a zero guess only)
+        const bool pair = (h->planar || zero || (!d_f && path == kF64)) && q + 1 < nsweeps;
         add_sweep(pg, p->stage, *h, level, path, zero ? nullptr : cur, oth, d_f, nullptr,
                   (zero ? kZeroIn : 0) | (pair ? kTwoSweeps : 0), nullptr, nullptr);
         std::swap(cur, oth);

@@ -198,6 +198,7 @@ bool build_slot(const Slot &S, int i, SolveState *state, Staging &R, std::vector
 {
     mhs_plan *p = S.plan;
     BatchedTiling tiling(p->h3);
+    p->h3.faces = S.opts.faces == MHS_FACES_GIVEN;
     const mhs_opts &o = S.opts;
     if (S.phase == kBoundary) {
         Hierarchy &h = p->h2;

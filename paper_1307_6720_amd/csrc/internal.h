@@ -113,6 +113,7 @@ struct LevelItem {
     int32_t tile_base;     // first global tile of this item in its launch
     int32_t kz;            // planes per workgroup (smoother: fine planes, restriction: coarse planes)
     int32_t lgx;           // pair kernel: a row takes 2^lgx lanes of a wave
+    int32_t ext;           // pair kernel: 2 if windows reach past the boundary at the right and upper edge
     int32_t spread;        // read on a launch's first item: 1 = its tiles go to the XCDs in turn
                            // (items of several shapes), 0 = in contiguous ranges per XCD
 };

@@ -141,6 +141,13 @@ __device__ __forceinline__ double lane_above(double v)
 // 26.4 against 42.4 ms.  Merged it is bound by memory, alone by its
 // instructions: a window's halo and a march's first and last planes are
 // computed twice.
+//
+// Level 0 of the FP64 path has no right-hand side but Dirichlet data on its
+// boundary nodes: those keep their values, and where the side faces carry data
+// (ext = 2) the last window of a row or column reaches past the boundary node
+// instead of ending before it.  The first pair of a cycle also sums the
+// residual of its input.  257^3 in FP64, 9 cycles and the fields: 4.46 ms,
+// against 5.22 with single sweeps there.
 // ============================================================================
 template <typename T, int V, int R, int NW, int D, int FLAGS>
 __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__ items, int nitems)
@@ -149,6 +156,12 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     constexpr bool ZERO_IN = (FLAGS & kZeroIn) != 0;
     constexpr bool PROLONG = (FLAGS & kProlong) != 0;
     constexpr bool KEEPZ = (FLAGS & kPairKeepZ) != 0;
+    constexpr bool NORM = (FLAGS & kNorm) != 0;
+    // without a right-hand side the boundary nodes carry data (level 0 of the
+    // FP64 path) and keep their values; with one they are zero
+    constexpr bool DATA = !HAS_F;
+    static_assert(!DATA || V == 2, "the right edge of a window with data is masked per node of a pair");
+    static_assert(!NORM || DATA, "the norm is taken on level 0");
     constexpr int H = V / 2;
     constexpr int RC = R / 2 + 1; // coarse rows under a thread's rows
     constexpr int NS = 5 + D; // register slots: planes s-3 .. s+1+D
@@ -157,9 +170,12 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     // published rows: one colour of every row of the window (V/2 values per
     // lane and row), a row of zeros below and above it; four sets (old black
     // of plane s+1, red of s, black of s-1, red of s-2), two buffers
+    // (with the norm a fifth: old red of plane s+1)
+    constexpr int kSets = NORM ? 5 : 4;
     constexpr int kSet = (128 * NW + 128) * H;
     static_assert(R == 2 || R == 4, "the correction's rows come in pairs");
-    __shared__ T S[8 * kSet];
+    __shared__ T S[2 * kSets * kSet];
+    __shared__ double red[NW];
 
     const int tile = launch_tile(items, nitems);
     const LevelItem *it = items + find_item(items, nitems, tile);
@@ -180,8 +196,9 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     const int ty = local % it->nty;
     const int tz = local / it->nty;
     const bool lastx = tx == it->ntx - 1, lasty = ty == it->nty - 1;
-    const int iw = lastx ? max(nx - 1 - WX, 0) : tx * (WX - 8); // window origin (even)
-    const int jw = lasty ? max(ny - 1 - WY, 0) : ty * (WY - 8);
+    const int ext = DATA ? it->ext : 0;
+    const int iw = lastx ? max(nx - 1 + ext - WX, 0) : tx * (WX - 8); // window origin (even)
+    const int jw = lasty ? max(ny - 1 + ext - WY, 0) : ty * (WY - 8);
     const int xs = tx ? tx * (WX - 8) + 4 : 0, xe = lastx ? nx - 1 : (tx + 1) * (WX - 8) + 4; // nodes written
     const int ys = ty ? ty * (WY - 8) + 4 : 0, ye = lasty ? ny - 1 : (ty + 1) * (WY - 8) + 4;
     const int kb = 1 + tz * kz;
@@ -202,9 +219,10 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int j = j0 + r;
-        upd[r][1] = j >= 1 && j <= ny - 2;
-        upd[r][0] = upd[r][1] && i0 > 0;
-        wr[r] = upd[r][1] && i0 >= xs && i0 < xe && j >= ys && j < ye;
+        const bool row = j >= 1 && j <= ny - 2;
+        upd[r][1] = row && (!DATA || i0 < nx - 2);
+        upd[r][0] = row && i0 > 0 && (!DATA || i0 < nx - 1);
+        wr[r] = row && i0 >= xs && i0 < xe && j >= ys && j < ye;
     }
     // published rows: the row below the thread's, its first and last, the row
     // above them, at a0 + 0 .. 3 times the row's length
@@ -213,7 +231,7 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     // coarse rows from j0/2, columns i0/2 .. i0/2 + V/2
     const uint32_t cg = es * (uint32_t)((i0 >> 1) + ncx * (j0 >> 1));
     // the rows past the window's ends stay zero
-    for (int e = tid; e < 8 * LX * H; e += 64 * NW) {
+    for (int e = tid; e < 2 * kSets * LX * H; e += 64 * NW) {
         const int set = e / (LX * H), q = e - set * (LX * H);
         S[set * kSet + q] = (T)0;
         S[set * kSet + (2 * NW * (64 >> lgx) + 1) * LX * H + q] = (T)0;
@@ -221,10 +239,11 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
 
     // planes s0-1 .. (at most 64): cx, cy, 1/d
     const int s0 = max(kb - 3, 0) & ~1;
-    PlaneTab<T> tcx, tcy, tid_;
+    PlaneTab<T> tcx, tcy, tid_, tdd;
     tcx.load(coef, s0 - 4, 0, nz);
     tcy.load(coef, s0 - 4, 1, nz);
     tid_.load(coef, s0 - 4, 3, nz);
+    if constexpr (NORM) tdd.load(coef, s0 - 4, 2, nz);
 
     T u[NS][R][V], f[NS][R][V];
     T dr[R][H]; // red nodes of plane s-4
@@ -297,6 +316,11 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
             }
         }
     };
+    // a selected, not branched to (the compiler would branch around the update)
+    auto keep_or = [](bool c, T a, T old) -> T {
+        asm volatile("" : "+v"(a));
+        return c ? a : old;
+    };
     // 1/d of plane p, 0 on the boundary planes: a node that is not updated is a
     // boundary node, whose value (zero) comes out of the update as zero when
     // its 1/d is zero
@@ -324,15 +348,17 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         }
         return y;
     };
-    // one colour (0 red, 1 black) of a plane: k its coefficients, uc its columns, uu and ud those
+    // one colour (0 red, 1 black) of plane p: k its coefficients, uc its columns, uu and ud those
     // above and below, S rows at rd; par the plane's parity
-    auto colour = [&](const Coef &k, int par, int col, T(&uc)[R][V], const T(&uu)[R][V], const T(&dn)[R][V], const T(&fp)[R][V],
+    auto colour = [&](int p, const Coef &k, int par, int col, T(&uc)[R][V], const T(&uu)[R][V], const T(&dn)[R][V], const T(&fp)[R][V],
                       const Rows &y) {
         const T cx = k.cx, cy = k.cy, invd = k.inv;
+        const bool in = p >= 1 && p <= nz - 2;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int v0 = (r + par + col) & 1;
-            const T inv1 = upd[r][1] ? invd : (T)0, inv0 = v0 ? inv1 : upd[r][0] ? invd : (T)0;
+            const bool in1 = upd[r][1] && in, in0 = upd[r][0] && in;
+            const T inv1 = DATA ? invd : upd[r][1] ? invd : (T)0, inv0 = DATA || v0 ? inv1 : upd[r][0] ? invd : (T)0;
 #pragma unroll
             for (int m = 0; m < H; ++m) {
                 const int v = v0 + 2 * m;
@@ -342,8 +368,47 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
                 const T ys_ = r > 0 ? uc[(r + R - 1) % R][v] : y.below[m];
                 const T fv = HAS_F ? fp[r][v] : (T)0;
                 const T a = (fv - (cx * (e + w) + cy * (yn + ys_) + cz * (uu[r][v] + dn[r][v]))) * (v ? inv1 : inv0);
-                uc[r][v] = a;
+                uc[r][v] = DATA ? keep_or(v ? in1 : in0, a, uc[r][v]) : a;
             }
+        }
+    };
+    // residual of the input iterate at plane p (all values still old; old red
+    // of the plane below in ro), its outer neighbours yb (black) and yr (red)
+    double acc = 0.0;
+    T ro[R][H];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int h = 0; h < H; ++h) ro[r][h] = (T)0;
+    auto residual = [&](int p, int par, const T(&uc)[R][V], const T(&uu)[R][V], const T(&dn)[R][V], const Rows &yb_,
+                        const Rows &yr) {
+        if constexpr (NORM) {
+            const T cx = tcx(p), cy = tcy(p), dd = tdd(p);
+            const bool in = p >= kb && p < ke;
+#pragma unroll
+            for (int col = 0; col < 2; ++col) {
+                const Rows &y = col ? yr : yb_;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int v0 = (r + par + col) & 1;
+#pragma unroll
+                    for (int m = 0; m < H; ++m) {
+                        const int v = v0 + 2 * m;
+                        const T e = v + 1 < V ? uc[r][(v + 1) % V] : lane_above(uc[r][0]);
+                        const T w = v > 0 ? uc[r][(v + V - 1) % V] : lane_below(uc[r][V - 1]);
+                        const T yn = r + 1 < R ? uc[(r + 1) % R][v] : y.above[m];
+                        const T ys_ = r > 0 ? uc[(r + R - 1) % R][v] : y.below[m];
+                        const T d_ = col ? ro[r][m] : dn[r][v];
+                        const T rv = cx * (e + w) + cy * (yn + ys_) + cz * (uu[r][v] + d_) + dd * uc[r][v];
+                        const double z = in && wr[r] && upd[r][v ? 1 : 0] ? (double)rv : 0.0;
+                        acc += z * z;
+                    }
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int m = 0; m < H; ++m) ro[r][m] = uc[r][((r + par) & 1) + 2 * m];
         }
     };
     auto publish = [&](int par, int col, const T(&uc)[R][V], T *first, T *last) {
@@ -365,9 +430,9 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         constexpr int cnx = (d + 4 + D) % NS, cnf = (d + 3 + D) % NS;
         // (the offsets of the two buffers stay in scalar registers: folded
         // into the addresses they would take a vector register each)
-        int ro = Q * 4 * kSet, wo = P * 4 * kSet;
-        asm volatile("" : "+s"(ro), "+s"(wo));
-        const T *rb = S + (a0 + ro), *ra = S + (a0 + (ro + 3 * LH));
+        int so = Q * kSets * kSet, wo = P * kSets * kSet;
+        asm volatile("" : "+s"(so), "+s"(wo));
+        const T *rb = S + (a0 + so), *ra = S + (a0 + (so + 3 * LH));
         T *w0 = S + (a0 + (wo + LH)), *w1 = S + (a0 + (wo + 2 * LH));
         fetch_u(s + 1 + D, u[cnx]);
         fetch_f(s + D, f[cnf]);
@@ -385,6 +450,7 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         if constexpr (!ZERO_IN) y0 = outer(rb, ra);
         const Rows y1 = outer(rb + kSet, ra + kSet), y2 = outer(rb + 2 * kSet, ra + 2 * kSet), y3 = outer(rb + 3 * kSet, ra + 3 * kSet);
         q[c0] = coef_of(s);
+        if constexpr (NORM) residual(s, P, u[c0], u[cp1], u[cm1], y0, outer(rb + 4 * kSet, ra + 4 * kSet));
         // first sweep
         if constexpr (ZERO_IN) {
             const T invd = q[c0].inv;
@@ -401,11 +467,11 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
                 }
             }
         } else {
-            colour(q[c0], P, 0, u[c0], u[cp1], u[cm1], f[c0], y0);
+            colour(s, q[c0], P, 0, u[c0], u[cp1], u[cm1], f[c0], y0);
         }
-        colour(q[cm1], Q, 1, u[cm1], u[c0], u[cm2], f[cm1], y1);
+        colour(s - 1, q[cm1], Q, 1, u[cm1], u[c0], u[cm2], f[cm1], y1);
         // second sweep
-        colour(q[cm2], P, 0, u[cm2], u[cm1], u[cm3], f[cm2], y2);
+        colour(s - 2, q[cm2], P, 0, u[cm2], u[cm1], u[cm3], f[cm2], y2);
         {
             // below plane s-3 only its red nodes are needed, kept in dr
             T dn[R][V];
@@ -419,13 +485,14 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
                     dn[r][v] = dr[r][m];
                     dn[r][v ^ 1] = (T)0;
                 }
-            colour(q[cm3], Q, 1, u[cm3], u[cm2], dn, f[cm3], y3);
+            colour(s - 3, q[cm3], Q, 1, u[cm3], u[cm2], dn, f[cm3], y3);
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
                 for (int m = 0; m < H; ++m) dr[r][m] = u[cm3][r][((r + Q) & 1) + 2 * m];
         }
         if constexpr (!ZERO_IN) publish(Q, 1, u[cp1], w0, w1);
+        if constexpr (NORM) publish(Q, 0, u[cp1], w0 + 4 * kSet, w1 + 4 * kSet);
         publish(P, 0, u[c0], w0 + kSet, w1 + kSet);
         publish(Q, 1, u[cm1], w0 + 2 * kSet, w1 + 2 * kSet);
         publish(P, 0, u[cm2], w0 + 3 * kSet, w1 + 3 * kSet);
@@ -468,10 +535,17 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     // be finite (what it computes from them is not used, but a boundary node
     // is kept by a factor of zero)
 #pragma unroll
-    for (int e = 5; e < 8; ++e)
+    for (int e = kSets + 1; e < kSets + 4; ++e)
 #pragma unroll
         for (int m = 0; m < H; ++m) S[e * kSet + a0 + LH + m] = S[e * kSet + a0 + 2 * LH + m] = (T)0;
-    if constexpr (!ZERO_IN) publish(0, 1, u[3], S + 4 * kSet + a0 + LH, S + 4 * kSet + a0 + 2 * LH);
+    if constexpr (!ZERO_IN) publish(0, 1, u[3], S + kSets * kSet + a0 + LH, S + kSets * kSet + a0 + 2 * LH);
+    if constexpr (NORM) {
+        publish(0, 0, u[3], S + (kSets + 4) * kSet + a0 + LH, S + (kSets + 4) * kSet + a0 + 2 * LH);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int m = 0; m < H; ++m) ro[r][m] = u[2][r][((r + 1) & 1) + 2 * m]; // old red of plane s0-1
+    }
     lds_barrier();
     const int send = ke + 2; // the last step writes plane ke - 1
     for (int s = s0; s <= send; s += NS) {
@@ -486,45 +560,48 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
             step(s + 7, std::integral_constant<int, 7>{});
         }
     }
+    if constexpr (NORM) {
+        const double tot = block_sum<64 * NW>(acc, red);
+        if (tid == 0) gout<double>(it->partials)[tile - it->tile_base] = tot;
+    }
 }
 
-template <typename T, int V, int R, int NW, int D>
+template <typename T, int V, int NW, int D>
 hipError_t pair_dispatch(const LevelItem *items, int nitems, int ntiles, int flags, hipStream_t s)
 {
     dim3 grid(ntiles), block(64 * NW);
-    switch (flags) {
 #define MHS_CASE(F)                                                                           \
     case F:                                                                                   \
-        hipLaunchKernelGGL((k_pair3<T, V, R, NW, D, F>), grid, block, 0, s, items, nitems);   \
-        break;
-        MHS_CASE(kHasF) MHS_CASE(kHasF | kProlong) MHS_CASE(kHasF | kProlong | kPairKeepZ) MHS_CASE(kHasF | kZeroIn)
-#undef MHS_CASE
-    default:
-        return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_pair3<T, V, 2, NW, D, F>), grid, block, 0, s, items, nitems);   \
+        return hipGetLastError();
+    switch (flags) {
+        MHS_CASE(kHasF | kZeroIn)
     }
-    return hipGetLastError();
+    // sixteen waves leave 128 registers per lane, too few for the others
+    if constexpr (NW < 16) {
+        switch (flags) {
+            MHS_CASE(kHasF) MHS_CASE(kHasF | kProlong) MHS_CASE(kHasF | kProlong | kPairKeepZ)
+        }
+        // level 0 of the FP64 path
+        if constexpr (sizeof(T) == 8) {
+            switch (flags) {
+                MHS_CASE(0) MHS_CASE(kNorm) MHS_CASE(kProlong) MHS_CASE(kProlong | kPairKeepZ)
+            }
+        }
+    }
+#undef MHS_CASE
+    return hipErrorInvalidValue;
 }
 
 template <typename T, int V>
 hipError_t pair_variant(const LevelItem *items, int nitems, int ntiles, int flags, int variant, hipStream_t s)
 {
     static_assert(kPairNVariants == 4, "one case per variant");
-    // instances the tiling does not choose (pair_fits) are not built
     switch (variant) {
-    case 0:
-        if constexpr (sizeof(T) == 4)
-            return pair_dispatch<T, V, 2, kPairVariants[0].waves, kPairVariants[0].depth>(items, nitems, ntiles, flags, s);
-        break;
-    case 1:
-        if constexpr (sizeof(T) == 4) {
-            if (flags != (kHasF | kZeroIn)) break;
-            hipLaunchKernelGGL((k_pair3<T, V, 2, kPairVariants[1].waves, kPairVariants[1].depth, kHasF | kZeroIn>),
-                               dim3(ntiles), dim3(64 * kPairVariants[1].waves), 0, s, items, nitems);
-            return hipGetLastError();
-        }
-        break;
-    case 2: return pair_dispatch<T, V, 2, kPairVariants[2].waves, kPairVariants[2].depth>(items, nitems, ntiles, flags, s);
-    case 3: return pair_dispatch<T, V, 2, kPairVariants[3].waves, kPairVariants[3].depth>(items, nitems, ntiles, flags, s);
+#define MHS_VAR(N) \
+    case N: return pair_dispatch<T, V, kPairVariants[N].waves, kPairVariants[N].depth>(items, nitems, ntiles, flags, s);
+        MHS_VAR(0) MHS_VAR(1) MHS_VAR(2) MHS_VAR(3)
+#undef MHS_VAR
     }
     return hipErrorInvalidValue;
 }

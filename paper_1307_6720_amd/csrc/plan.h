@@ -43,6 +43,12 @@ struct PairTiling {
     int tiles() const { return nt[0] * nt[1] * nt[2]; }
 };
 
+// Kinds of two-sweep launches with a tiling of their own: with a right-hand
+// side, the same from a zero guess, and without one (level 0 of the FP64 path,
+// whose boundary nodes carry data) when the data on the side faces are zero
+// or given.
+enum PairKind : int { kPairF = 0, kPairZero = 1, kPairData = 2, kPairDataFaces = 3, kPairKinds = 4 };
+
 struct Level {
     int n[3] = {0, 0, 0}; // nx, ny, nz (nz = 1 for the 2D problem)
     double h[3] = {0, 0, 0};
@@ -64,9 +70,9 @@ struct Level {
     int zs = 0;            // xi of plane k is xi[k << zs] of the finest grid
     bool keepz = false;    // the step to level+1 halves x and y only
     bool keepxy = false;   // the step to level+1 halves z only
-    // two-sweep launches, per path, start (zero guess or not) and for a single
-    // request or a batch's merged launches
-    PairTiling pair[2][2][2];
+    // two-sweep launches, per path, kind (PairKind) and for a single request
+    // or a batch's merged launches
+    PairTiling pair[2][kPairKinds][2];
     int ity = 0;           // refinement-step tiles in y (kTY rows; the smoother's are kSTY)
     int sweep_tiles() const { return st[0] * st[1] * st[2]; }
     int ir_tiles() const { return st[0] * ity * st[2]; }
@@ -81,6 +87,7 @@ struct Hierarchy {
     int mcap = 0;           // largest coarsest-grid size the inverse buffer holds
     Level lv[kMaxLevels];
     int lds_bytes = 0;      // bottom solver LDS footprint
+    bool faces = false;     // the side faces carry data (mhs_opts.faces): builders of level 0 of the FP64 path
     bool batched = false;   // builders record launches for merging (z-chunking kz_b, kc_b)
     double *minv = nullptr; // device m x m
     int m = 0;              // coarsest unknowns

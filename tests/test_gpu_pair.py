@@ -42,3 +42,31 @@ def test_two_sweeps_in_one_launch_equal_two_launches(S, dims, precision):
         plan.stage_smooth(model, 3, level, one, f, 1, precision, zero_guess=True)
         plan.stage_smooth(model, 3, level, one, f, 1, precision)
         assert torch.equal(one, two), f"level {level} {shape}"
+
+
+@pytest.mark.parametrize("dims", [(9, 9, 9), (17, 9, 33), (33, 33, 33), (65, 129, 33), (129, 65, 65), (257, 33, 9),
+                                  (33, 257, 17)])
+def test_two_sweeps_with_boundary_data_equal_two_launches(S, dims):
+    lengths = [n - 1.0 for n in dims]
+    g = synth.make_grid(*dims, *lengths)
+    plan = S.Plan(g, 1)
+    model = synth.make_model(g, 0.01, 0.5, 0.2 * lengths[2])
+    rng = np.random.default_rng(6)
+    two = torch.from_numpy(rng.standard_normal(plan.shape)).to("cuda")
+    one = two.clone()
+    plan.stage_smooth(model, 3, 0, two, None, 2)
+    plan.stage_smooth(model, 3, 0, one, None, 1)
+    plan.stage_smooth(model, 3, 0, one, None, 1)
+    assert torch.equal(one, two)
+
+
+def test_two_fp32_sweeps_without_a_right_hand_side(S):
+    g = synth.make_grid(33, 17, 33, 32.0, 16.0, 32.0)
+    plan = S.Plan(g, 2)
+    model = synth.make_model(g, 0.01, 0.5, 6.0)
+    two = torch.from_numpy(np.random.default_rng(7).standard_normal(plan.shape)).to("cuda", torch.float32)
+    one = two.clone()
+    plan.stage_smooth(model, 3, 0, two, None, 2, 2)
+    plan.stage_smooth(model, 3, 0, one, None, 1, 2)
+    plan.stage_smooth(model, 3, 0, one, None, 1, 2)
+    assert torch.equal(one, two)
