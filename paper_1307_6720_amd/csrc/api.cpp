@@ -70,6 +70,12 @@ size_t bottom_lds(const Hierarchy &h, int l)
     return 8 * (n + h.lv[l].N);
 }
 
+// Pairs of x nodes the threads of the bottom solver own on a level.
+int bottom_pairs(const Level &lv, bool planar)
+{
+    return (lv.n[0] - 1) / 2 * (lv.n[1] - 2) * (planar ? 1 : lv.n[2] - 2);
+}
+
 int chunk(int planes, int xy_tiles, int cap, int target = kTargetGroups)
 {
     const long want = ((long)planes * xy_tiles + target - 1) / target;
@@ -192,7 +198,7 @@ int build_geometry(Hierarchy &h, const int n0[3], const double len[3], bool plan
         return fail(MHS_ERR_GRID, "coarsest grid has %d unknowns (max %d): axes too unequal", h.m, kMaxCoarse);
     h.b = -1;
     for (int l = 1; l < L; ++l)
-        if (bottom_lds(h, l) <= (size_t)kBottomLdsMax) {
+        if (bottom_lds(h, l) <= (size_t)kBottomLdsMax && bottom_pairs(h.lv[l], planar) <= kBottomMaxPairs) {
             h.b = l;
             break;
         }
@@ -501,7 +507,7 @@ int set_depth(Hierarchy &h, int L)
                     "has %d unknowns (max %d)", t.m, t.mcap);
     t.b = -1;
     for (int l = 1; l < L; ++l)
-        if (bottom_lds(t, l) <= (size_t)kBottomLdsMax) {
+        if (bottom_lds(t, l) <= (size_t)kBottomLdsMax && bottom_pairs(t.lv[l], t.planar) <= kBottomMaxPairs) {
             t.b = l;
             break;
         }
@@ -823,6 +829,8 @@ BottomItem bottom_item(const Hierarchy &h, int path, const void *f_top, void *u_
         b.coef[q] = h.lv[l].coef64;
         b.cz[q] = h.lv[l].cz;
         for (int a = 0; a < 3; ++a) b.n[q][a] = h.lv[l].n[a];
+        const uint32_t my = (uint32_t)(h.lv[l].n[1] - 2);
+        b.inv[q] = my == 1 ? 0u : (uint32_t)(((1ull << 32) + my - 1) / my);
         b.off_u[q] = off;
         off += (int)h.lv[l].N;
         b.off_f[q] = off;

@@ -80,6 +80,8 @@ constexpr int kFY = MHS_FIELDS_TILE_Y;
 constexpr int kFThreads = MHS_FIELDS_THREADS;
 // bottom solver: one workgroup per item.
 constexpr int kBottomThreads = 1024;
+// pairs of x nodes a level of the bottom solver may have (three per thread)
+constexpr int kBottomMaxPairs = 3 * kBottomThreads;
 // largest coarsest-grid system solved by the dense inverse
 constexpr int kMaxCoarse = 1024;
 
@@ -130,6 +132,7 @@ struct BottomItem {
     int32_t off_u[kMaxLevels];    // LDS offsets (doubles)
     int32_t off_f[kMaxLevels];
     int32_t off_c[kMaxLevels];    // LDS copy of the level's coefficient table (4 * nz)
+    uint32_t inv[kMaxLevels];     // ceil(2^32 / (ny - 2)), 0 for ny = 3: r / (ny - 2) = high word of r * inv
     int32_t off_r;
     int32_t nlev;
     int32_t m;                    // unknowns of the coarsest grid

@@ -16,31 +16,6 @@
 namespace mhs {
 namespace {
 
-// Trilinear interpolation of the coarse correction at fine node (i, j, k):
-// coincident nodes copy, edge/face/cell midpoints average 2/4/8 values.
-template <typename T, typename Ptr>
-__device__ __forceinline__ T interp3(Ptr ec, int ncx, int ncy, int i, int j, int k)
-{
-    const size_t sy = (size_t)ncx, sz = (size_t)ncx * ncy;
-    const Ptr p = ec + (size_t)(i >> 1) + sy * (size_t)(j >> 1) + sz * (size_t)(k >> 1);
-    const int oi = i & 1, oj = j & 1, ok = k & 1;
-    const T h = (T)0.5;
-    auto X = [&](Ptr q) -> T { return oi ? h * (q[0] + q[1]) : (T)q[0]; };
-    auto Y = [&](Ptr q) -> T { return oj ? h * (X(q) + X(q + sy)) : X(q); };
-    return ok ? h * (Y(p) + Y(p + sz)) : Y(p);
-}
-
-template <typename T, typename Ptr>
-__device__ __forceinline__ T interp2(Ptr ec, int ncx, int i, int j)
-{
-    const size_t sy = (size_t)ncx;
-    const Ptr p = ec + (size_t)(i >> 1) + sy * (size_t)(j >> 1);
-    const int oi = i & 1, oj = j & 1;
-    const T h = (T)0.5;
-    auto X = [&](Ptr q) -> T { return oi ? h * (q[0] + q[1]) : (T)q[0]; };
-    return oj ? h * (X(p) + X(p + sy)) : X(p);
-}
-
 // ============================================================================
 // 3D red-black Gauss-Seidel sweep, ping-pong (u_in -> u_out).
 //
@@ -1244,189 +1219,6 @@ __global__ __launch_bounds__(kThreads) void k_ir3(const LevelItem *__restrict__ 
 }
 
 // ============================================================================
-// Bottom solver: one workgroup runs a whole V(nu1,nu2) cycle over the small
-// levels of one request, from a zero initial guess, in FP64, with exact
-// red-black Gauss-Seidel ordering (a barrier between colours) and an exact
-// dense solve on the coarsest grid.  Every work array lives in LDS (up to
-// 160 KB on gfx950), so each phase costs LDS latency, not HBM latency.
-// ============================================================================
-// Threads of the bottom solver work row by row: a row is the interior nodes
-// (j, k) fixed, i running; `cnt` nodes of a row go to a power-of-two group
-// of 2^lg lanes and the workgroup covers 1024 / 2^lg rows at a time, so
-// node coordinates come from shifts and one small division per row.
-__device__ __forceinline__ int ceil_log2(int v) { return v <= 1 ? 0 : 32 - __clz(v - 1); }
-
-template <typename Fn>
-__device__ __forceinline__ void bottom_rows(int cnt, int my, int nrows, Fn &&fn)
-{
-    const int lg = ceil_log2(cnt);
-    if ((1 << lg) > kBottomThreads) { // rows longer than the workgroup
-        for (int r = 0; r < nrows; ++r) {
-            const int kk = r / my;
-            for (int q = (int)threadIdx.x; q < cnt; q += kBottomThreads) fn(q, r - kk * my, kk);
-        }
-        return;
-    }
-    const int q = (int)threadIdx.x & ((1 << lg) - 1);
-    if (q >= cnt) return;
-    for (int r = (int)threadIdx.x >> lg; r < nrows; r += kBottomThreads >> lg) {
-        const int kk = r / my;
-        fn(q, r - kk * my, kk);
-    }
-}
-
-// One colour of red-black Gauss-Seidel on level l (colour = (i + j + k) & 1).
-__device__ __forceinline__ void bottom_colour(double *smem, const BottomItem &b, int l, bool planar, int colour)
-{
-    const int nx = b.n[l][0], ny = b.n[l][1], nz = b.n[l][2];
-    const int mx = nx - 2, my = ny - 2, mz = planar ? 1 : nz - 2;
-    double *u = smem + b.off_u[l];
-    const double *f = smem + b.off_f[l];
-    const double *cf = smem + b.off_c[l];
-    const double cz = b.cz[l];
-    const int sxy = nx * ny;
-    bottom_rows((mx + 1) >> 1, my, my * mz, [&](int q, int jj, int kk) {
-        const int j = jj + 1, k = planar ? 0 : kk + 1;
-        const int i = 1 + ((j + k + 1 + colour) & 1) + 2 * q;
-        if (i > mx) return;
-        const int idx = i + nx * j + sxy * k;
-        double off = cf[4 * k] * (u[idx + 1] + u[idx - 1]) + cf[4 * k + 1] * (u[idx + nx] + u[idx - nx]);
-        if (!planar) off += cz * (u[idx + sxy] + u[idx - sxy]);
-        u[idx] = (f[idx] - off) * cf[4 * k + 3];
-    });
-}
-
-__device__ __forceinline__ void bottom_smooth(double *smem, const BottomItem &b, int l, bool planar, int nsweeps)
-{
-    for (int s = 0; s < nsweeps; ++s) {
-        bottom_colour(smem, b, l, planar, 0);
-        lds_barrier();
-        bottom_colour(smem, b, l, planar, 1);
-        lds_barrier();
-    }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBottomThreads) void k_bottom(const BottomItem *__restrict__ items, int nitems)
-{
-    extern __shared__ double smem[];
-    const BottomItem &b = items[blockIdx.x];
-    if (b.state && gin<SolveState>(b.state)->done) return;
-    const bool planar = b.planar != 0;
-    const int tid = threadIdx.x;
-    const int L = b.nlev;
-    double *r = smem + b.off_r;
-    // every level's u = 0 and f (the top level's from global memory), and
-    // the coefficient tables, into LDS
-    for (int l = 0; l < L; ++l) {
-        const int N = b.n[l][0] * b.n[l][1] * b.n[l][2];
-        double *u = smem + b.off_u[l];
-        double *f = smem + b.off_f[l];
-        const MHS_GLOBAL T *ft = gin<T>(b.f_top);
-        for (int e = tid; e < N; e += kBottomThreads) {
-            u[e] = 0.0;
-            f[e] = (l == 0) ? (double)ft[e] : 0.0;
-        }
-        const int nc = 4 * b.n[l][2];
-        const MHS_GLOBAL double *cg = gin<double>(b.coef[l]);
-        for (int e = tid; e < nc; e += kBottomThreads) smem[b.off_c[l] + e] = cg[e];
-    }
-    lds_barrier();
-    for (int l = 0; l < L - 1; ++l) {
-        const int nx = b.n[l][0], ny = b.n[l][1], nz = b.n[l][2];
-        const int sxy = nx * ny;
-        const int mx = nx - 2, my = ny - 2, mz = planar ? 1 : nz - 2;
-        bottom_smooth(smem, b, l, planar, b.nu1);
-        // residual on interior nodes
-        {
-            const double *u = smem + b.off_u[l];
-            const double *f = smem + b.off_f[l];
-            const double *cf = smem + b.off_c[l];
-            const double cz = b.cz[l];
-            bottom_rows(mx, my, my * mz, [&](int q, int jj, int kk) {
-                const int i = q + 1, j = jj + 1, k = planar ? 0 : kk + 1;
-                const int idx = i + nx * j + sxy * k;
-                double au = cf[4 * k] * (u[idx + 1] + u[idx - 1]) + cf[4 * k + 1] * (u[idx + nx] + u[idx - nx]) +
-                            cf[4 * k + 2] * u[idx];
-                if (!planar) au += cz * (u[idx + sxy] + u[idx - sxy]);
-                r[idx] = f[idx] - au;
-            });
-        }
-        lds_barrier();
-        // full weighting onto the interior of level l+1 (within planes when
-        // the step keeps z)
-        {
-            const int cnx = b.n[l + 1][0], cny = b.n[l + 1][1], cnz = b.n[l + 1][2];
-            const bool zc = !planar && cnz < nz; // the step halves z
-            const bool xyc = cnx < nx;           // the step halves x and y
-            double *fc = smem + b.off_f[l + 1];
-            const int cmx = cnx - 2, cmy = cny - 2, cmz = planar ? 1 : cnz - 2;
-            bottom_rows(cmx, cmy, cmy * cmz, [&](int q, int jj, int kk) {
-                const int I = q + 1, J = jj + 1, K = planar ? 0 : kk + 1;
-                const int fidx = (xyc ? 2 * I : I) + nx * (xyc ? 2 * J : J) + sxy * (zc ? 2 * K : K);
-                auto row = [&](int c) { return 0.25 * r[c - 1] + 0.5 * r[c] + 0.25 * r[c + 1]; };
-                auto pl = [&](int c) { return xyc ? 0.25 * row(c - nx) + 0.5 * row(c) + 0.25 * row(c + nx) : r[c]; };
-                const double v = !zc ? pl(fidx) : 0.25 * pl(fidx - sxy) + 0.5 * pl(fidx) + 0.25 * pl(fidx + sxy);
-                fc[I + cnx * J + cnx * cny * K] = v;
-            });
-        }
-        lds_barrier();
-    }
-    // exact solve on the coarsest grid: u = Minv f over interior nodes
-    {
-        const int nx = b.n[L - 1][0], ny = b.n[L - 1][1];
-        const int mx = nx - 2, my = ny - 2;
-        const int sxy = nx * ny;
-        const int m = b.m;
-        double *u = smem + b.off_u[L - 1];
-        const double *f = smem + b.off_f[L - 1];
-        for (int p = tid; p < m; p += kBottomThreads) {
-            double acc = 0.0;
-            for (int q = 0; q < m; ++q) {
-                const int qi = q % mx, qr = q / mx;
-                const int qj = qr % my, qk = qr / my;
-                const int fidx = (qi + 1) + nx * (qj + 1) + sxy * (planar ? 0 : qk + 1);
-                acc += gin<double>(b.minv)[(size_t)p * m + q] * f[fidx];
-            }
-            const int pi = p % mx, pr = p / mx;
-            const int pj = pr % my, pk = pr / my;
-            u[(pi + 1) + nx * (pj + 1) + sxy * (planar ? 0 : pk + 1)] = acc;
-        }
-        lds_barrier();
-    }
-    for (int l = L - 2; l >= 0; --l) {
-        const int nx = b.n[l][0], ny = b.n[l][1], nz = b.n[l][2];
-        const int cnx = b.n[l + 1][0], cny = b.n[l + 1][1];
-        const bool zc = !planar && b.n[l + 1][2] < nz;
-        const bool xyc = cnx < nx;
-        const int sxy = nx * ny;
-        const int mx = nx - 2, my = ny - 2, mz = planar ? 1 : nz - 2;
-        double *u = smem + b.off_u[l];
-        const double *ec = smem + b.off_u[l + 1];
-        bottom_rows(mx, my, my * mz, [&](int q, int jj, int kk) {
-            const int i = q + 1, j = jj + 1, k = planar ? 0 : kk + 1;
-            double v;
-            if (xyc) {
-                v = zc ? interp3<double>(ec, cnx, cny, i, j, k)
-                       : interp2<double>(ec + (size_t)cnx * cny * k, cnx, i, j);
-            } else { // x and y kept: linear along z
-                const double *e0 = ec + i + nx * j + sxy * (k >> 1);
-                v = (k & 1) ? 0.5 * e0[0] + 0.5 * e0[sxy] : e0[0];
-            }
-            u[i + nx * j + sxy * k] += v;
-        });
-        lds_barrier();
-        bottom_smooth(smem, b, l, planar, b.nu2);
-    }
-    {
-        const int N0 = b.n[0][0] * b.n[0][1] * b.n[0][2];
-        const double *u = smem + b.off_u[0];
-        MHS_GLOBAL T *ut = gout<T>(b.u_top);
-        for (int e = tid; e < N0; e += kBottomThreads) ut[e] = (T)u[e];
-    }
-}
-
-// ============================================================================
 // Convergence check: fixed-order sum of the per-tile partials, then the
 // stopping rule ||r_c|| <= rtol ||r_0|| (or divergence, or the cap).
 // ============================================================================
@@ -2205,28 +1997,6 @@ hipError_t launch_ir3(const LevelItem *items, int nitems, int ntiles, bool has_e
         hipLaunchKernelGGL((k_ir3<false, true>), grid, block, 0, s, items, nitems);
     else
         hipLaunchKernelGGL((k_ir3<false, false>), grid, block, 0, s, items, nitems);
-    return hipGetLastError();
-}
-
-hipError_t launch_bottom(const BottomItem *items, int nitems, int lds_bytes, bool dbl, hipStream_t s)
-{
-    if (nitems <= 0) return hipSuccess;
-    if (lds_bytes <= 0 || lds_bytes > kBottomLdsMax) return hipErrorInvalidValue;
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bottom<double>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kBottomLdsMax);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bottom<float>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kBottomLdsMax);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    dim3 grid(nitems), block(kBottomThreads);
-    if (dbl)
-        hipLaunchKernelGGL((k_bottom<double>), grid, block, lds_bytes, s, items, nitems);
-    else
-        hipLaunchKernelGGL((k_bottom<float>), grid, block, lds_bytes, s, items, nitems);
     return hipGetLastError();
 }
 
