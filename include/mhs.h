@@ -137,7 +137,7 @@ const char *mhs_last_error(void);
 
 /* Bytes of device workspace a plan for `grid` needs.  `precisions` is a
  * bit mask of MHS_PREC_* paths the plan must support (at least one), plus
- * MHS_PLAN_GENERAL for the general-operator entry points (about 3.4 more
+ * MHS_PLAN_GENERAL for the general-operator entry points (about 3.6 more
  * doubles per node of the grid, and the same for its faces).  Validates the grid
  * (MHS_ERR_GRID for a bad axis). */
 int mhs_workspace_bytes(const mhs_grid *grid, int32_t precisions, size_t *bytes);

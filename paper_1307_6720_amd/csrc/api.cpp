@@ -83,8 +83,8 @@ int chunk(int planes, int xy_tiles, int cap, int target = kTargetGroups)
 }
 
 // Tiling of a two-sweep launch over an n[0] x n[1] x n[2] level, chosen by an
-// estimate of its time.
-PairTiling pair_tiling(const int n[3], int path, int kind, bool batched)
+// estimate of its time among variants of at most max_waves waves.
+PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max_waves)
 {
     const int V = path == kF64 ? kPairV64 : kPairV32;
     const int ext = kind == kPairDataFaces ? 2 : 0;
@@ -97,7 +97,7 @@ PairTiling pair_tiling(const int n[3], int path, int kind, bool batched)
     double tbest = 0.0;
     for (int q = 0; q < kPairNVariants; ++q) {
         const PairVariant &pv = kPairVariants[q];
-        if (pv.waves == 16 && kind != kPairZero) continue; // not built
+        if (pv.waves > max_waves || (pv.waves == 16 && kind != kPairZero)) continue; // not built
         const int wy = 2 * pv.waves * (64 >> lgx);
         if (wy <= 8 && wy < my) continue;
         const int ntx = wx >= mx ? 1 : 1 + ceil_div(mx - wx, wx - 8);
@@ -235,7 +235,7 @@ int build_geometry(Hierarchy &h, const int n0[3], const double len[3], bool plan
             lv.stz_b = ceil_div(lv.n[2] - 2, lv.kz_b);
             for (int path = 0; path < 2; ++path)
                 for (int k = 0; k < kPairKinds; ++k)
-                    for (int bt = 0; bt < 2; ++bt) lv.pair[path][k][bt] = pair_tiling(lv.n, path, k, bt != 0);
+                    for (int bt = 0; bt < 2; ++bt) lv.pair[path][k][bt] = pair_tiling(lv.n, path, k, bt != 0, 16);
         }
         if (l + 1 < L) {
             const Level &c2 = h.lv[l + 1];
@@ -829,8 +829,6 @@ BottomItem bottom_item(const Hierarchy &h, int path, const void *f_top, void *u_
         b.coef[q] = h.lv[l].coef64;
         b.cz[q] = h.lv[l].cz;
         for (int a = 0; a < 3; ++a) b.n[q][a] = h.lv[l].n[a];
-        const uint32_t my = (uint32_t)(h.lv[l].n[1] - 2);
-        b.inv[q] = my == 1 ? 0u : (uint32_t)(((1ull << 32) + my - 1) / my);
         b.off_u[q] = off;
         off += (int)h.lv[l].N;
         b.off_f[q] = off;
@@ -1135,9 +1133,9 @@ hipError_t exec_launch(const Launch &L, hipStream_t s)
         return launch_sweep2((const LevelItem *)L.items, L.nitems, L.ntiles, L.flags, L.dbl, s);
     case Launch::kRestrict3:
         return launch_restrict3((const LevelItem *)L.items, L.nitems, L.ntiles, (L.flags & kRestrictHasF) != 0,
-                                (L.flags & kRestrictKeepZ) != 0, L.dbl, s);
+                                (L.flags & kRestrictKeepZ) != 0, (L.flags & kRestrictGen) != 0, L.dbl, s);
     case Launch::kRestrict2:
-        return launch_restrict2((const LevelItem *)L.items, L.nitems, L.ntiles, L.dbl, s);
+        return launch_restrict2((const LevelItem *)L.items, L.nitems, L.ntiles, (L.flags & kRestrictGen) != 0, L.dbl, s);
     case Launch::kRestrict3Z:
         return launch_restrict3_z((const LevelItem *)L.items, L.nitems, L.ntiles, (L.flags & kRestrictHasF) != 0,
                                   L.dbl, s);
@@ -1146,7 +1144,7 @@ hipError_t exec_launch(const Launch &L, hipStream_t s)
     case Launch::kIr3:
         return launch_ir3((const LevelItem *)L.items, L.nitems, L.ntiles, (L.flags & 1) != 0, (L.flags & 2) != 0, s);
     case Launch::kBottom:
-        return launch_bottom((const BottomItem *)L.items, L.nitems, L.lds, L.dbl, s);
+        return launch_bottom((const BottomItem *)L.items, L.nitems, L.lds, L.flags != 0, L.dbl, s);
     case Launch::kFinalize:
         return launch_finalize((const FinalizeItem *)L.items, L.nitems, s);
     case Launch::kCopy:
@@ -1161,7 +1159,6 @@ hipError_t exec_launch(const Launch &L, hipStream_t s)
     case Launch::kGenResid:
     case Launch::kGenRestrict:
     case Launch::kGenProlong:
-    case Launch::kGenCoarsest:
         return gen_exec(L, s);
     case Launch::kZero:
         return launch_zero(L.dst, (size_t)L.n, s);

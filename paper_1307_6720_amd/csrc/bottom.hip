@@ -44,7 +44,7 @@ __device__ __forceinline__ double &at_byte(int off) { return *(double *)((char *
 
 struct BottomLevel {
     int nx, sxy, lg, cnt, rows, my;
-    uint32_t inv;
+    float rmy; // 1 / my
     int u, f, cf; // byte offsets in LDS
     double cz;
 };
@@ -58,7 +58,7 @@ __device__ __forceinline__ BottomLevel bottom_level(const BottomItem &b, int l)
     v.lg = 30 - __builtin_clz((unsigned)(nx - 1)); // 2^lg = (nx - 1) / 2 pairs per row
     v.cnt = 1 << v.lg;
     v.my = ny - 2;
-    v.inv = b.inv[l];
+    v.rmy = 1.0f / (float)v.my;
     v.rows = v.my * (b.planar ? 1 : nz - 2);
     v.u = 8 * b.off_u[l];
     v.f = 8 * b.off_f[l];
@@ -76,6 +76,10 @@ __device__ __forceinline__ void bottom_sync()
     else
         lds_barrier();
 }
+
+// a / d for 0 <= a < 2^20, r = 1.0f / d: (a + 1/2) / d is at least 1/(2d) away
+// from an integer, and the product off by less than that.
+__device__ __forceinline__ int bottom_div(int a, float r) { return (int)(((float)a + 0.5f) * r); }
 
 // Place of column i in a row of a level with cnt pairs per row: odd columns
 // first.
@@ -97,7 +101,7 @@ __device__ __forceinline__ double bottom_weighted(int c, int o, int ry, int rz, 
 __device__ __forceinline__ void bottom_node(const BottomLevel &L, int p, bool planar, int &I, int &J, int &K)
 {
     const int mx = L.nx - 2;
-    const int pr = p / mx, pk = L.inv ? (int)__umulhi((uint32_t)pr, L.inv) : pr; // pr / my
+    const int pr = p / mx, pk = bottom_div(pr, L.rmy);
     I = 1 + p - pr * mx;
     J = 1 + pr - pk * L.my;
     K = planar ? 0 : pk + 1;
@@ -178,7 +182,8 @@ __device__ __forceinline__ void bottom_tables(const BottomItem &b)
 }
 
 // The pairs of one thread on one level, by colour (0 red, 1 black).
-template <bool PLANAR, int NP, bool WAVE>
+// GEN: the general operator, whose diagonal differs from node to node.
+template <bool PLANAR, int NP, bool WAVE, bool GEN>
 struct BottomPairs {
     BottomLevel L;
     int r;                      // byte offset of the residual
@@ -187,7 +192,9 @@ struct BottomPairs {
     int st[NP][2];              // where the node is stored
     bool on[NP][2], pair[NP];   // an interior node; the pair exists
     bool busy;                  // the wave has pairs
-    double u[NP][2], f[NP][2], c0[NP], c1[NP], cd[NP], c3[NP];
+    double u[NP][2], f[NP][2], c0[NP], c1[NP];
+    double cd[NP][GEN ? 2 : 1], c3[NP][GEN ? 2 : 1]; // diagonal and its inverse
+    double be[NP][GEN ? 2 : 1];                      // b/a
 
     __device__ __forceinline__ BottomPairs(const BottomItem &b, int l) : L(bottom_level(b, l)), r(8 * b.off_r)
     {
@@ -200,7 +207,7 @@ struct BottomPairs {
             pair[p] = row < L.rows;
             any |= pair[p];
             const int rr = pair[p] ? row : 0;
-            const int kk = PLANAR ? 0 : L.inv ? (int)__umulhi((uint32_t)rr, L.inv) : rr; // rr / my
+            const int kk = PLANAR ? 0 : bottom_div(rr, L.rmy);
             j[p] = 1 + rr - kk * L.my;
             k[p] = PLANAR ? 0 : kk + 1;
             const int s = (j[p] + k[p] + 1) & 1; // the red node is the pair's first (0) or second
@@ -217,6 +224,13 @@ struct BottomPairs {
             }
         }
         busy = WAVE || __any(any);
+        if constexpr (GEN) {
+            const MHS_GLOBAL double *bg = gin<double>(b.beta[l]);
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) be[p][c] = bg[i[p][c] + L.nx * j[p] + L.sxy * k[p]];
+        }
     }
     // coefficients and right-hand side from LDS, and u (on the way up)
     __device__ __forceinline__ void load(bool with_u)
@@ -227,8 +241,16 @@ struct BottomPairs {
             const int c = L.cf + 32 * k[p];
             c0[p] = at_byte(c);
             c1[p] = at_byte(c + 8);
-            cd[p] = at_byte(c + 16);
-            c3[p] = at_byte(c + 24);
+            if constexpr (GEN) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    cd[p][h] = be[p][h] + at_byte(c + 16);
+                    c3[p][h] = 1.0 / cd[p][h];
+                }
+            } else {
+                cd[p][0] = at_byte(c + 16);
+                c3[p][0] = at_byte(c + 24);
+            }
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 f[p][h] = at_byte(at[p][h] + (L.f - L.u));
@@ -258,7 +280,7 @@ struct BottomPairs {
         if (busy) {
             double v[NP];
 #pragma unroll
-            for (int p = 0; p < NP; ++p) v[p] = (f[p][C] - neighbours(p, C)) * c3[p];
+            for (int p = 0; p < NP; ++p) v[p] = (f[p][C] - neighbours(p, C)) * c3[p][GEN ? C : 0];
             set(C, v);
         }
         bottom_sync<WAVE>();
@@ -278,7 +300,7 @@ struct BottomPairs {
         if (busy) {
             double v[NP];
 #pragma unroll
-            for (int p = 0; p < NP; ++p) v[p] = f[p][0] * c3[p];
+            for (int p = 0; p < NP; ++p) v[p] = f[p][0] * c3[p][0];
             set(0, v);
         }
         bottom_sync<WAVE>();
@@ -292,7 +314,7 @@ struct BottomPairs {
                 for (int c = 0; c < 2; ++c) {
                     const int a = at[p][c], ry = 8 * L.nx, rz = 8 * L.sxy;
                     double au = c0[p] * (at_byte(ext[p][c]) + u[p][1 - c]) +
-                                c1[p] * (at_byte(a + ry) + at_byte(a - ry)) + cd[p] * u[p][c];
+                                c1[p] * (at_byte(a + ry) + at_byte(a - ry)) + cd[p][GEN ? c : 0] * u[p][c];
                     if constexpr (!PLANAR) au += L.cz * (at_byte(a + rz) + at_byte(a - rz));
                     v[p][c] = f[p][c] - au;
                 }
@@ -327,19 +349,19 @@ struct BottomPairs {
     }
 };
 
-template <bool PLANAR, int NP, bool WAVE>
+template <bool PLANAR, int NP, bool WAVE, bool GEN>
 __device__ __forceinline__ void bottom_down(const BottomItem &b, int l)
 {
-    BottomPairs<PLANAR, NP, WAVE> P(b, l);
+    BottomPairs<PLANAR, NP, WAVE, GEN> P(b, l);
     bottom_restrict<PLANAR, WAVE>(b, l, P.L, false);
     P.load(false);
     P.down(b.nu1);
 }
 
-template <bool PLANAR, int NP, bool WAVE>
+template <bool PLANAR, int NP, bool WAVE, bool GEN>
 __device__ __forceinline__ void bottom_up(const BottomItem &b, int l)
 {
-    BottomPairs<PLANAR, NP, WAVE> P(b, l);
+    BottomPairs<PLANAR, NP, WAVE, GEN> P(b, l);
     P.load(true);
     const BottomLevel C = bottom_level(b, l + 1);
     P.correct(C, C.nx < P.L.nx, !PLANAR && b.n[l + 1][2] < b.n[l][2]);
@@ -348,12 +370,12 @@ __device__ __forceinline__ void bottom_up(const BottomItem &b, int l)
 
 // The cycle over levels of at most NP pairs per thread; false if the solve
 // was done (nothing has been computed then).
-template <typename T, bool PLANAR, int NP>
+template <typename T, bool GEN, bool PLANAR, int NP>
 __device__ __forceinline__ bool bottom_cycle(const BottomItem &b)
 {
     const int n = b.nlev;
     {
-        BottomPairs<PLANAR, NP, false> P(b, 0);
+        BottomPairs<PLANAR, NP, false, GEN> P(b, 0);
         const MHS_GLOBAL T *ft = gin<T>(b.f_top);
         const int done = b.state ? gin<SolveState>(b.state)->done : 0;
         T ftop[NP][2];
@@ -376,16 +398,16 @@ __device__ __forceinline__ bool bottom_cycle(const BottomItem &b)
     int l = 1;
     for (; l < n - 1 && pairs(l) > 64; ++l) {
         if (pairs(l) <= kBottomThreads)
-            bottom_down<PLANAR, 1, false>(b, l);
+            bottom_down<PLANAR, 1, false, GEN>(b, l);
         else
-            bottom_down<PLANAR, 3, false>(b, l);
+            bottom_down<PLANAR, 3, false, GEN>(b, l);
     }
     const int w = l; // the first level that one wave runs
     if (w < n - 1) {
         if (threadIdx.x < 64) {
-            for (; l < n - 1; ++l) bottom_down<PLANAR, 1, true>(b, l);
+            for (; l < n - 1; ++l) bottom_down<PLANAR, 1, true, GEN>(b, l);
             bottom_coarsest<T, PLANAR, true>(b);
-            for (l = n - 2; l >= w; --l) bottom_up<PLANAR, 1, true>(b, l);
+            for (l = n - 2; l >= w; --l) bottom_up<PLANAR, 1, true, GEN>(b, l);
         }
         lds_barrier();
     } else {
@@ -393,15 +415,15 @@ __device__ __forceinline__ bool bottom_cycle(const BottomItem &b)
     }
     for (l = w - 1; l > 0; --l) {
         if (pairs(l) <= kBottomThreads)
-            bottom_up<PLANAR, 1, false>(b, l);
+            bottom_up<PLANAR, 1, false, GEN>(b, l);
         else
-            bottom_up<PLANAR, 3, false>(b, l);
+            bottom_up<PLANAR, 3, false, GEN>(b, l);
     }
-    bottom_up<PLANAR, NP, false>(b, 0);
+    bottom_up<PLANAR, NP, false, GEN>(b, 0);
     return true;
 }
 
-template <typename T, bool PLANAR>
+template <typename T, bool GEN, bool PLANAR>
 __device__ __forceinline__ bool bottom_solve(const BottomItem &b)
 {
     const int pairs = ((b.n[0][0] - 1) >> 1) * (b.n[0][1] - 2) * (PLANAR ? 1 : b.n[0][2] - 2);
@@ -410,12 +432,12 @@ __device__ __forceinline__ bool bottom_solve(const BottomItem &b)
         bottom_coarsest<T, PLANAR, false>(b);
         return true;
     }
-    if (pairs <= kBottomThreads) return bottom_cycle<T, PLANAR, 1>(b);
-    if (pairs <= 2 * kBottomThreads) return bottom_cycle<T, PLANAR, 2>(b);
-    return bottom_cycle<T, PLANAR, 3>(b);
+    if (pairs <= kBottomThreads) return bottom_cycle<T, GEN, PLANAR, 1>(b);
+    if (pairs <= 2 * kBottomThreads) return bottom_cycle<T, GEN, PLANAR, 2>(b);
+    return bottom_cycle<T, GEN, PLANAR, 3>(b);
 }
 
-template <typename T>
+template <typename T, bool GEN>
 __global__ __launch_bounds__(kBottomThreads) void k_bottom(const BottomItem *__restrict__ items, int nitems, int lds_bytes)
 {
     const BottomItem &b = items[blockIdx.x];
@@ -430,38 +452,40 @@ __global__ __launch_bounds__(kBottomThreads) void k_bottom(const BottomItem *__r
     }
     for (int e = (int)threadIdx.x; e < lds_bytes / 8; e += kBottomThreads) smem[e] = 0.0;
     lds_barrier();
-    if (!(b.planar ? bottom_solve<T, true>(b) : bottom_solve<T, false>(b))) return;
+    if (!(b.planar ? bottom_solve<T, GEN, true>(b) : bottom_solve<T, GEN, false>(b))) return;
     const int nx = b.n[0][0], N0 = nx * b.n[0][1] * b.n[0][2];
     const double *u = smem + b.off_u[0];
     MHS_GLOBAL T *ut = gout<T>(b.u_top);
-    const float rnx = 1.0f / (float)nx; // exact row numbers: e is far below 2^20
+    const float rnx = 1.0f / (float)nx;
     for (int e = (int)threadIdx.x; e < N0; e += kBottomThreads) {
-        const int row = (int)(((float)e + 0.5f) * rnx);
+        const int row = bottom_div(e, rnx);
         ut[e] = (T)u[row * nx + bottom_col(e - row * nx, (nx - 1) >> 1)];
     }
 }
 
 } // namespace
 
-hipError_t launch_bottom(const BottomItem *items, int nitems, int lds_bytes, bool dbl, hipStream_t s)
+hipError_t launch_bottom(const BottomItem *items, int nitems, int lds_bytes, bool gen, bool dbl, hipStream_t s)
 {
     if (nitems <= 0) return hipSuccess;
-    if (lds_bytes <= 0 || lds_bytes > kBottomLdsMax) return hipErrorInvalidValue;
+    if (lds_bytes <= 0 || lds_bytes > kBottomLdsMax || (gen && !dbl)) return hipErrorInvalidValue;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bottom<double>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kBottomLdsMax);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bottom<float>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kBottomLdsMax);
-        if (e != hipSuccess) return e;
+        for (const void *k : {reinterpret_cast<const void *>(&k_bottom<double, false>),
+                              reinterpret_cast<const void *>(&k_bottom<float, false>),
+                              reinterpret_cast<const void *>(&k_bottom<double, true>)}) {
+            const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kBottomLdsMax);
+            if (e != hipSuccess) return e;
+        }
         attr_set = true;
     }
     dim3 grid(nitems), block(kBottomThreads);
-    if (dbl)
-        hipLaunchKernelGGL((k_bottom<double>), grid, block, lds_bytes, s, items, nitems, lds_bytes);
+    if (gen)
+        hipLaunchKernelGGL((k_bottom<double, true>), grid, block, lds_bytes, s, items, nitems, lds_bytes);
+    else if (dbl)
+        hipLaunchKernelGGL((k_bottom<double, false>), grid, block, lds_bytes, s, items, nitems, lds_bytes);
     else
-        hipLaunchKernelGGL((k_bottom<float>), grid, block, lds_bytes, s, items, nitems, lds_bytes);
+        hipLaunchKernelGGL((k_bottom<float, false>), grid, block, lds_bytes, s, items, nitems, lds_bytes);
     return hipGetLastError();
 }
 

@@ -5,19 +5,27 @@
 //     lap_h u + beta u = gamma,  beta = b/a,  gamma = c/a,
 // which has the same discrete solution.
 //
-// Unlike the solve of (8), whose coefficients depend on z only and live in
-// per-plane tables, every stage here reads per-node beta, so the kernels are
-// one thread per node (or per node of one colour), reading neighbours
-// through the caches: each level's arrays are streamed once or twice per
-// stage and the coarse levels are small.  The hierarchy (shapes and which
-// axes a step halves) is the one of (8), so the grid transfers are the same
-// full weighting and linear interpolation, applied per axis.
+// The cycle runs on the kernels of the solve of (8) in their variants with a
+// diagonal per node: two sweeps per pass (k_pair3 in the box, k_sweep2 on a
+// face), residual and restriction fused, the small levels in the bottom
+// solver; the coarsest operator is inverted once per solve.  Sweeps that are
+// left over from an odd count, and the transfers of a step that keeps x and y,
+// have plain kernels here, one thread per node.  The hierarchy (shapes and
+// which axes a step halves) is the one of (8), so the grid transfers are the
+// same full weighting and linear interpolation, applied per axis.
+//
+// Measured on a 257^3 unit box to rtol 1e-10 (9 cycles): 5.9 ms, against
+// 17.2 ms with a launch per colour and per stage (each of the two colour
+// launches of a sweep touched every line of u, b/a and the right-hand side);
+// a 129 x 65 face 0.41 against 1.33 ms.  Level 0 is bound by memory: a pair of
+// sweeps moves 32 bytes per node in 173 us (198 with the prolongation).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <vector>
 
 #include "plan.h"
 
@@ -33,9 +41,11 @@ struct GenItem {
     double *f;           // right-hand side gamma (level 0: c / a)
     double *beta;        // b / a (sampled at this level's nodes)
     double *r;           // residual of this level (for the restriction)
-    double *uc, *fc;     // next coarser level: iterate and right-hand side
+    const double *uc;    // next coarser level: iterate
+    double *fc;          // next coarser level: right-hand side
     double *betac;       // next coarser level: beta (filled by the prep)
     const double *a, *b, *c; // level 0 prep: the caller's coefficients
+    double *twin;        // level 0 prep: receives u's boundary values
     SolveState *state;   // stages are skipped once state->done != 0
     double *partials;    // per-block sums (norm) or {max beta, bad count} (prep)
     double cx, cy, cz;   // 1 / h^2 per axis (cz = 0 on a face)
@@ -50,8 +60,11 @@ struct GenHier {
     bool ok = false;        // geometry built
     double *u0 = nullptr;   // faces: level-0 iterate (a copy of the face)
     double *u[kMaxLevels] = {}, *f[kMaxLevels] = {}, *beta[kMaxLevels] = {}, *r[kMaxLevels] = {};
+    double *t[kMaxLevels] = {}; // ping-pong partner of u
+    double *minv = nullptr;     // inverse of the coarsest operator
     double *partials = nullptr;
     int npart = 0;
+    PairTiling pair[kMaxLevels][2]; // two-sweep launches: without and with the prolongation
 };
 
 struct GenPlan {
@@ -93,30 +106,35 @@ __device__ __forceinline__ int64_t gen_interior(const GenItem &it)
 }
 
 // Level 0: beta = b/a and gamma = c/a on interior nodes (0 elsewhere), the
-// interior of u zeroed unless warm-started; per block the largest beta and
-// the number of interior nodes whose a vanishes or whose a, b, c are not
-// finite.
+// interior of u zeroed unless warm-started, its boundary values copied to the
+// ping-pong partner; per block the largest beta and the number of interior
+// nodes whose a vanishes or whose a, b, c are not finite.  A bounded number of
+// blocks, so that the reduction of their results is short (with one block per
+// 256 nodes it took 96 us at 257^3).
+constexpr int kGenPrepBlocks = 2048;
 __global__ __launch_bounds__(kGenThreads) void k_gen_prep(const GenItem *__restrict__ itp)
 {
     __shared__ double red[kGenThreads / 64];
     const GenItem &it = *itp;
-    const int64_t N = (int64_t)it.nx * it.ny * it.nz;
-    const int64_t e = (int64_t)blockIdx.x * kGenThreads + threadIdx.x;
+    const uint32_t N = (uint32_t)it.nx * (uint32_t)it.ny * (uint32_t)it.nz;
     double bmax = -INFINITY, bad = 0.0;
-    if (e < N) {
-        const int i = (int)(e % it.nx);
-        const int64_t q = e / it.nx;
-        const int j = (int)(q % it.ny), k = (int)(q / it.ny);
+    for (uint32_t e = blockIdx.x * kGenThreads + threadIdx.x; e < N; e += gridDim.x * kGenThreads) {
+        const uint32_t q = e / (uint32_t)it.nx;
+        const int i = (int)(e - q * (uint32_t)it.nx);
+        const uint32_t kq = q / (uint32_t)it.ny;
+        const int j = (int)(q - kq * (uint32_t)it.ny), k = (int)kq;
         const bool in = i >= 1 && i <= it.nx - 2 && j >= 1 && j <= it.ny - 2 &&
                         (it.planar ? k == 0 : (k >= 1 && k <= it.nz - 2));
         double be = 0.0, ge = 0.0;
         if (in) {
             const double av = it.a[e], bv = it.b[e], cv = it.c[e];
-            if (!(av != 0.0 && isfinite(av) && isfinite(bv) && isfinite(cv))) bad = 1.0;
+            if (!(av != 0.0 && isfinite(av) && isfinite(bv) && isfinite(cv))) bad += 1.0;
             be = bv / av;
             ge = cv / av;
-            bmax = be;
+            bmax = fmax(bmax, be);
             if (!it.warm) it.u[e] = 0.0;
+        } else {
+            it.twin[e] = it.u[e];
         }
         it.beta[e] = be;
         it.f[e] = ge;
@@ -288,16 +306,14 @@ __global__ __launch_bounds__(kGenThreads) void k_gen_prolong(const GenItem *__re
     it.u[i + (int64_t)it.nx * j + (int64_t)it.nx * it.ny * k] += s;
 }
 
-// Exact solve of the coarsest grid (zero boundary values): the dense
-// operator of its m interior unknowns assembled in LDS, Gaussian elimination
-// (the negated operator is positive definite, so no pivoting), then back
-// substitution.  One workgroup.
-__global__ __launch_bounds__(kGenThreads) void k_gen_coarsest(const GenItem *__restrict__ itp)
+// Inverse of the coarsest grid's operator (zero boundary values) over its m
+// interior unknowns, by Gauss-Jordan elimination in LDS (the negated operator
+// is positive definite, so no pivoting).  One workgroup, once per solve.
+__global__ __launch_bounds__(kGenThreads) void k_gen_inverse(const GenItem *__restrict__ itp, double *__restrict__ minv)
 {
     const GenItem &it = *itp;
-    if (gen_skip(it)) return;
     __shared__ double M[kGenMaxCoarse * kGenMaxCoarse];
-    __shared__ double rhs[kGenMaxCoarse], lf[kGenMaxCoarse];
+    __shared__ double row[kGenMaxCoarse], col[kGenMaxCoarse];
     const int mx = it.nx - 2, my = it.ny - 2, mz = it.planar ? 1 : it.nz - 2;
     const int m = mx * my * mz;
     const int k0 = it.planar ? 0 : 1;
@@ -315,32 +331,22 @@ __global__ __launch_bounds__(kGenThreads) void k_gen_coarsest(const GenItem *__r
         if (j < it.ny - 2) M[r * m + r + mx] = it.cy;
         if (!it.planar && k > 1) M[r * m + r - mx * my] = it.cz;
         if (!it.planar && k < it.nz - 2) M[r * m + r + mx * my] = it.cz;
-        rhs[r] = it.f[e];
     }
     __syncthreads();
     for (int p = 0; p < m; ++p) {
-        for (int r = p + 1 + threadIdx.x; r < m; r += kGenThreads) lf[r] = M[r * m + p] / M[p * m + p];
-        __syncthreads();
-        const int w = m - p; // columns p .. m-1
-        for (int e = threadIdx.x; e < (m - p - 1) * w; e += kGenThreads) {
-            const int r = p + 1 + e / w, c = p + e % w;
-            M[r * m + c] -= lf[r] * M[p * m + c];
+        const double d = 1.0 / M[p * m + p];
+        for (int c = threadIdx.x; c < m; c += kGenThreads) {
+            row[c] = (c == p ? 1.0 : M[p * m + c]) * d;
+            col[c] = M[c * m + p];
         }
-        for (int r = p + 1 + threadIdx.x; r < m; r += kGenThreads) rhs[r] -= lf[r] * rhs[p];
+        __syncthreads();
+        for (int e = threadIdx.x; e < m * m; e += kGenThreads) {
+            const int r = e / m, c = e - r * m;
+            M[e] = r == p ? row[c] : (c == p ? 0.0 : M[e]) - col[r] * row[c];
+        }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        for (int r = m - 1; r >= 0; --r) {
-            double s = rhs[r];
-            for (int c = r + 1; c < m; ++c) s -= M[r * m + c] * rhs[c];
-            rhs[r] = s / M[r * m + r];
-        }
-    }
-    __syncthreads();
-    for (int r = threadIdx.x; r < m; r += kGenThreads) {
-        const int i = 1 + r % mx, j = 1 + (r / mx) % my, k = k0 + r / (mx * my);
-        it.u[i + (int64_t)it.nx * j + sxy * k] = rhs[r];
-    }
+    for (int e = threadIdx.x; e < m * m; e += kGenThreads) minv[e] = M[e];
 }
 
 // Face of the box <-> a contiguous (n2, n1) array: gather (to_face = 0)
@@ -395,9 +401,6 @@ hipError_t gen_exec(const Launch &L, hipStream_t s)
     case Launch::kGenProlong:
         hipLaunchKernelGGL(k_gen_prolong, dim3(nb), dim3(kGenThreads), 0, s, it);
         break;
-    case Launch::kGenCoarsest:
-        hipLaunchKernelGGL(k_gen_coarsest, dim3(1), dim3(kGenThreads), 0, s, it);
-        break;
     default:
         return hipErrorInvalidValue;
     }
@@ -420,11 +423,20 @@ void carve_gen(GenHier &g, Carver &cv, bool face)
     for (int l = 0; l < h.L; ++l) {
         const size_t N = h.lv[l].N;
         if (l > 0) g.u[l] = cv.take<double>(N);
+        if (l < h.b) g.t[l] = cv.take<double>(N);
         g.f[l] = cv.take<double>(N);
         g.beta[l] = cv.take<double>(N);
-        if (l + 1 < h.L) g.r[l] = cv.take<double>(N);
+        if (l < h.b && h.lv[l].keepxy) g.r[l] = cv.take<double>(N);
+        if (l < h.b && !h.planar) {
+            g.pair[l][0] = pair_tiling(h.lv[l].n, kF64, l == 0 ? kPairDataFaces : kPairF, false, 12);
+            // (twelve waves leave too few registers for the coarse data as well)
+            g.pair[l][1] = pair_tiling(h.lv[l].n, kF64, l == 0 ? kPairDataFaces : kPairF, false, 8);
+        }
     }
-    g.npart = (int)std::max<int64_t>(blocks_for((int64_t)h.lv[0].N), blocks_for(interior_count(h.lv[0], h.planar)));
+    const int m = std::min(h.m, kGenMaxCoarse); // (larger coarsest grids are refused)
+    g.minv = cv.take<double>((size_t)m * m);
+    g.npart = std::max((int)std::max<int64_t>(kGenPrepBlocks, blocks_for(interior_count(h.lv[0], h.planar))),
+                       std::max(g.pair[0][0].tiles(), h.lv[0].sweep_tiles()));
     g.partials = cv.take<double>(2 * (size_t)g.npart + 2);
 }
 
@@ -440,7 +452,8 @@ double lap_lambda_min(const Level &lv, bool planar)
     return s;
 }
 
-GenItem level_item(const GenHier &g, int l, double *u, SolveState *state)
+// Level l as the plain kernels see it; uc: the coarser level's iterate.
+GenItem gen_item(const GenHier &g, int l, double *u, const double *uc, SolveState *state)
 {
     const Hierarchy &h = g.geo;
     const Level &lv = h.lv[l];
@@ -460,7 +473,7 @@ GenItem level_item(const GenHier &g, int l, double *u, SolveState *state)
     it.planar = h.planar ? 1 : 0;
     if (l + 1 < h.L) {
         const Level &c = h.lv[l + 1];
-        it.uc = g.u[l + 1];
+        it.uc = uc;
         it.fc = g.f[l + 1];
         it.betac = g.beta[l + 1];
         it.ncx = c.n[0];
@@ -484,38 +497,233 @@ Launch gen_launch(Launch::Kind kind, const GenItem *d, int64_t threads, int flag
     return L;
 }
 
-// One V(nu1, nu2) cycle from level l down, appended to pg.
-void add_gen_vcycle(Program &pg, const GenHier &g, const GenItem *const *items, int l, int nu1, int nu2)
-{
-    const Hierarchy &h = g.geo;
-    const Level &lv = h.lv[l];
-    const int64_t in = interior_count(lv, h.planar);
-    const int64_t half = (int64_t)((lv.n[0] - 1) / 2) * (lv.n[1] - 2) * (h.planar ? 1 : lv.n[2] - 2);
-    // algorithmic bytes: a sweep reads u, beta, gamma and writes u once (half
-    // per colour launch); the residual reads u, beta, gamma and writes r
-    const double N = (double)lv.N;
-    if (l == h.L - 1) {
-        pg.launches.push_back(gen_launch(Launch::kGenCoarsest, items[l], 1, 0, 24.0 * N));
-        return;
+// The launches of one V(nu1, nu2) cycle.  Bytes are algorithmic: a pass reads
+// u (not from a zero guess), b/a and the right-hand side, and writes u.
+struct GenCycle {
+    Program &pg;
+    Staging &st;
+    const GenHier &g;
+    SolveState *state;
+    // cx, cy, -2 (cx + cy + cz), 0; for the bottom solver's levels per plane
+    const double *tab[kMaxLevels] = {};
+
+    template <typename T>
+    const T *put(const T &v)
+    {
+        const T *d = st.put(v);
+        if (!d) pg.ok = false;
+        return d;
     }
-    if (l > 0) {
-        Launch z{};
-        z.kind = Launch::kZero;
-        z.dst = g.u[l];
-        z.n = (int64_t)((lv.N * sizeof(double) + 15) & ~size_t(15));
-        pg.launches.push_back(z);
+    // the levels' coefficient tables
+    void tables()
+    {
+        std::vector<double> v;
+        for (int l = 0; l < g.geo.L; ++l) {
+            const GenItem it = gen_item(g, l, nullptr, nullptr, nullptr);
+            const int nk = l < g.geo.b ? 1 : it.nz;
+            v.assign(4 * (size_t)nk, 0.0);
+            for (int k = 0; k < nk; ++k) {
+                v[4 * k] = it.cx;
+                v[4 * k + 1] = it.cy;
+                v[4 * k + 2] = -(2.0 * (it.cx + it.cy + it.cz));
+            }
+            tab[l] = (const double *)st.put_bytes(v.data(), v.size() * sizeof(double));
+            if (!tab[l]) pg.ok = false;
+        }
     }
-    for (int s = 0; s < nu1; ++s)
-        for (int c = 0; c < 2; ++c) pg.launches.push_back(gen_launch(Launch::kGenSweep, items[l], half, c, 16.0 * N));
-    pg.launches.push_back(gen_launch(Launch::kGenResid, items[l], in, 0, 32.0 * N));
-    const Level &cl = h.lv[l + 1];
-    pg.launches.push_back(gen_launch(Launch::kGenRestrict, items[l], interior_count(cl, h.planar), 0,
-                                     8.0 * (N + (double)cl.N)));
-    add_gen_vcycle(pg, g, items, l + 1, nu1, nu2);
-    pg.launches.push_back(gen_launch(Launch::kGenProlong, items[l], in, 0, 16.0 * N + 8.0 * (double)cl.N));
-    for (int s = 0; s < nu2; ++s)
-        for (int c = 0; c < 2; ++c) pg.launches.push_back(gen_launch(Launch::kGenSweep, items[l], half, c, 16.0 * N));
-}
+    LevelItem item(int l)
+    {
+        const GenItem q = gen_item(g, l, nullptr, nullptr, state);
+        LevelItem it{};
+        it.f = q.f;
+        it.beta = q.beta;
+        it.coef = tab[l];
+        it.cz = q.cz;
+        it.state = state;
+        it.partials = q.partials;
+        it.nx = q.nx;
+        it.ny = q.ny;
+        it.nz = q.nz;
+        it.ncx = q.ncx;
+        it.ncy = q.ncy;
+        it.ncz = q.ncz;
+        return it;
+    }
+    void push(Launch::Kind kind, const LevelItem &it, int flags, double bytes)
+    {
+        Launch L{};
+        L.kind = kind;
+        L.flags = flags;
+        L.items = put(it);
+        L.ntiles = it.ntx * it.nty * it.ntz;
+        L.prof = MHS_PROF_GENERAL;
+        L.bytes = bytes;
+        L.pre = (flags & kNorm) != 0 && kind != Launch::kRestrict3 && kind != Launch::kRestrict2;
+        pg.launches.push_back(L);
+    }
+    // one launch of one or (kTwoSweeps) two sweeps, uin -> uout
+    void sweep(int l, const double *uin, double *uout, const double *ec, int flags)
+    {
+        const Hierarchy &h = g.geo;
+        const Level &lv = h.lv[l];
+        LevelItem it = item(l);
+        it.u_in = uin;
+        it.u_out = uout;
+        it.ec = ec;
+        double words = 4.0 - ((flags & kZeroIn) ? 1.0 : 0.0);
+        double bytes = 8.0 * words * (double)lv.N;
+        if (ec) bytes += 8.0 * (double)h.lv[l + 1].N;
+        flags |= kHasF | kPairGen;
+        if (h.planar) {
+            it.ntx = lv.st[0];
+            it.nty = lv.st[1];
+            it.ntz = it.kz = 1;
+            push(Launch::kSweep2, it, flags, bytes);
+            return;
+        }
+        const PairTiling &pt = g.pair[l][(flags & kProlong) ? 1 : 0];
+        it.lgx = pt.lgx;
+        it.ntx = pt.nt[0];
+        it.nty = pt.nt[1];
+        it.ntz = pt.nt[2];
+        it.kz = pt.kz;
+        if (l == 0) {
+            it.ext = 2;
+            flags |= kPairEdge;
+        }
+        if ((flags & kProlong) && lv.keepz) flags |= kPairKeepZ;
+        push(Launch::kPair3, it, flags | pt.var << kPairVariantShift, bytes);
+    }
+    // one sweep in place, colour by colour
+    void colours(int l, double *u)
+    {
+        const Hierarchy &h = g.geo;
+        const Level &lv = h.lv[l];
+        const GenItem *d = put(gen_item(g, l, u, nullptr, state));
+        const int64_t half = (int64_t)((lv.n[0] - 1) / 2) * (lv.n[1] - 2) * (h.planar ? 1 : lv.n[2] - 2);
+        for (int c = 0; c < 2; ++c) pg.launches.push_back(gen_launch(Launch::kGenSweep, d, half, c, 16.0 * (double)lv.N));
+    }
+    // n sweeps of level l from cur (first: kZeroIn, kNorm or kProlong with
+    // ec), ping-pong with oth; the norm's finalize follows its launch
+    void sweeps(int l, double *&cur, double *&oth, int n, int first, const double *ec)
+    {
+        const Hierarchy &h = g.geo;
+        const Level &lv = h.lv[l];
+        int s = 0;
+        if (h.planar || (n >= 2 && !(lv.keepxy && ec))) {
+            const int two = n >= 2 ? kTwoSweeps : 0;
+            sweep(l, (first & kZeroIn) ? nullptr : cur, oth, ec, first | two);
+            if (first & kNorm) finalize(pg.launches.back().ntiles);
+            std::swap(cur, oth);
+            s = two ? 2 : 1;
+        } else if (first & kZeroIn) {
+            Launch z{};
+            z.kind = Launch::kZero;
+            z.dst = cur;
+            z.n = (int64_t)((lv.N * sizeof(double) + 15) & ~size_t(15));
+            pg.launches.push_back(z);
+        } else if (first & kNorm) {
+            GenItem it = gen_item(g, l, cur, nullptr, state);
+            it.r = nullptr;
+            const int64_t in = interior_count(lv, h.planar);
+            Launch L = gen_launch(Launch::kGenResid, put(it), in, 1, 24.0 * (double)lv.N);
+            L.pre = true;
+            pg.launches.push_back(L);
+            finalize((int)blocks_for(in));
+        } else if (ec) {
+            pg.launches.push_back(gen_launch(Launch::kGenProlong, put(gen_item(g, l, cur, ec, state)),
+                                             interior_count(lv, h.planar), 0,
+                                             16.0 * (double)lv.N + 8.0 * (double)h.lv[l + 1].N));
+        }
+        while (s < n) {
+            if (h.planar || n - s >= 2) {
+                const int two = n - s >= 2 ? kTwoSweeps : 0;
+                sweep(l, cur, oth, nullptr, two);
+                std::swap(cur, oth);
+                s += two ? 2 : 1;
+            } else {
+                colours(l, cur);
+                ++s;
+            }
+        }
+    }
+    void finalize(int n)
+    {
+        add_finalize(pg, st, g.partials, n, state);
+        pg.launches.back().pre = true;
+    }
+    void restriction(int l, double *u)
+    {
+        const Hierarchy &h = g.geo;
+        const Level &lv = h.lv[l], &c = h.lv[l + 1];
+        const double N = (double)lv.N;
+        if (lv.keepxy) {
+            const GenItem *d = put(gen_item(g, l, u, nullptr, state));
+            pg.launches.push_back(gen_launch(Launch::kGenResid, d, interior_count(lv, h.planar), 0, 32.0 * N));
+            pg.launches.push_back(
+                gen_launch(Launch::kGenRestrict, d, interior_count(c, h.planar), 0, 8.0 * (N + (double)c.N)));
+            return;
+        }
+        LevelItem it = item(l);
+        it.u_in = u;
+        it.u_out = g.f[l + 1];
+        it.ntx = lv.rt[0];
+        it.nty = lv.rt[1];
+        it.ntz = lv.rt[2];
+        it.kz = lv.kc;
+        push(h.planar ? Launch::kRestrict2 : Launch::kRestrict3, it,
+             kRestrictHasF | kRestrictGen | (lv.keepz ? kRestrictKeepZ : 0), 24.0 * N + 8.0 * (double)c.N);
+    }
+    void bottom(int nu1, int nu2)
+    {
+        const Hierarchy &h = g.geo;
+        BottomItem b = bottom_item(h, kF64, g.f[h.b], g.u[h.b], nu1, nu2, state);
+        const double *beta[kMaxLevels] = {};
+        for (int q = 0; q < b.nlev; ++q) {
+            b.coef[q] = tab[h.b + q];
+            b.cz[q] = gen_item(g, h.b + q, nullptr, nullptr, nullptr).cz;
+            beta[q] = g.beta[h.b + q];
+        }
+        b.beta = (const double *const *)st.put_bytes(beta, sizeof beta);
+        if (!b.beta) pg.ok = false;
+        b.minv = g.minv;
+        Launch L{};
+        L.kind = Launch::kBottom;
+        L.flags = 1; // the general operator's variant
+        L.items = put(b);
+        L.lds = h.lds_bytes;
+        L.prof = MHS_PROF_GENERAL;
+        L.bytes = 24.0 * (double)h.lv[h.b].N;
+        pg.launches.push_back(L);
+    }
+    // the whole cycle on level-0 iterate u0, which holds the result
+    void build(double *u0, int nu1, int nu2)
+    {
+        const Hierarchy &h = g.geo;
+        double *cur[kMaxLevels], *oth[kMaxLevels];
+        for (int l = 0; l < h.b; ++l) {
+            cur[l] = l == 0 ? u0 : g.u[l];
+            oth[l] = g.t[l];
+            sweeps(l, cur[l], oth[l], nu1, l == 0 ? kNorm : kZeroIn, nullptr);
+            restriction(l, cur[l]);
+        }
+        bottom(nu1, nu2);
+        const double *ec = g.u[h.b];
+        for (int l = h.b - 1; l >= 0; --l) {
+            sweeps(l, cur[l], oth[l], nu2, kProlong, ec);
+            ec = cur[l];
+        }
+        if (cur[0] != u0) {
+            Launch c{};
+            c.kind = Launch::kCopy;
+            c.src = cur[0];
+            c.dst = u0;
+            c.n = (int64_t)h.lv[0].N;
+            c.gate = state;
+            pg.launches.push_back(c);
+        }
+    }
+};
 
 // Solve on hierarchy g with level-0 iterate u0 (boundary values = data).
 int gen_solve(mhs_plan *p, GenHier &g, double *u0, const double *a, const double *b, const double *c,
@@ -531,11 +739,12 @@ int gen_solve(mhs_plan *p, GenHier &g, double *u0, const double *a, const double
     SolveState *d_state = (SolveState *)p->stage.put(initial_state(o->rtol, o->max_cycles));
     const GenItem *items[kMaxLevels] = {};
     for (int l = 0; l < L; ++l) {
-        GenItem it = level_item(g, l, l == 0 ? u0 : g.u[l], d_state);
+        GenItem it = gen_item(g, l, l == 0 ? u0 : g.u[l], nullptr, d_state);
         if (l == 0) {
             it.a = a;
             it.b = b;
             it.c = c;
+            it.twin = g.t[0];
             it.warm = o->warm_start;
         }
         items[l] = p->stage.put(it);
@@ -544,27 +753,25 @@ int gen_solve(mhs_plan *p, GenHier &g, double *u0, const double *a, const double
     // result goes after them
     double *d_red = g.partials + 2 * (size_t)g.npart;
     Program cyc;
-    {
-        Launch chk = gen_launch(Launch::kGenResid, items[0], interior_count(h.lv[0], h.planar), 1,
-                                24.0 * (double)h.lv[0].N);
-        chk.pre = true;
-        cyc.launches.push_back(chk);
-        add_finalize(cyc, p->stage, g.partials, (int)blocks_for(interior_count(h.lv[0], h.planar)), d_state);
-        cyc.launches.back().pre = true;
-        add_gen_vcycle(cyc, g, items, 0, o->nu1, o->nu2);
-    }
+    GenCycle gc{cyc, p->stage, g, d_state};
+    gc.tables();
+    gc.build(u0, o->nu1, o->nu2);
     if (!d_state || !items[L - 1] || !cyc.ok) return fail(MHS_ERR_WORKSPACE, "staging area exhausted");
     if ((st = flush_staging(p, s))) return st;
-    // level-0 coefficients, then beta on every coarser level
+    // level-0 coefficients, then beta on every coarser level, and the inverse
+    // of the coarsest operator
     const int64_t N0 = (int64_t)h.lv[0].N;
-    hipLaunchKernelGGL(k_gen_prep, dim3(blocks_for(N0)), dim3(kGenThreads), 0, s, items[0]);
+    const unsigned nprep = std::min(blocks_for(N0), (unsigned)kGenPrepBlocks);
+    hipLaunchKernelGGL(k_gen_prep, dim3(nprep), dim3(kGenThreads), 0, s, items[0]);
     HIPCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_gen_prep_reduce, dim3(1), dim3(kGenThreads), 0, s, g.partials, (int)blocks_for(N0), d_red);
+    hipLaunchKernelGGL(k_gen_prep_reduce, dim3(1), dim3(kGenThreads), 0, s, g.partials, (int)nprep, d_red);
     HIPCHK(hipGetLastError());
     for (int l = 0; l + 1 < L; ++l) {
         hipLaunchKernelGGL(k_gen_inject, dim3(blocks_for((int64_t)h.lv[l + 1].N)), dim3(kGenThreads), 0, s, items[l]);
         HIPCHK(hipGetLastError());
     }
+    hipLaunchKernelGGL(k_gen_inverse, dim3(1), dim3(kGenThreads), 0, s, items[L - 1], g.minv);
+    HIPCHK(hipGetLastError());
     // definiteness and the coefficients' validity, read back once
     double hred[2] = {0.0, 0.0};
     HIPCHK(hipMemcpyAsync(p->h_states, d_red, sizeof hred, hipMemcpyDeviceToHost, s));

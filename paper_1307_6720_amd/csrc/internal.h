@@ -104,7 +104,10 @@ struct LevelItem {
     void *u_out;        // iterate written (smoother, refinement) / coarse rhs (restriction)
     const void *f;      // right-hand side, nullptr = 0
     const void *ec;     // coarse correction added before smoothing, or FP32 e (refinement)
-    void *r_out;        // refinement: FP32 residual output
+    union {
+        void *r_out;      // refinement: FP32 residual output
+        const void *beta; // general operator: b/a per node
+    };
     const void *coef;   // per-plane {cx, cy, d, 1/d} in the stage's arithmetic type
     double cz;          // z coupling 1/dz^2 (0 for the 2D problem)
     SolveState *state;  // stage is skipped once state->done != 0 (may be null)
@@ -120,6 +123,8 @@ struct LevelItem {
                            // (items of several shapes), 0 = in contiguous ranges per XCD
 };
 
+static_assert(sizeof(LevelItem) == 128, "a batch's descriptor tables are sized for items of two cache lines");
+
 // One request of the bottom solver: a full V-cycle from level `top` of the
 // bottom hierarchy to the coarsest grid, in FP64, by a single workgroup whose
 // work arrays all live in LDS (offsets in doubles into dynamic shared memory).
@@ -127,12 +132,12 @@ struct BottomItem {
     const void *f_top;            // right-hand side at the top bottom level (storage type)
     void *u_top;                  // correction written back (storage type)
     const double *coef[kMaxLevels];
+    const double *const *beta;      // general operator: b/a per node, by level (device array)
     double cz[kMaxLevels];
     int32_t n[kMaxLevels][3];
     int32_t off_u[kMaxLevels];    // LDS offsets (doubles)
     int32_t off_f[kMaxLevels];
     int32_t off_c[kMaxLevels];    // LDS copy of the level's coefficient table (4 * nz)
-    uint32_t inv[kMaxLevels];     // ceil(2^32 / (ny - 2)), 0 for ny = 3: r / (ny - 2) = high word of r * inv
     int32_t off_r;
     int32_t nlev;
     int32_t m;                    // unknowns of the coarsest grid
@@ -141,6 +146,8 @@ struct BottomItem {
     const double *minv;           // m x m inverse of the coarsest operator
     SolveState *state;
 };
+
+static_assert(sizeof(BottomItem) <= 704, "as LevelItem");
 
 // Largest LDS footprint of a bottom hierarchy (u, f and coefficients per
 // level, r for the top level).
@@ -222,6 +229,8 @@ enum SweepFlags : int {
     kProlong = 8,   // add the interpolated coarse correction to u_in first
     kTwoSweeps = 16, // two complete sweeps in one launch
     kPairKeepZ = 32, // two sweeps in 3D: the step to the coarse level keeps z
+    kPairGen = 64,   // two sweeps in 3D, or 2D sweeps: the general operator (a diagonal per node)
+    kPairEdge = 128, // two sweeps in 3D: boundary nodes carry data although there is a right-hand side
     // launch flags of the 3D two-sweep kernel carry its variant from this bit on
     kPairVariantShift = 8,
     kPairVariantBit = 1 << kPairVariantShift,
@@ -231,6 +240,7 @@ enum SweepFlags : int {
 enum RestrictFlags : int {
     kRestrictHasF = 1,  // read the right-hand side
     kRestrictKeepZ = 2, // the step to the coarse level halves x and y only
+    kRestrictGen = 4,   // the general operator: b/a per node
 };
 
 hipError_t launch_sweep3(const LevelItem *items, int nitems, int ntiles, int flags, bool dbl,
@@ -248,9 +258,9 @@ hipError_t launch_pair3(const LevelItem *items, int nitems, int ntiles, int flag
                         hipStream_t s);
 hipError_t launch_sweep2(const LevelItem *items, int nitems, int ntiles, int flags, bool dbl,
                          hipStream_t s);
-hipError_t launch_restrict3(const LevelItem *items, int nitems, int ntiles, bool has_f, bool keepz, bool dbl,
+hipError_t launch_restrict3(const LevelItem *items, int nitems, int ntiles, bool has_f, bool keepz, bool gen, bool dbl,
                             hipStream_t s);
-hipError_t launch_restrict2(const LevelItem *items, int nitems, int ntiles, bool dbl,
+hipError_t launch_restrict2(const LevelItem *items, int nitems, int ntiles, bool gen, bool dbl,
                             hipStream_t s);
 // steps that keep x and y: one thread per node (ntiles = ceil(nodes / kThreads))
 hipError_t launch_restrict3_z(const LevelItem *items, int nitems, int ntiles, bool has_f, bool dbl, hipStream_t s);
@@ -258,7 +268,7 @@ hipError_t launch_prolong3_z(const LevelItem *items, int nitems, int ntiles, boo
 // zero_in: the iterate's interior is read as zero (a cold start's first two
 // refinement steps; only its boundary nodes are loaded)
 hipError_t launch_ir3(const LevelItem *items, int nitems, int ntiles, bool has_e, bool zero_in, hipStream_t s);
-hipError_t launch_bottom(const BottomItem *items, int nitems, int lds_bytes, bool dbl, hipStream_t s);
+hipError_t launch_bottom(const BottomItem *items, int nitems, int lds_bytes, bool gen, bool dbl, hipStream_t s);
 hipError_t launch_finalize(const FinalizeItem *items, int nitems, hipStream_t s);
 hipError_t launch_fields(const FieldsItem *items, int nitems, int ntiles, hipStream_t s);
 hipError_t launch_diag(const DiagItem &item, hipStream_t s);

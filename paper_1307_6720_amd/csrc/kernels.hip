@@ -644,6 +644,7 @@ __global__ __launch_bounds__(kThreads) void k_sweep2(const LevelItem *__restrict
     constexpr bool ZERO_IN = (FLAGS & kZeroIn) != 0;
     constexpr bool NORM = (FLAGS & kNorm) != 0;
     constexpr bool PROLONG = (FLAGS & kProlong) != 0;
+    constexpr bool GEN = (FLAGS & kPairGen) != 0; // the general operator: d + b/a per node
     constexpr int NS = (FLAGS & kTwoSweeps) ? 2 : 1;
     constexpr int H = 2 * NS; // halo
     constexpr int WX = kTX + 2 * H, WY = kTY2 + 2 * H;
@@ -658,6 +659,7 @@ __global__ __launch_bounds__(kThreads) void k_sweep2(const LevelItem *__restrict
     const MHS_GLOBAL T *__restrict__ f = gin<T>(it->f);
     const MHS_GLOBAL T *__restrict__ ec = gin<T>(it->ec);
     const MHS_CONST T *__restrict__ coef = gconst<T>(it->coef);
+    const MHS_GLOBAL T *__restrict__ be = gin<T>(it->beta);
     const int nx = it->nx, ny = it->ny;
     const int ncx = it->ncx;
     const int local = tile - it->tile_base;
@@ -690,7 +692,9 @@ __global__ __launch_bounds__(kThreads) void k_sweep2(const LevelItem *__restrict
             if (i <= nx - 2 && j <= ny - 2) {
                 T fv = (T)0;
                 if constexpr (HAS_F) fv = f[(size_t)i + (size_t)nx * j];
-                const T r = fv - (cx * (S[w][c + 1] + S[w][c - 1]) + cy * (S[w + 1][c] + S[w - 1][c]) + d * S[w][c]);
+                T dv = d;
+                if constexpr (GEN) dv += be[(size_t)i + (size_t)nx * j];
+                const T r = fv - (cx * (S[w][c + 1] + S[w][c - 1]) + cy * (S[w + 1][c] + S[w - 1][c]) + dv * S[w][c]);
                 acc += (double)r * (double)r;
             }
         }
@@ -711,7 +715,11 @@ __global__ __launch_bounds__(kThreads) void k_sweep2(const LevelItem *__restrict
             if (i >= 1 && i <= nx - 2 && j >= 1 && j <= ny - 2) {
                 T fv = (T)0;
                 if constexpr (HAS_F) fv = f[(size_t)i + (size_t)nx * j];
-                S[w][c] = (fv - (cx * (S[w][c + 1] + S[w][c - 1]) + cy * (S[w + 1][c] + S[w - 1][c]))) * invd;
+                const T n = fv - (cx * (S[w][c + 1] + S[w][c - 1]) + cy * (S[w + 1][c] + S[w - 1][c]));
+                if constexpr (GEN)
+                    S[w][c] = n / (be[(size_t)i + (size_t)nx * j] + d);
+                else
+                    S[w][c] = n * invd;
             }
         }
     };
@@ -749,7 +757,7 @@ constexpr int kRRX = 2 * kCX + 1;
 constexpr int kRRY = 2 * kCY + 1;
 static_assert(kCX * kCY == kThreads, "one coarse node per thread");
 
-template <typename T, bool HAS_F, bool KEEPZ>
+template <typename T, bool HAS_F, bool KEEPZ, bool GEN = false>
 __global__ __launch_bounds__(kThreads) void k_restrict3(const LevelItem *__restrict__ items, int nitems)
 {
     constexpr int kCells = kRWY * kRWX;
@@ -828,8 +836,10 @@ __global__ __launch_bounds__(kThreads) void k_restrict3(const LevelItem *__restr
     // register set q holds u plane p and f plane p - 1 (the residual plane
     // computed in the step that stages u plane p)
     T pre[D][kPer];
-    T fpre[D][HAS_F ? kRPer : 1];
-    auto fetch = [&](int p, T(&dst)[kPer], T(&fdst)[HAS_F ? kRPer : 1]) {
+    // (and b/a there, for the general operator)
+    T fpre[D][HAS_F ? kRPer : 1], bpre[D][GEN ? kRPer : 1];
+    const MHS_GLOBAL T *__restrict__ be = gin<T>(it->beta);
+    auto fetch = [&](int p, T(&dst)[kPer], T(&fdst)[HAS_F ? kRPer : 1], T(&bdst)[GEN ? kRPer : 1]) {
         const MHS_GLOBAL T *pl = u + sxy * (size_t)p;
 #pragma unroll
         for (int r = 0; r < kPer; ++r) dst[r] = at(pl, st_g[r]);
@@ -837,6 +847,11 @@ __global__ __launch_bounds__(kThreads) void k_restrict3(const LevelItem *__restr
             const MHS_GLOBAL T *fl = f + sxy * (size_t)max(p - 1, 0);
 #pragma unroll
             for (int r = 0; r < kRPer; ++r) fdst[r] = at(fl, rc_g[r]);
+        }
+        if constexpr (GEN) {
+            const MHS_GLOBAL T *bl = be + sxy * (size_t)max(p - 1, 0);
+#pragma unroll
+            for (int r = 0; r < kRPer; ++r) bdst[r] = at(bl, rc_g[r]);
         }
     };
     auto stash = [&](int p, const T(&src)[kPer]) {
@@ -856,19 +871,22 @@ __global__ __launch_bounds__(kThreads) void k_restrict3(const LevelItem *__restr
     // the residual planes' cx, cy, d (at most 2 kKC + 1 <= 64)
     static_assert(2 * kKC + 1 <= 64, "one plane per lane");
     PlaneTab<T> tcx, tcy, tdd;
-    tcx.load(coef, mfirst, 0, it->nz);
-    tcy.load(coef, mfirst, 1, it->nz);
-    tdd.load(coef, mfirst, 2, it->nz);
+    // (the general operator's are the same on every plane)
+    if constexpr (!GEN) {
+        tcx.load(coef, mfirst, 0, it->nz);
+        tcy.load(coef, mfirst, 1, it->nz);
+        tdd.load(coef, mfirst, 2, it->nz);
+    }
 #pragma unroll
     for (int q = 0; q < D; ++q) {
-        fetch(min(pbase + q, ptop), pre[q], fpre[q]);
+        fetch(min(pbase + q, ptop), pre[q], fpre[q], bpre[q]);
         __builtin_amdgcn_sched_barrier(0);
     }
     stash(pbase, pre[0]);
     stash(pbase + 1, pre[1]);
-    fetch(min(pbase + D, ptop), pre[0], fpre[0]);
+    fetch(min(pbase + D, ptop), pre[0], fpre[0], bpre[0]);
     __builtin_amdgcn_sched_barrier(0);
-    fetch(min(pbase + D + 1, ptop), pre[1], fpre[1]);
+    fetch(min(pbase + D + 1, ptop), pre[1], fpre[1], bpre[1]);
     __builtin_amdgcn_sched_barrier(0);
     T acc = (T)0;
     const T q4 = (T)0.25, h2 = (T)0.5;
@@ -887,7 +905,7 @@ __global__ __launch_bounds__(kThreads) void k_restrict3(const LevelItem *__restr
             stash(m + 1, pre[ri]);
             lds_barrier();
             if (live) {
-                const T cx = tcx(m), cy = tcy(m), d = tdd(m);
+                const T cx = GEN ? coef[0] : tcx(m), cy = GEN ? coef[1] : tcy(m), d = GEN ? coef[2] : tdd(m);
                 const T *P = U + (m & 3) * USLOT;
                 const T *Pm = U + ((m - 1) & 3) * USLOT;
                 const T *Pp = U + ((m + 1) & 3) * USLOT;
@@ -900,13 +918,15 @@ __global__ __launch_bounds__(kThreads) void k_restrict3(const LevelItem *__restr
                     if ((rc_int >> r) & 1) {
                         T fv = (T)0;
                         if constexpr (HAS_F) fv = fpre[ri][r];
+                        T dv = d;
+                        if constexpr (GEN) dv += bpre[ri][r];
                         rv = fv - (cx * (P[o + 1] + P[o - 1]) + cy * (P[o + kRWX] + P[o - kRWX]) +
-                                   cz * (Pp[o] + Pm[o]) + d * P[o]);
+                                   cz * (Pp[o] + Pm[o]) + dv * P[o]);
                     }
                     R[ri_] = rv;
                 }
             }
-            fetch(min(m + 1 + D, ptop), pre[ri], fpre[ri]);
+            fetch(min(m + 1 + D, ptop), pre[ri], fpre[ri], bpre[ri]);
             lds_barrier();
             if (!live) continue;
             auto row = [&](int w) {
@@ -991,7 +1011,7 @@ __global__ __launch_bounds__(kThreads) void k_prolong3_z(const LevelItem *__rest
     u[col + sxy * k] += v;
 }
 
-template <typename T>
+template <typename T, bool GEN>
 __global__ __launch_bounds__(kThreads) void k_restrict2(const LevelItem *__restrict__ items, int nitems)
 {
     __shared__ T U[kRWY][kRWX];
@@ -1014,6 +1034,7 @@ __global__ __launch_bounds__(kThreads) void k_restrict2(const LevelItem *__restr
     const int tI = tid % kCX, tJ = tid / kCX;
     const int I = I0 + tI, J = J0 + tJ;
     const T cx = coef[0], cy = coef[1], d = coef[2];
+    const MHS_GLOBAL T *__restrict__ be = gin<T>(it->beta);
     for (int e = tid; e < kRWY * kRWX; e += kThreads) {
         const int w = e / kRWX, c = e - w * kRWX;
         const int i = ui0 + c, j = uj0 + w;
@@ -1026,8 +1047,10 @@ __global__ __launch_bounds__(kThreads) void k_restrict2(const LevelItem *__restr
         T r = (T)0;
         if (i >= 1 && i <= nx - 2 && j >= 1 && j <= ny - 2) {
             const int uw = w + 1, uc = c + 1;
+            T dv = d;
+            if constexpr (GEN) dv += be[(size_t)i + (size_t)nx * j];
             r = f[(size_t)i + (size_t)nx * j] -
-                (cx * (U[uw][uc + 1] + U[uw][uc - 1]) + cy * (U[uw + 1][uc] + U[uw - 1][uc]) + d * U[uw][uc]);
+                (cx * (U[uw][uc + 1] + U[uw][uc - 1]) + cy * (U[uw + 1][uc] + U[uw - 1][uc]) + dv * U[uw][uc]);
         }
         R[w][c] = r;
     }
@@ -1883,7 +1906,7 @@ template <typename T>
 hipError_t sweep2_dispatch(const LevelItem *items, int nitems, int ntiles, int flags, hipStream_t s)
 {
     dim3 grid(ntiles), block(kThreads);
-    switch (flags & 31) {
+    switch (flags) {
 #define MHS_CASE(F)                                                                      \
     case F:                                                                              \
         hipLaunchKernelGGL((k_sweep2<T, F>), grid, block, 0, s, items, nitems);         \
@@ -1894,6 +1917,9 @@ hipError_t sweep2_dispatch(const LevelItem *items, int nitems, int ntiles, int f
         // one sweep or two
         MHS_CASE(0) MHS_CASE(1) MHS_CASE(3) MHS_CASE(4) MHS_CASE(5) MHS_CASE(8) MHS_CASE(9)
         MHS_CASE(16) MHS_CASE(17) MHS_CASE(19) MHS_CASE(20) MHS_CASE(21) MHS_CASE(24) MHS_CASE(25)
+        // the general operator on a face
+        MHS_CASE(kPairGen | 1) MHS_CASE(kPairGen | 3) MHS_CASE(kPairGen | 5) MHS_CASE(kPairGen | 9)
+        MHS_CASE(kPairGen | 17) MHS_CASE(kPairGen | 19) MHS_CASE(kPairGen | 21) MHS_CASE(kPairGen | 25)
 #undef MHS_CASE
     default:
         return hipErrorInvalidValue;
@@ -1926,12 +1952,18 @@ static void restrict3_variant(const LevelItem *items, int nitems, dim3 grid, boo
         hipLaunchKernelGGL((k_restrict3<T, HAS_F, false>), grid, dim3(kThreads), 0, s, items, nitems);
 }
 
-hipError_t launch_restrict3(const LevelItem *items, int nitems, int ntiles, bool has_f, bool keepz, bool dbl,
+hipError_t launch_restrict3(const LevelItem *items, int nitems, int ntiles, bool has_f, bool keepz, bool gen, bool dbl,
                             hipStream_t s)
 {
     if (ntiles <= 0) return hipSuccess;
     dim3 grid(ntiles);
-    if (dbl) {
+    if (gen) {
+        if (!dbl || !has_f) return hipErrorInvalidValue;
+        if (keepz)
+            hipLaunchKernelGGL((k_restrict3<double, true, true, true>), grid, dim3(kThreads), 0, s, items, nitems);
+        else
+            hipLaunchKernelGGL((k_restrict3<double, true, false, true>), grid, dim3(kThreads), 0, s, items, nitems);
+    } else if (dbl) {
         if (has_f)
             restrict3_variant<double, true>(items, nitems, grid, keepz, s);
         else
@@ -1974,14 +2006,17 @@ hipError_t launch_prolong3_z(const LevelItem *items, int nitems, int ntiles, boo
     return hipGetLastError();
 }
 
-hipError_t launch_restrict2(const LevelItem *items, int nitems, int ntiles, bool dbl, hipStream_t s)
+hipError_t launch_restrict2(const LevelItem *items, int nitems, int ntiles, bool gen, bool dbl, hipStream_t s)
 {
     if (ntiles <= 0) return hipSuccess;
     dim3 grid(ntiles), block(kThreads);
-    if (dbl)
-        hipLaunchKernelGGL((k_restrict2<double>), grid, block, 0, s, items, nitems);
+    if (gen && !dbl) return hipErrorInvalidValue;
+    if (gen)
+        hipLaunchKernelGGL((k_restrict2<double, true>), grid, block, 0, s, items, nitems);
+    else if (dbl)
+        hipLaunchKernelGGL((k_restrict2<double, false>), grid, block, 0, s, items, nitems);
     else
-        hipLaunchKernelGGL((k_restrict2<float>), grid, block, 0, s, items, nitems);
+        hipLaunchKernelGGL((k_restrict2<float, false>), grid, block, 0, s, items, nitems);
     return hipGetLastError();
 }
 

@@ -159,7 +159,10 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     constexpr bool NORM = (FLAGS & kNorm) != 0;
     // without a right-hand side the boundary nodes carry data (level 0 of the
     // FP64 path) and keep their values; with one they are zero
-    constexpr bool DATA = !HAS_F;
+    constexpr bool DATA = !HAS_F || (FLAGS & kPairEdge) != 0;
+    // the general operator: a diagonal of its own at every node
+    constexpr bool GEN = (FLAGS & kPairGen) != 0;
+    constexpr bool KEEP = DATA || GEN; // nodes that are not updated keep their values
     static_assert(!DATA || V == 2, "the right edge of a window with data is masked per node of a pair");
     static_assert(!NORM || DATA, "the norm is taken on level 0");
     constexpr int H = V / 2;
@@ -184,6 +187,7 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     MHS_GLOBAL T *__restrict__ uout = gout<T>(it->u_out);
     const MHS_GLOBAL T *__restrict__ fin = gin<T>(it->f);
     const MHS_GLOBAL T *__restrict__ ec = gin<T>(it->ec);
+    const MHS_GLOBAL T *__restrict__ bin = gin<T>(it->beta);
     const MHS_CONST T *__restrict__ coef = gconst<T>(it->coef);
     const T cz = (T)it->cz;
     const int nx = it->nx, ny = it->ny, nz = it->nz;
@@ -239,13 +243,21 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
 
     // planes s0-1 .. (at most 64): cx, cy, 1/d
     const int s0 = max(kb - 3, 0) & ~1;
+    // (the general operator's are the same on every plane)
     PlaneTab<T> tcx, tcy, tid_, tdd;
-    tcx.load(coef, s0 - 4, 0, nz);
-    tcy.load(coef, s0 - 4, 1, nz);
-    tid_.load(coef, s0 - 4, 3, nz);
-    if constexpr (NORM) tdd.load(coef, s0 - 4, 2, nz);
+    T gcx = (T)0, gcy = (T)0, gdd = (T)0;
+    if constexpr (GEN) {
+        gcx = coef[0];
+        gcy = coef[1];
+        gdd = coef[2];
+    } else {
+        tcx.load(coef, s0 - 4, 0, nz);
+        tcy.load(coef, s0 - 4, 1, nz);
+        tid_.load(coef, s0 - 4, 3, nz);
+        if constexpr (NORM) tdd.load(coef, s0 - 4, 2, nz);
+    }
 
-    T u[NS][R][V], f[NS][R][V];
+    T u[NS][R][V], f[NS][R][V], be[GEN ? NS : 1][R][V];
     T dr[R][H]; // red nodes of plane s-4
     // prolongation: coarse rows interpolated to the thread's two rows, of the
     // coarse plane below and above; the next coarse plane in flight
@@ -257,7 +269,7 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
 #pragma unroll
         for (int q = 0; q < NS; ++q)
 #pragma unroll
-            for (int v = 0; v < V; ++v) u[q][r][v] = f[q][r][v] = (T)0;
+            for (int v = 0; v < V; ++v) u[q][r][v] = f[q][r][v] = be[GEN ? q : 0][r][v] = (T)0;
 #pragma unroll
         for (int h = 0; h <= H; ++h) ya[r][h] = yb[r][h] = raw[r / 2][h] = raw[RC - 1][h] = (T)0;
     }
@@ -272,6 +284,13 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     auto fetch_f = [&](int p, T(&dst)[R][V]) {
         if constexpr (HAS_F) {
             const auto rs = plane_rsrc(fin + sxy * (size_t)min(max(p, 0), nz - 1), plane_bytes);
+#pragma unroll
+            for (int r = 0; r < R; ++r) bload_vec<V>(dst[r], rs, og, r * row_bytes);
+        }
+    };
+    auto fetch_b = [&](int p, T(&dst)[R][V]) {
+        if constexpr (GEN) {
+            const auto rs = plane_rsrc(bin + sxy * (size_t)min(max(p, 0), nz - 1), plane_bytes);
 #pragma unroll
             for (int r = 0; r < R; ++r) bload_vec<V>(dst[r], rs, og, r * row_bytes);
         }
@@ -321,15 +340,20 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         asm volatile("" : "+v"(a));
         return c ? a : old;
     };
-    // 1/d of plane p, 0 on the boundary planes: a node that is not updated is a
+    // 1/d of plane p (GEN: the Laplacian's diagonal, which the node's b/a adds
+    // to), 0 on the boundary planes: a node that is not updated is a
     // boundary node, whose value (zero) comes out of the update as zero when
     // its 1/d is zero
     struct Coef {
         T cx, cy, inv;
     };
     auto coef_of = [&](int p) {
-        const T cx = tcx(p), cy = tcy(p), inv = tid_(p);
-        return Coef{cx, cy, p >= 1 && p <= nz - 2 ? inv : (T)0};
+        if constexpr (GEN) {
+            return Coef{gcx, gcy, gdd};
+        } else {
+            const T cx = tcx(p), cy = tcy(p), inv = tid_(p);
+            return Coef{cx, cy, p >= 1 && p <= nz - 2 ? inv : (T)0};
+        }
     };
     Coef q[NS]; // of the planes in the slots
 #pragma unroll
@@ -351,14 +375,14 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     // one colour (0 red, 1 black) of plane p: k its coefficients, uc its columns, uu and ud those
     // above and below, S rows at rd; par the plane's parity
     auto colour = [&](int p, const Coef &k, int par, int col, T(&uc)[R][V], const T(&uu)[R][V], const T(&dn)[R][V], const T(&fp)[R][V],
-                      const Rows &y) {
+                      const T(&bp)[R][V], const Rows &y) {
         const T cx = k.cx, cy = k.cy, invd = k.inv;
         const bool in = p >= 1 && p <= nz - 2;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int v0 = (r + par + col) & 1;
             const bool in1 = upd[r][1] && in, in0 = upd[r][0] && in;
-            const T inv1 = DATA ? invd : upd[r][1] ? invd : (T)0, inv0 = DATA || v0 ? inv1 : upd[r][0] ? invd : (T)0;
+            const T inv1 = KEEP ? invd : upd[r][1] ? invd : (T)0, inv0 = KEEP || v0 ? inv1 : upd[r][0] ? invd : (T)0;
 #pragma unroll
             for (int m = 0; m < H; ++m) {
                 const int v = v0 + 2 * m;
@@ -367,8 +391,9 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
                 const T yn = r + 1 < R ? uc[(r + 1) % R][v] : y.above[m];
                 const T ys_ = r > 0 ? uc[(r + R - 1) % R][v] : y.below[m];
                 const T fv = HAS_F ? fp[r][v] : (T)0;
-                const T a = (fv - (cx * (e + w) + cy * (yn + ys_) + cz * (uu[r][v] + dn[r][v]))) * (v ? inv1 : inv0);
-                uc[r][v] = DATA ? keep_or(v ? in1 : in0, a, uc[r][v]) : a;
+                const T n = fv - (cx * (e + w) + cy * (yn + ys_) + cz * (uu[r][v] + dn[r][v]));
+                const T a = GEN ? n / (bp[r][v] + invd) : n * (v ? inv1 : inv0);
+                uc[r][v] = KEEP ? keep_or(v ? in1 : in0, a, uc[r][v]) : a;
             }
         }
     };
@@ -380,10 +405,10 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int h = 0; h < H; ++h) ro[r][h] = (T)0;
-    auto residual = [&](int p, int par, const T(&uc)[R][V], const T(&uu)[R][V], const T(&dn)[R][V], const Rows &yb_,
-                        const Rows &yr) {
+    auto residual = [&](int p, int par, const T(&uc)[R][V], const T(&uu)[R][V], const T(&dn)[R][V], const T(&fp)[R][V],
+                        const T(&bp)[R][V], const Rows &yb_, const Rows &yr) {
         if constexpr (NORM) {
-            const T cx = tcx(p), cy = tcy(p), dd = tdd(p);
+            const T cx = GEN ? gcx : tcx(p), cy = GEN ? gcy : tcy(p), dd = GEN ? gdd : tdd(p);
             const bool in = p >= kb && p < ke;
 #pragma unroll
             for (int col = 0; col < 2; ++col) {
@@ -399,7 +424,9 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
                         const T yn = r + 1 < R ? uc[(r + 1) % R][v] : y.above[m];
                         const T ys_ = r > 0 ? uc[(r + R - 1) % R][v] : y.below[m];
                         const T d_ = col ? ro[r][m] : dn[r][v];
-                        const T rv = cx * (e + w) + cy * (yn + ys_) + cz * (uu[r][v] + d_) + dd * uc[r][v];
+                        const T dv = GEN ? bp[r][v] + dd : dd;
+                        T rv = cx * (e + w) + cy * (yn + ys_) + cz * (uu[r][v] + d_) + dv * uc[r][v];
+                        if constexpr (HAS_F) rv = fp[r][v] - rv;
                         const double z = in && wr[r] && upd[r][v ? 1 : 0] ? (double)rv : 0.0;
                         acc += z * z;
                     }
@@ -420,6 +447,11 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         }
     };
 
+    // the general operator's divisions leave no registers for overlapping the
+    // updates
+    auto calm = [] {
+        if constexpr (GEN && (PROLONG || NORM)) __builtin_amdgcn_sched_barrier(0);
+    };
     // one step at plane s; d: its position in the round of NS steps (s0 is
     // even, so the plane's parity is d's).  Plane s + e lives in slot
     // (d + e + 3) % NS.
@@ -436,6 +468,7 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         T *w0 = S + (a0 + (wo + LH)), *w1 = S + (a0 + (wo + 2 * LH));
         fetch_u(s + 1 + D, u[cnx]);
         fetch_f(s + D, f[cnf]);
+        fetch_b(s + D, be[GEN ? cnf : 0]);
         __builtin_amdgcn_sched_barrier(0); // issued before the step's arithmetic
         // plane s+1 gets its correction (coarse plane (s+2)/2 or, on a step
         // that keeps z, s+1)
@@ -448,30 +481,46 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         }
         Rows y0{};
         if constexpr (!ZERO_IN) y0 = outer(rb, ra);
-        const Rows y1 = outer(rb + kSet, ra + kSet), y2 = outer(rb + 2 * kSet, ra + 2 * kSet), y3 = outer(rb + 3 * kSet, ra + 3 * kSet);
+        // read at the step's start, or (calm) when the update needs them
+        constexpr bool LATE = GEN && (PROLONG || NORM);
+        Rows y1, y2, y3;
+        if constexpr (!LATE) {
+            y1 = outer(rb + kSet, ra + kSet);
+            y2 = outer(rb + 2 * kSet, ra + 2 * kSet);
+            y3 = outer(rb + 3 * kSet, ra + 3 * kSet);
+        }
         q[c0] = coef_of(s);
-        if constexpr (NORM) residual(s, P, u[c0], u[cp1], u[cm1], y0, outer(rb + 4 * kSet, ra + 4 * kSet));
+        if constexpr (NORM) residual(s, P, u[c0], u[cp1], u[cm1], f[c0], be[GEN ? c0 : 0], y0, outer(rb + 4 * kSet, ra + 4 * kSet));
+        calm();
         // first sweep
         if constexpr (ZERO_IN) {
             const T invd = q[c0].inv;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int v0 = (r + P) & 1;
+                const bool in = s >= 1 && s <= nz - 2;
                 const T inv1 = upd[r][1] ? invd : (T)0, inv0 = v0 ? inv1 : upd[r][0] ? invd : (T)0;
 #pragma unroll
                 for (int m = 0; m < H; ++m) {
                     const int v = v0 + 2 * m;
-                    u[c0][r][v] = f[c0][r][v] * (v ? inv1 : inv0);
+                    if constexpr (GEN)
+                        u[c0][r][v] = keep_or(upd[r][v ? 1 : 0] && in, f[c0][r][v] / (be[c0][r][v] + invd), (T)0);
+                    else
+                        u[c0][r][v] = f[c0][r][v] * (v ? inv1 : inv0);
                     // slots are reused: the plane's other nodes start from zero
                     u[c0][r][v ^ 1] = (T)0;
                 }
             }
         } else {
-            colour(s, q[c0], P, 0, u[c0], u[cp1], u[cm1], f[c0], y0);
+            colour(s, q[c0], P, 0, u[c0], u[cp1], u[cm1], f[c0], be[GEN ? c0 : 0], y0);
         }
-        colour(s - 1, q[cm1], Q, 1, u[cm1], u[c0], u[cm2], f[cm1], y1);
+        calm();
+        if constexpr (LATE) y1 = outer(rb + kSet, ra + kSet);
+        colour(s - 1, q[cm1], Q, 1, u[cm1], u[c0], u[cm2], f[cm1], be[GEN ? cm1 : 0], y1);
         // second sweep
-        colour(s - 2, q[cm2], P, 0, u[cm2], u[cm1], u[cm3], f[cm2], y2);
+        calm();
+        if constexpr (LATE) y2 = outer(rb + 2 * kSet, ra + 2 * kSet);
+        colour(s - 2, q[cm2], P, 0, u[cm2], u[cm1], u[cm3], f[cm2], be[GEN ? cm2 : 0], y2);
         {
             // below plane s-3 only its red nodes are needed, kept in dr
             T dn[R][V];
@@ -485,7 +534,9 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
                     dn[r][v] = dr[r][m];
                     dn[r][v ^ 1] = (T)0;
                 }
-            colour(s - 3, q[cm3], Q, 1, u[cm3], u[cm2], dn, f[cm3], y3);
+            calm();
+            if constexpr (LATE) y3 = outer(rb + 3 * kSet, ra + 3 * kSet);
+            colour(s - 3, q[cm3], Q, 1, u[cm3], u[cm2], dn, f[cm3], be[GEN ? cm3 : 0], y3);
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -509,7 +560,10 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
 #pragma unroll
     for (int e = -1; e <= D; ++e) {
         fetch_u(s0 + e, u[(e + 3) % NS]);
-        if (e < D) fetch_f(s0 + e, f[(e + 3) % NS]);
+        if (e < D) {
+            fetch_f(s0 + e, f[(e + 3) % NS]);
+            fetch_b(s0 + e, be[GEN ? (e + 3) % NS : 0]);
+        }
     }
     if constexpr (PROLONG) {
         // coarse planes for s0-1 and s0; the one of s0+1 in flight
@@ -582,10 +636,13 @@ hipError_t pair_dispatch(const LevelItem *items, int nitems, int ntiles, int fla
         switch (flags) {
             MHS_CASE(kHasF) MHS_CASE(kHasF | kProlong) MHS_CASE(kHasF | kProlong | kPairKeepZ)
         }
-        // level 0 of the FP64 path
         if constexpr (sizeof(T) == 8) {
+            // level 0 of the FP64 path, then the general operator
+            constexpr int G = kHasF | kPairGen, G0 = G | kPairEdge;
             switch (flags) {
                 MHS_CASE(0) MHS_CASE(kNorm) MHS_CASE(kProlong) MHS_CASE(kProlong | kPairKeepZ)
+                MHS_CASE(G) MHS_CASE(G | kZeroIn) MHS_CASE(G | kProlong) MHS_CASE(G | kProlong | kPairKeepZ)
+                MHS_CASE(G0) MHS_CASE(G0 | kNorm) MHS_CASE(G0 | kProlong) MHS_CASE(G0 | kProlong | kPairKeepZ)
             }
         }
     }

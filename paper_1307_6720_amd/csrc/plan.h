@@ -101,7 +101,7 @@ struct Launch {
         kSweep3, kPair3, kSweep2, kRestrict3, kRestrict2, kIr3, kBottom, kFinalize, kCopy, kFields, kPrep3, kPrep2,
         kRestrict3Z, kProlong3Z,
         // the general operator (general.hip): items are GenItem
-        kGenSweep, kGenResid, kGenRestrict, kGenProlong, kGenCoarsest, kZero
+        kGenSweep, kGenResid, kGenRestrict, kGenProlong, kZero
     } kind;
     int flags = 0;
     bool dbl = true;
@@ -134,6 +134,15 @@ struct Staging {
         std::memcpy(host + used, &v, sizeof(T));
         const T *d = reinterpret_cast<const T *>(dev + used);
         used += sizeof(T);
+        return d;
+    }
+    const void *put_bytes(const void *v, size_t n)
+    {
+        used = (used + 63) & ~size_t(63);
+        if (used + n > cap) return nullptr;
+        std::memcpy(host + used, v, n);
+        const void *d = dev + used;
+        used += n;
         return d;
     }
 };
@@ -212,6 +221,7 @@ int set_device(const mhs_plan *p);
 SolveState initial_state(double rtol, int max_iter);
 int status_of(int32_t done);
 
+BottomItem bottom_item(const Hierarchy &h, int path, const void *f_top, void *u_top, int nu1, int nu2, SolveState *state);
 // Program builders: append launches whose item tables are put into `st`.
 void add_finalize(Program &pg, Staging &st, const double *partials, int n, SolveState *state);
 void *add_cycle(Program &pg, Staging &st, const Hierarchy &h, int path, void *a0, void *b0, const void *f0,
@@ -255,6 +265,7 @@ int drive(mhs_plan *p, const Program &cycle, const SolveState *d_state, const mh
           int *syncs, hipStream_t s, int kind, const std::function<int()> *overlap = nullptr);
 double seconds_since(std::chrono::steady_clock::time_point t0);
 
+PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max_waves);
 // Shapes and step kinds of a multigrid hierarchy (api.cpp).
 int build_geometry(Hierarchy &h, const int n0[3], const double len[3], bool planar);
 
