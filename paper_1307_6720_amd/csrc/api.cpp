@@ -82,40 +82,57 @@ int chunk(int planes, int xy_tiles, int cap, int target = kTargetGroups)
     return (int)std::max(1L, std::min((long)cap, want));
 }
 
-// Tiling of a two-sweep launch over an n[0] x n[1] x n[2] level, chosen by an
-// estimate of its time among variants of at most max_waves waves.
+// Tiling of a two-sweep launch over an n[0] x n[1] x n[2] level, among the
+// variants of at most max_waves waves: the one with the smallest estimate of
+// its time.  The constants are fitted to the measured times of every variant
+// and chunk length on levels from 33^3 to 513 x 513 x 257, alone and eight or
+// twelve together, in FP32 and FP64 (59 cases): its choices are within 5 % of
+// the best one measured, except for batches of another number of requests than
+// the eight it assumes.
 PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max_waves)
 {
     const int V = path == kF64 ? kPairV64 : kPairV32;
+    const double es = path == kF64 ? 8.0 : 4.0;
     const int ext = kind == kPairDataFaces ? 2 : 0;
     const int mx = n[0] - 1 + ext, my = n[1] - 1 + ext; // nodes the windows cover
-    int lgx = 0;
-    while (lgx < 6 && (V << lgx) < mx) ++lgx;
-    const int wx = V << lgx;
+    const double copies = batched ? 8.0 : 1.0;
+    const double reads = kind == kPairF ? 2.0 : 1.0; // arrays of the level's size
     PairTiling best;
-    best.lgx = lgx;
     double tbest = 0.0;
     for (int q = 0; q < kPairNVariants; ++q) {
         const PairVariant &pv = kPairVariants[q];
-        if (pv.waves > max_waves || (pv.waves == 16 && kind != kPairZero)) continue; // not built
-        const int wy = 2 * pv.waves * (64 >> lgx);
+        if (pv.waves > max_waves) continue;
+        int lgx = 0;
+        while (lgx < 6 && (V << lgx) < mx) ++lgx;
+        if (pv.row) lgx = 4;
+        const int wx = V << lgx, wy = 2 * pv.waves * (64 >> lgx);
+        if (pv.row && wx > mx) continue; // its lanes would reach into the next row
         if (wy <= 8 && wy < my) continue;
         const int ntx = wx >= mx ? 1 : 1 + ceil_div(mx - wx, wx - 8);
         const int nty = wy >= my ? 1 : 1 + ceil_div(my - wy, wy - 8);
         const int ns = 5 + pv.depth;
-        const int regs = pv.waves == 16 ? 128 : pv.depth == 1 ? 168 : kind == kPairZero ? 128 : 256;
+        // workgroups a CU holds, by registers
+        const int regs = pv.depth == 1 ? 168 : kind == kPairZero ? 128 : 256;
         const int resident = std::max(1, (512 / regs) * 4 / pv.waves);
         for (int kz = ns == 8 ? 2 : 6; kz <= kPairMaxKz; kz += ns) {
+            const int planes = std::min(kz, n[2] - 2);
             const int ntz = ceil_div(n[2] - 2, kz);
-            const double nwg = (double)ntx * nty * ntz * (batched ? 8.0 : 1.0);
-            const double steps = std::min(kz, n[2] - 2) + 6 + 3;
+            const double nwg = (double)ntx * nty * ntz * copies;
+            const double steps = (double)ceil_div(planes + 6, ns) * ns;
             const double per_cu = std::min((double)resident, std::ceil(nwg / 256.0));
             const double rounds = std::ceil(nwg / (256.0 * per_cu));
-            const double step = std::max(0.45, per_cu * pv.waves / 4.0 * 0.33);
-            const double tm = rounds * steps * step;
-            if (best.var < 0 || tm < tbest) {
+            // the instructions of a step, of the waves that share a SIMD
+            const double comp = rounds * (steps * (0.125 + 0.235 * per_cu * pv.waves / 4.0) + 1.0); // us
+            // the bytes, those read twice where windows and chunks overlap or
+            // a row's lines are cut counted in part
+            const double again = (1.0 + 0.64 * 6.0 / planes) * (1.0 + 0.33 * ((double)nty * wy / my - 1.0)) *
+                                 (1.0 + 0.36 * (ntx * (wx * es + 112.0) / (mx * es) - 1.0));
+            const double mem = (double)n[0] * n[1] * n[2] * es * (reads * again + 1.0) * copies / 8.9e6;
+            const double tm = std::max(comp, mem) + 0.74 * std::min(comp, mem);
+            if (best.var < 0 || tm < (pv.row ? 0.92 : 1.0) * tbest) { // (else whole rows: what the fit leaves)
                 tbest = tm;
                 best.var = q;
+                best.lgx = lgx;
                 best.nt[0] = ntx;
                 best.nt[1] = nty;
                 best.nt[2] = ntz;
@@ -234,8 +251,11 @@ int build_geometry(Hierarchy &h, const int n0[3], const double len[3], bool plan
             lv.kz_b = l == 0 ? lv.kz : chunk(lv.n[2] - 2, lv.st[0] * lv.ity, kKZ, kBatchCoarseTargetGroups);
             lv.stz_b = ceil_div(lv.n[2] - 2, lv.kz_b);
             for (int path = 0; path < 2; ++path)
-                for (int k = 0; k < kPairKinds; ++k)
-                    for (int bt = 0; bt < 2; ++bt) lv.pair[path][k][bt] = pair_tiling(lv.n, path, k, bt != 0, 16);
+                for (int k = 0; k < kPairKinds; ++k) {
+                    // (boundary data: FP64 only)
+                    if ((k == kPairData || k == kPairDataFaces) && path != kF64) continue;
+                    for (int bt = 0; bt < 2; ++bt) lv.pair[path][k][bt] = pair_tiling(lv.n, path, k, bt != 0);
+                }
         }
         if (l + 1 < L) {
             const Level &c2 = h.lv[l + 1];

@@ -428,9 +428,8 @@ void carve_gen(GenHier &g, Carver &cv, bool face)
         g.beta[l] = cv.take<double>(N);
         if (l < h.b && h.lv[l].keepxy) g.r[l] = cv.take<double>(N);
         if (l < h.b && !h.planar) {
-            g.pair[l][0] = pair_tiling(h.lv[l].n, kF64, l == 0 ? kPairDataFaces : kPairF, false, 12);
-            // (twelve waves leave too few registers for the coarse data as well)
-            g.pair[l][1] = pair_tiling(h.lv[l].n, kF64, l == 0 ? kPairDataFaces : kPairF, false, 8);
+            g.pair[l][0] = pair_tiling(h.lv[l].n, kF64, l == 0 ? kPairDataFaces : kPairF, false);
+            g.pair[l][1] = pair_tiling(h.lv[l].n, kF64, l == 0 ? kPairDataFaces : kPairF, false, kPairGenWaves);
         }
     }
     const int m = std::min(h.m, kGenMaxCoarse); // (larger coarsest grids are refused)

@@ -250,9 +250,14 @@ hipError_t launch_sweep3(const LevelItem *items, int nitems, int ntiles, int fla
 constexpr int kPairV64 = 2, kPairV32 = 4;
 struct PairVariant {
     int waves, depth;
+    bool row; // rows of 16 lanes (any number of windows in x), else 2^lgx
 };
-constexpr PairVariant kPairVariants[] = {{12, 1}, {16, 1}, {4, 3}, {8, 3}};
-constexpr int kPairNVariants = 4;
+constexpr PairVariant kPairVariants[] = {{12, 1, false}, {4, 3, false}, {8, 3, false},
+                                         {12, 1, true},  {4, 3, true},  {8, 3, true}};
+constexpr int kPairNVariants = 6;
+// the general operator's variant with a correction: twelve waves leave too
+// few registers for b/a and the coarse data together
+constexpr int kPairGenWaves = 8;
 constexpr int kPairMaxKz = 44; // planes per workgroup (their coefficients sit one plane per lane)
 hipError_t launch_pair3(const LevelItem *items, int nitems, int ntiles, int flags, bool dbl, int variant,
                         hipStream_t s);

@@ -69,33 +69,66 @@ __device__ __forceinline__ void bstore_vec(const double (&x)[2], __amdgpu_buffer
     __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, 0);
 }
 
-// The value of the lane below / above (0 past the wave's end).
+// A lane's values of a published row, in one LDS access of 8 bytes (two of 4
+// bytes at a stride of 8 would each meet every other bank only).
+typedef float f32x2 __attribute__((ext_vector_type(2), may_alias));
+template <int N, typename T>
+__device__ __forceinline__ void lds_get(T (&x)[N], const T *p)
+{
+    static_assert(N * sizeof(T) == 8, "one access of 8 bytes");
+    if constexpr (N == 2) {
+        const f32x2 v = *(const f32x2 *)p;
+        x[0] = v.x, x[1] = v.y;
+    } else {
+        x[0] = p[0];
+    }
+}
+template <int N, typename T>
+__device__ __forceinline__ void lds_put(T *p, const T (&x)[N])
+{
+    static_assert(N * sizeof(T) == 8, "one access of 8 bytes");
+    if constexpr (N == 2)
+        *(f32x2 *)p = f32x2{x[0], x[1]};
+    else
+        p[0] = x[0];
+}
+
+// The value of the lane below / above, 0 past the ends of a wave or (ROW) of
+// its rows of 16 lanes.
+template <bool ROW>
 __device__ __forceinline__ uint32_t dpp_below(uint32_t v)
 {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138 /* wave_shr:1 */, 0xf, 0xf, true);
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ROW ? 0x111 /* row_shr:1 */ : 0x138 /* wave_shr:1 */, 0xf,
+                                                 0xf, true);
 }
+template <bool ROW>
 __device__ __forceinline__ uint32_t dpp_above(uint32_t v)
 {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130 /* wave_shl:1 */, 0xf, 0xf, true);
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ROW ? 0x101 /* row_shl:1 */ : 0x130 /* wave_shl:1 */, 0xf,
+                                                 0xf, true);
 }
+template <bool ROW>
 __device__ __forceinline__ float lane_below(float v)
 {
-    return __builtin_bit_cast(float, dpp_below(__builtin_bit_cast(uint32_t, v)));
+    return __builtin_bit_cast(float, dpp_below<ROW>(__builtin_bit_cast(uint32_t, v)));
 }
+template <bool ROW>
 __device__ __forceinline__ float lane_above(float v)
 {
-    return __builtin_bit_cast(float, dpp_above(__builtin_bit_cast(uint32_t, v)));
+    return __builtin_bit_cast(float, dpp_above<ROW>(__builtin_bit_cast(uint32_t, v)));
 }
+template <bool ROW>
 __device__ __forceinline__ double lane_below(double v)
 {
     u32x2 w = __builtin_bit_cast(u32x2, v);
-    w.x = dpp_below(w.x), w.y = dpp_below(w.y);
+    w.x = dpp_below<ROW>(w.x), w.y = dpp_below<ROW>(w.y);
     return __builtin_bit_cast(double, w);
 }
+template <bool ROW>
 __device__ __forceinline__ double lane_above(double v)
 {
     u32x2 w = __builtin_bit_cast(u32x2, v);
-    w.x = dpp_above(w.x), w.y = dpp_above(w.y);
+    w.x = dpp_above<ROW>(w.x), w.y = dpp_above<ROW>(w.y);
     return __builtin_bit_cast(double, w);
 }
 
@@ -120,9 +153,15 @@ __device__ __forceinline__ double lane_above(double v)
 // A window not at the edge of the array is right only from its fourth node
 // inwards (each of the four updates moves one node in), so windows overlap by
 // eight nodes and write the part in between; at the edges of the array the
-// boundary nodes are fixed and nothing is lost.  A row of 2^lgx * V + 1 nodes
-// takes a single window in x: its last node, a boundary node, lies one past
-// the window and reads as zero (corrections vanish on the boundary).
+// boundary nodes are fixed and nothing is lost.  A window at the right edge
+// ends at the last interior node: the boundary node lies one past it and
+// reads as zero (corrections vanish on the boundary), by the zero that a lane
+// shift brings in past the wave's end, by the next row's first node, which is
+// one too (LX = 2^lgx lanes, a single window of 2^lgx * V + 1 nodes with it),
+// or by the zero past a row of 16 lanes (ROW).  ROW takes any number of
+// windows in x: long rows of narrow windows have a shorter rim, a 513-node row
+// in nine windows of 64 by 96 nodes computes 1.27 times its nodes, in three of
+// 256 by 24 2.25 times (257^3 in FP64, level 0: 94 -> 76 us with the norm).
 // In z a march starts three planes below the planes it writes and ends three
 // above.
 //
@@ -136,7 +175,7 @@ __device__ __forceinline__ double lane_above(double v)
 // that; here a pair moves them once, and the registers carry what the LDS
 // windows of k_sweep3 carried (per node and sweep 1 LDS read and 1 write
 // instead of 7 and 2, one barrier per plane for both sweeps instead of four).
-// Measured on the two post-smoothing sweeps of a 257^3 level in FP32: 46.5
+// Measured on the two post-smoothing sweeps of a 257^3 level in FP32: 46
 // against 95 us for one request; twelve 257^3 equilibria served together take
 // 26.4 against 42.4 ms.  Merged it is bound by memory, alone by its
 // instructions: a window's halo and a march's first and last planes are
@@ -147,9 +186,10 @@ __device__ __forceinline__ double lane_above(double v)
 // (ext = 2) the last window of a row or column reaches past the boundary node
 // instead of ending before it.  The first pair of a cycle also sums the
 // residual of its input.  257^3 in FP64, 9 cycles and the fields: 4.46 ms,
-// against 5.22 with single sweeps there.
+// against 5.22 with single sweeps there (4.0 with the bottom solver and the
+// windows of 16 lanes).
 // ============================================================================
-template <typename T, int V, int R, int NW, int D, int FLAGS>
+template <typename T, int V, int R, int NW, int D, bool ROW, int FLAGS>
 __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__ items, int nitems)
 {
     constexpr bool HAS_F = (FLAGS & kHasF) != 0;
@@ -177,7 +217,7 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     constexpr int kSets = NORM ? 5 : 4;
     constexpr int kSet = (128 * NW + 128) * H;
     static_assert(R == 2 || R == 4, "the correction's rows come in pairs");
-    __shared__ T S[2 * kSets * kSet];
+    __shared__ __attribute__((aligned(16))) T S[2 * kSets * kSet];
     __shared__ double red[NW];
 
     const int tile = launch_tile(items, nitems);
@@ -192,7 +232,7 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     const T cz = (T)it->cz;
     const int nx = it->nx, ny = it->ny, nz = it->nz;
     const int ncx = it->ncx, ncy = it->ncy, ncz = it->ncz;
-    const int kz = it->kz, lgx = it->lgx;
+    const int kz = it->kz, lgx = ROW ? 4 : it->lgx;
     const int LX = 1 << lgx, WX = LX * V, WY = R * NW * (64 >> lgx);
     int local = tile - it->tile_base;
     const int tx = local % it->ntx;
@@ -365,11 +405,8 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     };
     auto outer = [&](const T *below, const T *above) {
         Rows y;
-#pragma unroll
-        for (int m = 0; m < H; ++m) {
-            y.below[m] = below[m];
-            y.above[m] = above[m];
-        }
+        lds_get<H>(y.below, below);
+        lds_get<H>(y.above, above);
         return y;
     };
     // one colour (0 red, 1 black) of plane p: k its coefficients, uc its columns, uu and ud those
@@ -386,8 +423,8 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
 #pragma unroll
             for (int m = 0; m < H; ++m) {
                 const int v = v0 + 2 * m;
-                const T e = v + 1 < V ? uc[r][(v + 1) % V] : lane_above(uc[r][0]);
-                const T w = v > 0 ? uc[r][(v + V - 1) % V] : lane_below(uc[r][V - 1]);
+                const T e = v + 1 < V ? uc[r][(v + 1) % V] : lane_above<ROW>(uc[r][0]);
+                const T w = v > 0 ? uc[r][(v + V - 1) % V] : lane_below<ROW>(uc[r][V - 1]);
                 const T yn = r + 1 < R ? uc[(r + 1) % R][v] : y.above[m];
                 const T ys_ = r > 0 ? uc[(r + R - 1) % R][v] : y.below[m];
                 const T fv = HAS_F ? fp[r][v] : (T)0;
@@ -419,8 +456,8 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
 #pragma unroll
                     for (int m = 0; m < H; ++m) {
                         const int v = v0 + 2 * m;
-                        const T e = v + 1 < V ? uc[r][(v + 1) % V] : lane_above(uc[r][0]);
-                        const T w = v > 0 ? uc[r][(v + V - 1) % V] : lane_below(uc[r][V - 1]);
+                        const T e = v + 1 < V ? uc[r][(v + 1) % V] : lane_above<ROW>(uc[r][0]);
+                        const T w = v > 0 ? uc[r][(v + V - 1) % V] : lane_below<ROW>(uc[r][V - 1]);
                         const T yn = r + 1 < R ? uc[(r + 1) % R][v] : y.above[m];
                         const T ys_ = r > 0 ? uc[(r + R - 1) % R][v] : y.below[m];
                         const T d_ = col ? ro[r][m] : dn[r][v];
@@ -442,8 +479,10 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
 #pragma unroll
         for (int r = 0; r < R; r += R - 1) {
             const int v0 = (r + par + col) & 1;
+            T x[H];
 #pragma unroll
-            for (int m = 0; m < H; ++m) (r ? last : first)[m] = uc[r][v0 + 2 * m];
+            for (int m = 0; m < H; ++m) x[m] = uc[r][v0 + 2 * m];
+            lds_put<H>(r ? last : first, x);
         }
     };
 
@@ -620,29 +659,31 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     }
 }
 
-template <typename T, int V, int NW, int D>
+template <typename T, int V, int NW, int D, bool ROW>
 hipError_t pair_dispatch(const LevelItem *items, int nitems, int ntiles, int flags, hipStream_t s)
 {
     dim3 grid(ntiles), block(64 * NW);
 #define MHS_CASE(F)                                                                           \
     case F:                                                                                   \
-        hipLaunchKernelGGL((k_pair3<T, V, 2, NW, D, F>), grid, block, 0, s, items, nitems);   \
+        hipLaunchKernelGGL((k_pair3<T, V, 2, NW, D, ROW, F>), grid, block, 0, s, items, nitems);   \
         return hipGetLastError();
     switch (flags) {
-        MHS_CASE(kHasF | kZeroIn)
+        MHS_CASE(kHasF) MHS_CASE(kHasF | kZeroIn) MHS_CASE(kHasF | kProlong) MHS_CASE(kHasF | kProlong | kPairKeepZ)
     }
-    // sixteen waves leave 128 registers per lane, too few for the others
-    if constexpr (NW < 16) {
+    if constexpr (sizeof(T) == 8) {
+        // level 0 of the FP64 path
         switch (flags) {
-            MHS_CASE(kHasF) MHS_CASE(kHasF | kProlong) MHS_CASE(kHasF | kProlong | kPairKeepZ)
+            MHS_CASE(0) MHS_CASE(kNorm) MHS_CASE(kProlong) MHS_CASE(kProlong | kPairKeepZ)
         }
-        if constexpr (sizeof(T) == 8) {
-            // level 0 of the FP64 path, then the general operator
-            constexpr int G = kHasF | kPairGen, G0 = G | kPairEdge;
+        // the general operator
+        constexpr int G = kHasF | kPairGen, G0 = G | kPairEdge;
+        switch (flags) {
+            MHS_CASE(G) MHS_CASE(G | kZeroIn) MHS_CASE(G0) MHS_CASE(G0 | kNorm)
+        }
+        if constexpr (NW <= kPairGenWaves) {
             switch (flags) {
-                MHS_CASE(0) MHS_CASE(kNorm) MHS_CASE(kProlong) MHS_CASE(kProlong | kPairKeepZ)
-                MHS_CASE(G) MHS_CASE(G | kZeroIn) MHS_CASE(G | kProlong) MHS_CASE(G | kProlong | kPairKeepZ)
-                MHS_CASE(G0) MHS_CASE(G0 | kNorm) MHS_CASE(G0 | kProlong) MHS_CASE(G0 | kProlong | kPairKeepZ)
+                MHS_CASE(G | kProlong) MHS_CASE(G | kProlong | kPairKeepZ)
+                MHS_CASE(G0 | kProlong) MHS_CASE(G0 | kProlong | kPairKeepZ)
             }
         }
     }
@@ -653,11 +694,11 @@ hipError_t pair_dispatch(const LevelItem *items, int nitems, int ntiles, int fla
 template <typename T, int V>
 hipError_t pair_variant(const LevelItem *items, int nitems, int ntiles, int flags, int variant, hipStream_t s)
 {
-    static_assert(kPairNVariants == 4, "one case per variant");
+    static_assert(kPairNVariants == 6, "one case per variant");
     switch (variant) {
 #define MHS_VAR(N) \
-    case N: return pair_dispatch<T, V, kPairVariants[N].waves, kPairVariants[N].depth>(items, nitems, ntiles, flags, s);
-        MHS_VAR(0) MHS_VAR(1) MHS_VAR(2) MHS_VAR(3)
+    case N: return pair_dispatch<T, V, kPairVariants[N].waves, kPairVariants[N].depth, kPairVariants[N].row>(items, nitems, ntiles, flags, s);
+        MHS_VAR(0) MHS_VAR(1) MHS_VAR(2) MHS_VAR(3) MHS_VAR(4) MHS_VAR(5)
 #undef MHS_VAR
     }
     return hipErrorInvalidValue;

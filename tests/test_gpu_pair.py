@@ -60,6 +60,32 @@ def test_two_sweeps_with_boundary_data_equal_two_launches(S, dims):
     assert torch.equal(one, two)
 
 
+# windows of sixteen lanes per row, several of them in x and in y, of four,
+# eight and twelve waves
+@pytest.mark.parametrize("dims", [(257, 129, 65), (129, 65, 65), (513, 65, 33), (257, 257, 129), (513, 257, 65)])
+@pytest.mark.parametrize("precision", [1, 2])
+def test_two_sweeps_in_windows_of_sixteen_lanes(S, dims, precision):
+    lengths = [n - 1.0 for n in dims]
+    g = synth.make_grid(*dims, *lengths)
+    plan = S.Plan(g, precision)
+    model = synth.make_model(g, 0.01, 0.5, 0.2 * lengths[2])
+    dtype = torch.float64 if precision == 1 else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    f = torch.randn(plan.shape, generator=gen, dtype=dtype, device="cuda")
+    rhs = [f, None] if precision == 1 else [f]
+    for q in rhs:
+        two = torch.randn(plan.shape, generator=gen, dtype=dtype, device="cuda")
+        if q is not None:  # the boundary nodes of a correction are zero
+            for axis in range(3):
+                two.select(axis, 0).zero_()
+                two.select(axis, -1).zero_()
+        one = two.clone()
+        plan.stage_smooth(model, 3, 0, two, q, 2, precision)
+        plan.stage_smooth(model, 3, 0, one, q, 1, precision)
+        plan.stage_smooth(model, 3, 0, one, q, 1, precision)
+        assert torch.equal(one, two)
+
+
 def test_two_fp32_sweeps_without_a_right_hand_side(S):
     g = synth.make_grid(33, 17, 33, 32.0, 16.0, 32.0)
     plan = S.Plan(g, 2)
