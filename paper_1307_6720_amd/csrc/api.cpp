@@ -86,7 +86,7 @@ int chunk(int planes, int xy_tiles, int cap, int target = kTargetGroups)
 // variants of at most max_waves waves: the one with the smallest estimate of
 // its time.  The constants are fitted to the measured times of every variant
 // and chunk length on levels from 33^3 to 513 x 513 x 257, alone and eight or
-// twelve together, in FP32 and FP64 (59 cases): its choices are within 5 % of
+// twelve together, in FP32 and FP64 (91 cases): its choices are within 5 % of
 // the best one measured, except for batches of another number of requests than
 // the eight it assumes.
 PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max_waves)
@@ -95,8 +95,21 @@ PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max
     const double es = path == kF64 ? 8.0 : 4.0;
     const int ext = kind == kPairDataFaces ? 2 : 0;
     const int mx = n[0] - 1 + ext, my = n[1] - 1 + ext; // nodes the windows cover
+    const bool rest = kind == kPairRestF || kind == kPairRestZero;
+    const int over = rest ? kPairOverRest : kPairOver;
+    const int halo = rest ? 11 : 6; // planes of a march besides those it writes
     const double copies = batched ? 8.0 : 1.0;
-    const double reads = kind == kPairF ? 2.0 : 1.0; // arrays of the level's size
+    // arrays of the level's size read and written
+    const double reads = kind == kPairF || kind == kPairRestF ? 2.0 : 1.0, writes = rest ? 1.125 : 1.0;
+    // us of a step and per wave of a SIMD, us of a workgroup; MB/us; what is
+    // counted of the bytes read twice in z, in y and by lines cut in x; what
+    // of the smaller of the two times is not hidden
+    struct Cost {
+        double step, wave, group, rate, z, y, x, rest;
+    };
+    constexpr Cost kPlain{0.125, 0.235, 1.0, 8.9, 0.64, 0.33, 0.36, 0.74};
+    constexpr Cost kRest{0.45, 0.30, 1.6, 6.5, 0.87, 0.07, 0.10, 0.45};
+    const Cost &c = rest ? kRest : kPlain;
     PairTiling best;
     double tbest = 0.0;
     for (int q = 0; q < kPairNVariants; ++q) {
@@ -107,29 +120,30 @@ PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max
         if (pv.row) lgx = 4;
         const int wx = V << lgx, wy = 2 * pv.waves * (64 >> lgx);
         if (pv.row && wx > mx) continue; // its lanes would reach into the next row
-        if (wy <= 8 && wy < my) continue;
-        const int ntx = wx >= mx ? 1 : 1 + ceil_div(mx - wx, wx - 8);
-        const int nty = wy >= my ? 1 : 1 + ceil_div(my - wy, wy - 8);
-        const int ns = 5 + pv.depth;
-        // workgroups a CU holds, by registers
+        if (wy <= over && wy < my) continue;
+        const int ntx = wx >= mx ? 1 : 1 + ceil_div(mx - wx, wx - over);
+        const int nty = wy >= my ? 1 : 1 + ceil_div(my - wy, wy - over);
+        // a march ends after a whole round of steps, with the restriction and
+        // short rounds after any two
+        const int round = pv.depth == 1 ? 6 : rest ? 2 : 8;
+        // workgroups a CU holds, by registers and LDS
         const int regs = pv.depth == 1 ? 168 : kind == kPairZero ? 128 : 256;
-        const int resident = std::max(1, (512 / regs) * 4 / pv.waves);
-        for (int kz = ns == 8 ? 2 : 6; kz <= kPairMaxKz; kz += ns) {
+        const int resident = rest && pv.waves == 8 ? 1 : std::max(1, (512 / regs) * 4 / pv.waves);
+        const double y = 1.0 + c.y * ((double)nty * wy / my - 1.0);
+        const double x = 1.0 + c.x * (ntx * (wx * es + 112.0) / (mx * es) - 1.0);
+        for (int kz = pv.depth == 1 ? 6 : 2; kz <= kPairMaxKz; kz += round == 2 ? (kz < 10 ? 2 : kz < 18 ? 4 : 8) : round) {
             const int planes = std::min(kz, n[2] - 2);
             const int ntz = ceil_div(n[2] - 2, kz);
             const double nwg = (double)ntx * nty * ntz * copies;
-            const double steps = (double)ceil_div(planes + 6, ns) * ns;
+            const double steps = (double)ceil_div(planes + halo, round) * round;
             const double per_cu = std::min((double)resident, std::ceil(nwg / 256.0));
             const double rounds = std::ceil(nwg / (256.0 * per_cu));
-            // the instructions of a step, of the waves that share a SIMD
-            const double comp = rounds * (steps * (0.125 + 0.235 * per_cu * pv.waves / 4.0) + 1.0); // us
-            // the bytes, those read twice where windows and chunks overlap or
-            // a row's lines are cut counted in part
-            const double again = (1.0 + 0.64 * 6.0 / planes) * (1.0 + 0.33 * ((double)nty * wy / my - 1.0)) *
-                                 (1.0 + 0.36 * (ntx * (wx * es + 112.0) / (mx * es) - 1.0));
-            const double mem = (double)n[0] * n[1] * n[2] * es * (reads * again + 1.0) * copies / 8.9e6;
-            const double tm = std::max(comp, mem) + 0.74 * std::min(comp, mem);
-            if (best.var < 0 || tm < (pv.row ? 0.92 : 1.0) * tbest) { // (else whole rows: what the fit leaves)
+            const double comp = rounds * (steps * (c.step + c.wave * per_cu * pv.waves / 4.0) + c.group);
+            const double again = (1.0 + c.z * halo / planes) * y * x;
+            const double mem = (double)n[0] * n[1] * n[2] * es * (reads * again + writes) * copies / (c.rate * 1e6);
+            // (whole rows unless the others gain more than the fit's error)
+            const double tm = (std::max(comp, mem) + c.rest * std::min(comp, mem)) * (pv.row ? 1.087 : 1.0);
+            if (best.var < 0 || tm < tbest) {
                 tbest = tm;
                 best.var = q;
                 best.lgx = lgx;
@@ -250,12 +264,9 @@ int build_geometry(Hierarchy &h, const int n0[3], const double len[3], bool plan
             lv.st[2] = ceil_div(lv.n[2] - 2, lv.kz);
             lv.kz_b = l == 0 ? lv.kz : chunk(lv.n[2] - 2, lv.st[0] * lv.ity, kKZ, kBatchCoarseTargetGroups);
             lv.stz_b = ceil_div(lv.n[2] - 2, lv.kz_b);
-            for (int path = 0; path < 2; ++path)
-                for (int k = 0; k < kPairKinds; ++k) {
-                    // (boundary data: FP64 only)
-                    if ((k == kPairData || k == kPairDataFaces) && path != kF64) continue;
-                    for (int bt = 0; bt < 2; ++bt) lv.pair[path][k][bt] = pair_tiling(lv.n, path, k, bt != 0);
-                }
+            // (their partial sums are part of the workspace)
+            if (l == 0)
+                for (int k : {kPairData, kPairDataFaces}) lv.pair[kF64][k][0] = pair_tiling(lv.n, kF64, k, false);
         }
         if (l + 1 < L) {
             const Level &c2 = h.lv[l + 1];
@@ -330,6 +341,21 @@ size_t carve_plan(mhs_plan *p, char *base, int precisions)
     p->stage.cap = kStagingBytes;
     if (precisions & MHS_PLAN_GENERAL) gen_create(p, cv);
     return cv.off + kAlign;
+}
+
+// Tilings of the two-sweep launches of the paths in `paths`, and of merged
+// launches (`merged`).
+void tile_pairs(Hierarchy &h, int paths, bool merged)
+{
+    for (int l = 0; l < h.L; ++l)
+        for (int path = 0; path < 2; ++path)
+            for (int k = 0; k < kPairKinds; ++k) {
+                const bool data = k == kPairData || k == kPairDataFaces;
+                if (!(paths & (1 << path)) || (data && path != kF64)) continue;
+                Level &lv = h.lv[l];
+                for (int bt = 0; bt < (merged ? 2 : 1); ++bt)
+                    if (lv.pair[path][k][bt].var < 0) lv.pair[path][k][bt] = pair_tiling(lv.n, path, k, bt != 0);
+            }
 }
 
 int geometry(mhs_plan *p, const mhs_grid *g)
@@ -737,7 +763,7 @@ LevelItem level_item(const Hierarchy &h, int l, int path)
 }
 
 void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, const void *uin, void *uout,
-               const void *f, const void *ec, int flags, SolveState *state, double *partials)
+               const void *f, const void *ec, int flags, SolveState *state, double *partials, void *fc = nullptr)
 {
     LevelItem it = level_item(h, l, path);
     const Level &lv = h.lv[l];
@@ -756,7 +782,8 @@ void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, co
     it.ntz = bt ? lv.stz_b : lv.st[2];
     it.kz = bt ? lv.kz_b : lv.kz;
     // (the norm's partial sums depend on the tiling: the single request's)
-    const int kind = !f ? (h.faces ? kPairDataFaces : kPairData) : (flags & kZeroIn) ? kPairZero : kPairF;
+    const int kind = !f ? (h.faces ? kPairDataFaces : kPairData)
+                        : (flags & kZeroIn) ? (fc ? kPairRestZero : kPairZero) : (fc ? kPairRestF : kPairF);
     const PairTiling &pt = lv.pair[path][kind][h.batched && !(flags & kNorm) ? 1 : 0];
     if (pair3) {
         it.ext = kind == kPairDataFaces ? 2 : 0;
@@ -765,6 +792,7 @@ void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, co
         it.nty = pt.nt[1];
         it.ntz = pt.nt[2];
         it.kz = pt.kz;
+        if (fc) it.r_out = fc;
     }
     it.tile_base = 0;
     const LevelItem *d = st.put(it);
@@ -776,7 +804,8 @@ void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, co
     L.kind = h.planar ? Launch::kSweep2 : pair3 ? Launch::kPair3 : Launch::kSweep3;
     L.flags = flags | (f ? kHasF : 0);
     if (pair3) {
-        if ((flags & kProlong) && lv.keepz) L.flags |= kPairKeepZ;
+        if (fc) L.flags |= kPairRestrict;
+        if (((flags & kProlong) || fc) && lv.keepz) L.flags |= kPairKeepZ;
         L.flags |= pt.var << kPairVariantShift;
     }
     L.dbl = path == kF64;
@@ -790,7 +819,7 @@ void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, co
         if (!(L.flags & kZeroIn)) words += 1.0;  // read u
         if (L.flags & kHasF) words += 1.0;       // read f
         L.bytes = es * words * (double)lv.N;
-        if ((L.flags & kProlong) && l + 1 < h.L) L.bytes += es * (double)h.lv[l + 1].N;
+        if (((L.flags & kProlong) || fc) && l + 1 < h.L) L.bytes += es * (double)h.lv[l + 1].N;
     }
     L.pre = (flags & kNorm) != 0;
     pg.launches.push_back(L);
@@ -958,13 +987,21 @@ void *add_cycle(Program &pg, Staging &st, const Hierarchy &h, int path, void *a0
     void *cur = a0, *oth = b0;
     // sweeps s0 .. n-1 of level l after the first, ping-pong between c and
     // o, two per launch
-    auto more = [&](int l, void *&c, void *&o, const void *f, int s0, int n) {
+    auto more = [&](int l, void *&c, void *&o, const void *f, int s0, int n, void *fc) {
         for (int s = s0; s < n;) {
             const bool pair = s + 1 < n;
-            add_sweep(pg, st, h, l, path, c, o, f, nullptr, pair ? kTwoSweeps : 0, state, nullptr);
+            add_sweep(pg, st, h, l, path, c, o, f, nullptr, pair ? kTwoSweeps : 0, state, nullptr,
+                      s + 2 == n ? fc : nullptr);
             std::swap(c, o);
             s += pair ? 2 : 1;
         }
+    };
+    // the coarse right-hand side of level l, if the last two pre-smoothing
+    // sweeps write it as well (in 3D with a right-hand side, where a pair of
+    // sweeps comes last and the step halves x and y), else the restriction does
+    auto fused = [&](int l, const void *f) -> void * {
+        const Level &lv = h.lv[l];
+        return !h.planar && f && nu1 % 2 == 0 && !lv.keepxy ? h.lv[l + 1].f[path] : nullptr;
     };
     // the first sweep (flags) and the second with it
     auto pair_first = [&](int n) { return n >= 2 ? kTwoSweeps : 0; };
@@ -972,22 +1009,24 @@ void *add_cycle(Program &pg, Staging &st, const Hierarchy &h, int path, void *a0
         int flags = pair_first(nu1);
         if (first_zero) flags |= kZeroIn;
         if (first_norm) flags |= kNorm;
-        add_sweep(pg, st, h, 0, path, cur, oth, f0, nullptr, flags, state, h.partials);
+        void *fc = first_norm ? nullptr : fused(0, f0);
+        add_sweep(pg, st, h, 0, path, cur, oth, f0, nullptr, flags, state, h.partials, nu1 == 2 ? fc : nullptr);
         std::swap(cur, oth);
         if (first_norm) add_finalize(pg, st, h.partials, pg.ok ? pg.launches.back().ntiles : 0, state);
-        more(0, cur, oth, f0, (flags & kTwoSweeps) ? 2 : 1, nu1);
+        more(0, cur, oth, f0, (flags & kTwoSweeps) ? 2 : 1, nu1, fc);
+        if (!fc) add_restrict(pg, st, h, 0, path, cur, f0, h.lv[1].f[path], state);
     }
-    add_restrict(pg, st, h, 0, path, cur, f0, h.lv[1].f[path], state);
     void *lcur[kMaxLevels] = {};
     for (int l = 1; l < b; ++l) {
         const Level &lv = h.lv[l];
         void *c = lv.u[path], *o = lv.t[path];
         // first sweep from a zero guess writes lv.u
         const int fl = kZeroIn | pair_first(nu1);
-        add_sweep(pg, st, h, l, path, nullptr, c, lv.f[path], nullptr, fl, state, nullptr);
-        more(l, c, o, lv.f[path], (fl & kTwoSweeps) ? 2 : 1, nu1);
+        void *fc = fused(l, lv.f[path]);
+        add_sweep(pg, st, h, l, path, nullptr, c, lv.f[path], nullptr, fl, state, nullptr, nu1 == 2 ? fc : nullptr);
+        more(l, c, o, lv.f[path], (fl & kTwoSweeps) ? 2 : 1, nu1, fc);
         lcur[l] = c;
-        add_restrict(pg, st, h, l, path, c, lv.f[path], h.lv[l + 1].f[path], state);
+        if (!fc) add_restrict(pg, st, h, l, path, c, lv.f[path], h.lv[l + 1].f[path], state);
     }
     add_bottom(pg, st, h, path, h.lv[b].f[path], h.lv[b].u[path], nu1, nu2, state);
     const void *ec = h.lv[b].u[path];
@@ -998,14 +1037,14 @@ void *add_cycle(Program &pg, Staging &st, const Hierarchy &h, int path, void *a0
         const int fl = pair_first(nu2);
         add_correct_sweep(pg, st, h, l, path, c, o, lv.f[path], ec, state, fl);
         std::swap(c, o);
-        more(l, c, o, lv.f[path], fl ? 2 : 1, nu2);
+        more(l, c, o, lv.f[path], fl ? 2 : 1, nu2, nullptr);
         ec = c;
     }
     {
         const int fl = pair_first(nu2);
         add_correct_sweep(pg, st, h, 0, path, cur, oth, f0, ec, state, fl);
         std::swap(cur, oth);
-        more(0, cur, oth, f0, fl ? 2 : 1, nu2);
+        more(0, cur, oth, f0, fl ? 2 : 1, nu2, nullptr);
     }
     return cur;
 }
@@ -1556,6 +1595,7 @@ int mhs_plan_create(const mhs_grid *grid, int32_t precisions, void *d_ws, size_t
     p->ws = (char *)d_ws;
     p->ws_bytes = ws_bytes;
     carve_plan(p, p->ws, precisions);
+    tile_pairs(p->h3, precisions & 3, true);
     if (hipHostMalloc((void **)&p->stage.host, kStagingBytes, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&p->h_states, 4 * sizeof(SolveState), hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&p->stage.inflight, hipEventDisableTiming) != hipSuccess) {
@@ -2323,6 +2363,7 @@ int mhs_solve_interior_noalloc(const mhs_grid *grid, const mhs_model *model, dou
     p.ws = slot.dev;
     p.ws_bytes = kScratchBytes;
     const size_t used = carve_plan(&p, p.ws, o->precision) - kAlign;
+    tile_pairs(p.h3, o->precision, false);
     p.stage.host = g_scratch_stage[dev];
     p.h_states = slot.states;
     hipStream_t s = (hipStream_t)stream;

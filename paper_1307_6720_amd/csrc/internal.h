@@ -105,7 +105,7 @@ struct LevelItem {
     const void *f;      // right-hand side, nullptr = 0
     const void *ec;     // coarse correction added before smoothing, or FP32 e (refinement)
     union {
-        void *r_out;      // refinement: FP32 residual output
+        void *r_out;      // refinement: FP32 residual output; pair kernel: coarse right-hand side
         const void *beta; // general operator: b/a per node
     };
     const void *coef;   // per-plane {cx, cy, d, 1/d} in the stage's arithmetic type
@@ -231,8 +231,9 @@ enum SweepFlags : int {
     kPairKeepZ = 32, // two sweeps in 3D: the step to the coarse level keeps z
     kPairGen = 64,   // two sweeps in 3D, or 2D sweeps: the general operator (a diagonal per node)
     kPairEdge = 128, // two sweeps in 3D: boundary nodes carry data although there is a right-hand side
+    kPairRestrict = 256, // two sweeps in 3D: the result's residual goes, restricted, to r_out
     // launch flags of the 3D two-sweep kernel carry its variant from this bit on
-    kPairVariantShift = 8,
+    kPairVariantShift = 9,
     kPairVariantBit = 1 << kPairVariantShift,
 };
 
@@ -258,6 +259,8 @@ constexpr int kPairNVariants = 6;
 // the general operator's variant with a correction: twelve waves leave too
 // few registers for b/a and the coarse data together
 constexpr int kPairGenWaves = 8;
+// nodes that neighbouring windows overlap by, without and with the restriction
+constexpr int kPairOver = 8, kPairOverRest = 12;
 constexpr int kPairMaxKz = 44; // planes per workgroup (their coefficients sit one plane per lane)
 hipError_t launch_pair3(const LevelItem *items, int nitems, int ntiles, int flags, bool dbl, int variant,
                         hipStream_t s);

@@ -188,6 +188,19 @@ __device__ __forceinline__ double lane_above(double v)
 // residual of its input.  257^3 in FP64, 9 cycles and the fields: 4.46 ms,
 // against 5.22 with single sweeps there (4.0 with the bottom solver and the
 // windows of 16 lanes).
+//
+// kPairRestrict: the launch that ends a level's pre-smoothing also restricts
+// its residual (full weighting, as k_restrict3, whose expressions and order of
+// sums it keeps: the coarse right-hand sides are the same bits).  At step s the
+// residual of plane s-4 is taken from the registers, its outer y neighbours
+// from the published rows; a thread has one coarse row, whose lower fine row
+// another thread weights in x and publishes.  A coarse node reaches two nodes
+// further than a smoothed one, so windows overlap by twelve nodes and a march
+// is five steps longer.  It saves reading u and f again (8 of 20.5 bytes per
+// node in FP32) and a launch per level: level 0 of 513 x 513 x 257 mixed 198 +
+// 149 -> 255 us, of 257^3 46 + 35 -> 58 us, its 65^3 level 6.9 + 6.4 -> 12.7;
+// 257^3 mixed in all 3.28 -> 3.06 ms.  With the restriction among the updates
+// twelve waves spill, so there it comes after them.
 // ============================================================================
 template <typename T, int V, int R, int NW, int D, bool ROW, int FLAGS>
 __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__ items, int nitems)
@@ -203,6 +216,10 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     // the general operator: a diagonal of its own at every node
     constexpr bool GEN = (FLAGS & kPairGen) != 0;
     constexpr bool KEEP = DATA || GEN; // nodes that are not updated keep their values
+    // the residual of the result, restricted to the coarse right-hand side
+    constexpr bool REST = (FLAGS & kPairRestrict) != 0;
+    static_assert(!REST || !(KEEP || NORM || PROLONG), "the last pre-smoothing sweeps of a correction");
+    constexpr int OV = REST ? kPairOverRest : kPairOver; // nodes that windows overlap by
     static_assert(!DATA || V == 2, "the right edge of a window with data is masked per node of a pair");
     static_assert(!NORM || DATA, "the norm is taken on level 0");
     constexpr int H = V / 2;
@@ -214,10 +231,13 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     // lane and row), a row of zeros below and above it; four sets (old black
     // of plane s+1, red of s, black of s-1, red of s-2), two buffers
     // (with the norm a fifth: old red of plane s+1)
-    constexpr int kSets = NORM ? 5 : 4;
+    // (with the restriction a fifth: black of plane s-3)
+    constexpr int kSets = NORM || REST ? 5 : 4;
     constexpr int kSet = (128 * NW + 128) * H;
+    // and the residual of the row above each coarse row, for the thread above
+    constexpr int kSetC = REST ? (64 * NW + 64) * H : 0;
     static_assert(R == 2 || R == 4, "the correction's rows come in pairs");
-    __shared__ __attribute__((aligned(16))) T S[2 * kSets * kSet];
+    __shared__ __attribute__((aligned(16))) T S[2 * kSets * kSet + 2 * kSetC];
     __shared__ double red[NW];
 
     const int tile = launch_tile(items, nitems);
@@ -228,6 +248,7 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     const MHS_GLOBAL T *__restrict__ fin = gin<T>(it->f);
     const MHS_GLOBAL T *__restrict__ ec = gin<T>(it->ec);
     const MHS_GLOBAL T *__restrict__ bin = gin<T>(it->beta);
+    MHS_GLOBAL T *__restrict__ fco = gout<T>(it->r_out);
     const MHS_CONST T *__restrict__ coef = gconst<T>(it->coef);
     const T cz = (T)it->cz;
     const int nx = it->nx, ny = it->ny, nz = it->nz;
@@ -241,10 +262,10 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     const int tz = local / it->nty;
     const bool lastx = tx == it->ntx - 1, lasty = ty == it->nty - 1;
     const int ext = DATA ? it->ext : 0;
-    const int iw = lastx ? max(nx - 1 + ext - WX, 0) : tx * (WX - 8); // window origin (even)
-    const int jw = lasty ? max(ny - 1 + ext - WY, 0) : ty * (WY - 8);
-    const int xs = tx ? tx * (WX - 8) + 4 : 0, xe = lastx ? nx - 1 : (tx + 1) * (WX - 8) + 4; // nodes written
-    const int ys = ty ? ty * (WY - 8) + 4 : 0, ye = lasty ? ny - 1 : (ty + 1) * (WY - 8) + 4;
+    const int iw = lastx ? max(nx - 1 + ext - WX, 0) : tx * (WX - OV); // window origin (even)
+    const int jw = lasty ? max(ny - 1 + ext - WY, 0) : ty * (WY - OV);
+    const int xs = tx ? tx * (WX - OV) + 4 : 0, xe = lastx ? nx - 1 : (tx + 1) * (WX - OV) + 4; // nodes written
+    const int ys = ty ? ty * (WY - OV) + 4 : 0, ye = lasty ? ny - 1 : (ty + 1) * (WY - OV) + 4;
     const int kb = 1 + tz * kz;
     const int ke = min(kb + kz, nz - 1);
     const size_t sxy = (size_t)nx * ny, csxy = (size_t)ncx * ncy;
@@ -272,6 +293,7 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     // above them, at a0 + 0 .. 3 times the row's length
     const int LH = LX * H;
     const int a0 = 2 * t * LH + lx * H;
+    const int c0_ = t * LH + lx * H;
     // coarse rows from j0/2, columns i0/2 .. i0/2 + V/2
     const uint32_t cg = es * (uint32_t)((i0 >> 1) + ncx * (j0 >> 1));
     // the rows past the window's ends stay zero
@@ -281,8 +303,21 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         S[set * kSet + (2 * NW * (64 >> lgx) + 1) * LX * H + q] = (T)0;
     }
 
-    // planes s0-1 .. (at most 64): cx, cy, 1/d
-    const int s0 = max(kb - 3, 0) & ~1;
+    // coarse nodes written (2 I, 2 J): two nodes further in
+    uint32_t rog[H];
+    if constexpr (REST) {
+        const int cxs = tx ? xs + 2 : 2, cxe = lastx ? nx - 1 : xe + 2;
+        const int cys = ty ? ys + 2 : 2, cye = lasty ? ny - 1 : ye + 2;
+#pragma unroll
+        for (int m = 0; m < H; ++m) {
+            const int i = i0 + 2 * m;
+            rog[m] = i >= cxs && i < cxe && j0 >= cys && j0 < cye ? es * (uint32_t)((i >> 1) + ncx * (j0 >> 1))
+                                                                  : cplane_bytes;
+        }
+    }
+
+    // planes s0-4 .. (at most 64): cx, cy, 1/d
+    const int s0 = max(kb - (REST ? 4 : 3), 0) & ~1;
     // (the general operator's are the same on every plane)
     PlaneTab<T> tcx, tcy, tid_, tdd;
     T gcx = (T)0, gcy = (T)0, gdd = (T)0;
@@ -294,18 +329,22 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         tcx.load(coef, s0 - 4, 0, nz);
         tcy.load(coef, s0 - 4, 1, nz);
         tid_.load(coef, s0 - 4, 3, nz);
-        if constexpr (NORM) tdd.load(coef, s0 - 4, 2, nz);
+        if constexpr (NORM || REST) tdd.load(coef, s0 - 4, 2, nz);
     }
 
     T u[NS][R][V], f[NS][R][V], be[GEN ? NS : 1][R][V];
     T dr[R][H]; // red nodes of plane s-4
+    // restriction: black nodes of plane s-4, both colours of plane s-5; the
+    // residuals of plane s-5 weighted in x (row 0 and 1); the coarse row's sum
+    // over the planes below it
+    T db[R][H], dbb[R][H], drr[R][H], rx[R][H], sum[H];
     // prolongation: coarse rows interpolated to the thread's two rows, of the
     // coarse plane below and above; the next coarse plane in flight
     T ya[R][H + 1], yb[R][H + 1], raw[RC][H + 1];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
 #pragma unroll
-        for (int h = 0; h < H; ++h) dr[r][h] = (T)0;
+        for (int h = 0; h < H; ++h) dr[r][h] = db[r][h] = dbb[r][h] = drr[r][h] = rx[r][h] = sum[h] = (T)0;
 #pragma unroll
         for (int q = 0; q < NS; ++q)
 #pragma unroll
@@ -486,10 +525,11 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         }
     };
 
+    Rows y3p{}; // restriction: y3 of the step before
     // the general operator's divisions leave no registers for overlapping the
     // updates
     auto calm = [] {
-        if constexpr (GEN && (PROLONG || NORM)) __builtin_amdgcn_sched_barrier(0);
+        if constexpr ((GEN && (PROLONG || NORM)) || (REST && D == 1 && !ZERO_IN)) __builtin_amdgcn_sched_barrier(0);
     };
     // one step at plane s; d: its position in the round of NS steps (s0 is
     // even, so the plane's parity is d's).  Plane s + e lives in slot
@@ -505,6 +545,16 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         asm volatile("" : "+s"(so), "+s"(wo));
         const T *rb = S + (a0 + so), *ra = S + (a0 + (so + 3 * LH));
         T *w0 = S + (a0 + (wo + LH)), *w1 = S + (a0 + (wo + 2 * LH));
+        T rbelow[H] = {}; // residuals of plane s-5 in the row below, weighted in x
+        Rows yr{};        // black nodes of plane s-4
+        auto read_rest = [&] {
+            if constexpr (REST) {
+                int sc = 2 * kSets * kSet + Q * kSetC;
+                asm volatile("" : "+s"(sc));
+                lds_get<H>(rbelow, S + (c0_ + sc));
+                yr = outer(rb + 4 * kSet, ra + 4 * kSet);
+            }
+        };
         fetch_u(s + 1 + D, u[cnx]);
         fetch_f(s + D, f[cnf]);
         fetch_b(s + D, be[GEN ? cnf : 0]);
@@ -521,12 +571,15 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         Rows y0{};
         if constexpr (!ZERO_IN) y0 = outer(rb, ra);
         // read at the step's start, or (calm) when the update needs them
-        constexpr bool LATE = GEN && (PROLONG || NORM);
+        // twelve waves: the restriction after the updates, not among them
+        constexpr bool CALM = REST && D == 1 && !ZERO_IN;
+        constexpr bool LATE = (GEN && (PROLONG || NORM)) || CALM;
         Rows y1, y2, y3;
         if constexpr (!LATE) {
             y1 = outer(rb + kSet, ra + kSet);
             y2 = outer(rb + 2 * kSet, ra + 2 * kSet);
             y3 = outer(rb + 3 * kSet, ra + 3 * kSet);
+            read_rest();
         }
         q[c0] = coef_of(s);
         if constexpr (NORM) residual(s, P, u[c0], u[cp1], u[cm1], f[c0], be[GEN ? c0 : 0], y0, outer(rb + 4 * kSet, ra + 4 * kSet));
@@ -576,6 +629,63 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
             calm();
             if constexpr (LATE) y3 = outer(rb + 3 * kSet, ra + 3 * kSet);
             colour(s - 3, q[cm3], Q, 1, u[cm3], u[cm2], dn, f[cm3], be[GEN ? cm3 : 0], y3);
+            if constexpr (CALM) {
+                __builtin_amdgcn_sched_barrier(0);
+                read_rest();
+            }
+            if constexpr (REST) {
+                // full weighting: the plane s-5, complete with the row below
+                const T q4 = (T)0.25, h2 = (T)0.5;
+                T s2[H];
+#pragma unroll
+                for (int m = 0; m < H; ++m) s2[m] = q4 * rbelow[m] + h2 * rx[0][m] + q4 * rx[1][m];
+                const int pc = KEEPZ ? s - 5 : s - 6; // fine plane of the coarse one
+                if constexpr (KEEPZ || P == 0) {
+                    const auto rs = plane_rsrc(fco + csxy * (size_t)max(KEEPZ ? pc : pc >> 1, 0),
+                                               pc >= kb && pc < ke ? cplane_bytes : 0u);
+#pragma unroll
+                    for (int m = 0; m < H; ++m) bstore(KEEPZ ? s2[m] : sum[m] + q4 * s2[m], rs, rog[m]);
+                }
+#pragma unroll
+                for (int m = 0; m < H; ++m) sum[m] = P == 0 ? q4 * s2[m] : sum[m] + h2 * s2[m];
+                // residual of plane s-4
+                const T cx = q[cnx].cx, cy = q[cnx].cy, dd = tdd(s - 4);
+                auto at = [&](int r, int v) -> T { return (r + P + v) & 1 ? db[r][v >> 1] : dr[r][v >> 1]; };
+                T rv[R][V];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        const bool black = (r + P + v) & 1;
+                        const T e = v + 1 < V ? at(r, (v + 1) % V) : lane_above<ROW>(at(r, 0));
+                        const T w = v > 0 ? at(r, (v + V - 1) % V) : lane_below<ROW>(at(r, V - 1));
+                        const Rows &y = black ? y3p : yr;
+                        const T yn = r + 1 < R ? at((r + 1) % R, v) : y.above[v >> 1];
+                        const T ys_ = r > 0 ? at((r + R - 1) % R, v) : y.below[v >> 1];
+                        const T dn = black ? drr[r][v >> 1] : dbb[r][v >> 1];
+                        rv[r][v] = f[cnx][r][v] - (cx * (e + w) + cy * (yn + ys_) + cz * (u[cm3][r][v] + dn) +
+                                                   dd * at(r, v));
+                    }
+#pragma unroll
+                    for (int m = 0; m < H; ++m) {
+                        const T w = m > 0 ? rv[r][(2 * m + V - 1) % V] : lane_below<ROW>(rv[r][V - 1]);
+                        rx[r][m] = q4 * w + h2 * rv[r][2 * m] + q4 * rv[r][2 * m + 1];
+                    }
+                }
+                y3p = y3;
+                int sc = 2 * kSets * kSet + P * kSetC;
+                asm volatile("" : "+s"(sc));
+                lds_put<H>(S + (c0_ + (sc + LH)), rx[1]);
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int m = 0; m < H; ++m) {
+                        drr[r][m] = dr[r][m];
+                        dbb[r][m] = db[r][m];
+                        db[r][m] = u[cm3][r][((r + Q + 1) & 1) + 2 * m];
+                    }
+                publish(Q, 1, u[cm3], w0 + 4 * kSet, w1 + 4 * kSet);
+            }
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -640,15 +750,20 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
             for (int m = 0; m < H; ++m) ro[r][m] = u[2][r][((r + 1) & 1) + 2 * m]; // old red of plane s0-1
     }
     lds_barrier();
-    const int send = ke + 2; // the last step writes plane ke - 1
+    // the last step writes plane ke - 1, with the restriction coarse plane
+    // ke - 1 or (ke - 1) / 2
+    const int send = REST ? ke + (KEEPZ ? 4 : 5) : ke + 2;
     for (int s = s0; s <= send; s += NS) {
         step(s, std::integral_constant<int, 0>{});
         step(s + 1, std::integral_constant<int, 1>{});
+        if (REST && D == 3 && s + 2 > send) break;
         step(s + 2, std::integral_constant<int, 2>{});
         step(s + 3, std::integral_constant<int, 3>{});
+        if (REST && D == 3 && s + 4 > send) break;
         step(s + 4, std::integral_constant<int, 4>{});
         step(s + 5, std::integral_constant<int, 5>{});
         if constexpr (NS == 8) {
+            if (REST && D == 3 && s + 6 > send) break;
             step(s + 6, std::integral_constant<int, 6>{});
             step(s + 7, std::integral_constant<int, 7>{});
         }
@@ -669,6 +784,8 @@ hipError_t pair_dispatch(const LevelItem *items, int nitems, int ntiles, int fla
         return hipGetLastError();
     switch (flags) {
         MHS_CASE(kHasF) MHS_CASE(kHasF | kZeroIn) MHS_CASE(kHasF | kProlong) MHS_CASE(kHasF | kProlong | kPairKeepZ)
+        MHS_CASE(kHasF | kPairRestrict) MHS_CASE(kHasF | kPairRestrict | kPairKeepZ)
+        MHS_CASE(kHasF | kZeroIn | kPairRestrict) MHS_CASE(kHasF | kZeroIn | kPairRestrict | kPairKeepZ)
     }
     if constexpr (sizeof(T) == 8) {
         // level 0 of the FP64 path

@@ -46,8 +46,10 @@ struct PairTiling {
 // Kinds of two-sweep launches with a tiling of their own: with a right-hand
 // side, the same from a zero guess, and without one (level 0 of the FP64 path,
 // whose boundary nodes carry data) when the data on the side faces are zero
-// or given.
-enum PairKind : int { kPairF = 0, kPairZero = 1, kPairData = 2, kPairDataFaces = 3, kPairKinds = 4 };
+// or given; the first two also with the restriction of their residual.
+enum PairKind : int {
+    kPairF = 0, kPairZero = 1, kPairData = 2, kPairDataFaces = 3, kPairRestF = 4, kPairRestZero = 5, kPairKinds = 6
+};
 
 struct Level {
     int n[3] = {0, 0, 0}; // nx, ny, nz (nz = 1 for the 2D problem)
