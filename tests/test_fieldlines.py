@@ -257,3 +257,18 @@ def test_gpu_field_lines_edge_cases():
             trace_field_lines(plan, *B, seeds, kw["ds"], 3, kw["bmin"])
     torch.cuda.synchronize()
     plan.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nlines", [1, 3, 15, 16, 17, 63, 65])
+@pytest.mark.parametrize("ds", [0.004, 0.3])
+def test_gpu_field_lines_in_quads_of_lanes(nlines, ds):
+    """Line counts around the sixteen of a wave, steps within a cell (whose
+    corners stay in registers) and across many: every line as the oracle's."""
+    lengths = (1.0, 0.5, 2.0)
+    B = smooth_field((33, 9, 17), lengths, 3)
+    rng = np.random.default_rng(nlines)
+    seeds = rng.uniform(0.0, 1.0, size=(nlines, 3)) * np.array(lengths)
+    got = gpu_trace(synth.make_grid(17, 9, 33, *lengths), B, seeds, ds, 60, 0.01)
+    want = ofl.trace(*B, seeds, ds, 60, 0.01, lengths)
+    assert compare_lines(got, want) <= 1e-13
