@@ -57,6 +57,7 @@ constexpr int kCoarseTargetGroups = MHS_COARSE_TARGET_GROUPS;
 #endif
 constexpr int kBatchCoarseTargetGroups = MHS_BATCH_COARSE_TARGET_GROUPS;
 constexpr int kFieldsTargetGroups = 2048;
+constexpr int kDiagResident = 1024; // workgroups of the diagnostics that run at once
 // Largest coarsest grid (unknowns) a model may cut the 3D hierarchy to.
 constexpr int kMaxCutCoarse = 512;
 
@@ -2009,7 +2010,16 @@ int mhs_diagnostics(mhs_plan *p, const mhs_model *model, const double *d_Bx, con
     it.nx = nx;
     it.ny = ny;
     it.nz = nz;
-    it.kz = chunk(nz, ceil_div(nx, 64) * ceil_div(ny, 4), 64, kFieldsTargetGroups);
+    {
+        // the chunk that fills whole rounds of resident workgroups best (two
+        // planes of a chunk are read twice)
+        const long tiles = ceil_div(nx * ny, kDiagCols);
+        double best = 0.0;
+        for (int kz = 4; kz <= 64; ++kz) {
+            const double t = std::ceil((double)tiles * ceil_div(nz, kz) / kDiagResident) * (std::min(kz, nz) + 2);
+            if (it.kz == 0 || t < best) best = t, it.kz = kz;
+        }
+    }
     hipStream_t s = (hipStream_t)stream;
     Profiler &pr = p->prof;
     const bool timed = ((pr.mask >> MHS_PROF_DIAG) & 1) != 0;

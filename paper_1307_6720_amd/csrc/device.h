@@ -64,7 +64,6 @@ __device__ __forceinline__ void bstore(double v, __amdgpu_buffer_rsrc_t r, uint3
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, 0);
 }
-
 template <typename Item>
 __device__ __forceinline__ int find_item(const Item *items, int n, int tile)
 {

@@ -188,7 +188,9 @@ struct DiagItem {
     int32_t kz; // planes per workgroup
 };
 
-// Field-line tracing: one thread per line (seeds and points x, y, z
+constexpr int kDiagCols = 248; // (x, y) columns per workgroup
+
+// Field-line tracing: four lanes per line (seeds and points x, y, z
 // interleaved; points of step n at 3 (n nlines + l)).
 struct TraceItem {
     const double *Bx, *By, *Bz;

@@ -1535,27 +1535,50 @@ __global__ __launch_bounds__(kFThreads) void k_fields(const FieldsItem *__restri
 // Diagnostics of equations (1)-(3): j = curl B / mu0, the force-balance
 // residual |j x B - grad p - rho g e_z| and div B, by the differences of the
 // field recovery (central; one-sided second order at the base plane), zero on
-// the side and top faces.  One thread per (x, y) column marches a chunk of
-// planes; the values it needs on plane k+1 (its column of Bx, By, Bz, p and
-// their in-plane neighbours, rho) are loaded while plane k is computed.
-// In-plane neighbours come from the caches (the kernel is a diagnostic, off
-// the solve's path).  Contraction is off so that every value is rounded as
-// the differences are written (the oracle evaluates the same expressions).
+// the side and top faces.  A thread has an (x, y) column and marches a chunk
+// of planes; the values it needs on plane k+1 (its column of Bx, By, Bz, p,
+// their y neighbours, rho) are loaded while plane k is computed.  Contraction
+// is off so that every value is rounded as the differences are written (the
+// oracle evaluates the same expressions).
+//
+// Columns are taken in memory order, kDCols per wave with one more on either
+// side, so that the x neighbours are the next lanes' registers and rows of any
+// length fill their waves (side columns, whose neighbours are in other rows,
+// are zero).  The y neighbours come from the caches: workgroups of one XCD take
+// contiguous columns, so its L2 has the rows above and below.  257^3: 505 -> 400
+// us against one thread per column of 64 x 4 tiles (five x tiles for 257 nodes,
+// 21 loads per node instead of 13); 1.36 GB at 3.4 TB/s.  Multiplications for
+// the divisions saved 4 %, the y neighbours' loads cost 8 %: its ten streams
+// bound it.
 // ============================================================================
-constexpr int kDX = 64, kDY = 4;
-static_assert(kDX * kDY == kThreads, "diagnostics tile is one workgroup");
+constexpr int kDCols = 62; // columns a wave writes
+static_assert(kDiagCols == kDCols * (kThreads / 64), "columns of a workgroup");
+
+// The value of the lane below / above.
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double v)
+{
+    typedef int i32x2 __attribute__((ext_vector_type(2)));
+    i32x2 w = __builtin_bit_cast(i32x2, v);
+    w.x = __builtin_amdgcn_update_dpp(0, w.x, CTRL, 0xf, 0xf, true);
+    w.y = __builtin_amdgcn_update_dpp(0, w.y, CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, w);
+}
 
 __global__ __launch_bounds__(kThreads) void k_diag(const DiagItem it)
 {
 #pragma clang fp contract(off)
-    const int i = blockIdx.x * kDX + (int)(threadIdx.x % kDX);
-    const int j = blockIdx.y * kDY + (int)(threadIdx.x / kDX);
     const int nx = it.nx, ny = it.ny, nz = it.nz;
-    if (i >= nx || j >= ny) return;
-    const int k0 = blockIdx.z * it.kz;
+    const int nxy = (nx * ny + kDiagCols - 1) / kDiagCols;
+    const int tile = xcd_tile(), lane = (int)threadIdx.x & 63;
+    const int at = (tile % nxy) * kDiagCols + ((int)threadIdx.x >> 6) * kDCols + lane - 1;
+    const int own = min(max(at, 0), nx * ny - 1);
+    const bool writes = lane >= 1 && lane <= kDCols && at < nx * ny;
+    const int i = own % nx, j = own / nx;
+    const int k0 = (tile / nxy) * it.kz;
     const int k1 = min(k0 + it.kz, nz);
     const size_t sxy = (size_t)nx * ny;
-    const size_t col = (size_t)i + (size_t)nx * j;
+    const size_t col = (size_t)own;
     const bool side = i == 0 || i == nx - 1 || j == 0 || j == ny - 1;
     const MHS_GLOBAL double *Bx = gin<double>(it.Bx), *By = gin<double>(it.By), *Bz = gin<double>(it.Bz);
     const MHS_GLOBAL double *pp = gin<double>(it.p), *rho = gin<double>(it.rho);
@@ -1563,21 +1586,20 @@ __global__ __launch_bounds__(kThreads) void k_diag(const DiagItem it)
     MHS_GLOBAL double *ofr = gout<double>(it.fres), *odv = gout<double>(it.divb);
     const double tdx = 2.0 * it.dx, tdy = 2.0 * it.dy, tdz = 2.0 * it.dz;
     // in-plane neighbour offsets (clamped: side columns write zeros anyway)
-    const size_t xm = col - (i > 0 ? 1 : 0), xp = col + (i < nx - 1 ? 1 : 0);
     const size_t ym = col - (j > 0 ? (size_t)nx : 0), yp = col + (j < ny - 1 ? (size_t)nx : 0);
     struct Col {
         double bx, by, bz, p;
     };
-    // in-plane neighbours of the column on one plane, and rho there
+    // y neighbours of the column on one plane, and rho there
     struct Nb {
-        double bx_xp, bx_xm, bx_yp, bx_ym, by_xp, by_xm, by_yp, by_ym;
-        double bz_xp, bz_xm, bz_yp, bz_ym, p_xp, p_xm, p_yp, p_ym, rho;
+        double bx_yp, bx_ym, by_yp, by_ym, bz_yp, bz_ym, p_yp, p_ym, rho;
     };
     // byte offsets within a plane; loads go through per-plane buffer
-    // resources, so the per-lane address state is these five words
-    const uint32_t bc = 8u * (uint32_t)col, bxp = 8u * (uint32_t)xp, bxm = 8u * (uint32_t)xm;
+    // resources, so the per-lane address state is these four words
+    const uint32_t bc = 8u * (uint32_t)col;
     const uint32_t byp = 8u * (uint32_t)yp, bym = 8u * (uint32_t)ym;
     const uint32_t plane_bytes = 8u * (uint32_t)sxy;
+    const uint32_t out = writes ? bc : plane_bytes; // (past the plane's end a store is dropped)
     auto load_col = [&](int k) {
         const size_t pl = sxy * (size_t)min(max(k, 0), nz - 1);
         return Col{bload<double>(plane_rsrc(Bx + pl, plane_bytes), bc), bload<double>(plane_rsrc(By + pl, plane_bytes), bc),
@@ -1588,13 +1610,9 @@ __global__ __launch_bounds__(kThreads) void k_diag(const DiagItem it)
         const auto rx = plane_rsrc(Bx + pl, plane_bytes), ry = plane_rsrc(By + pl, plane_bytes);
         const auto rz = plane_rsrc(Bz + pl, plane_bytes), rp = plane_rsrc(pp + pl, plane_bytes);
         Nb q;
-        q.bx_xp = bload<double>(rx, bxp), q.bx_xm = bload<double>(rx, bxm);
         q.bx_yp = bload<double>(rx, byp), q.bx_ym = bload<double>(rx, bym);
-        q.by_xp = bload<double>(ry, bxp), q.by_xm = bload<double>(ry, bxm);
         q.by_yp = bload<double>(ry, byp), q.by_ym = bload<double>(ry, bym);
-        q.bz_xp = bload<double>(rz, bxp), q.bz_xm = bload<double>(rz, bxm);
         q.bz_yp = bload<double>(rz, byp), q.bz_ym = bload<double>(rz, bym);
-        q.p_xp = bload<double>(rp, bxp), q.p_xm = bload<double>(rp, bxm);
         q.p_yp = bload<double>(rp, byp), q.p_ym = bload<double>(rp, bym);
         q.rho = bload<double>(plane_rsrc(rho + pl, plane_bytes), bc);
         return q;
@@ -1608,6 +1626,11 @@ __global__ __launch_bounds__(kThreads) void k_diag(const DiagItem it)
         const Nb nbn = load_nb(k + 1);
         const Col w = k == 0 ? u2 : u; // plane 2 for the one-sided base difference
         double jx = 0.0, jy = 0.0, jz = 0.0, fr = 0.0, dv = 0.0;
+        constexpr int kBelow = 0x138 /* wave_shr:1 */, kAbove = 0x130 /* wave_shl:1 */;
+        const double ddx_bx = lane_shift<kAbove>(c.bx) - lane_shift<kBelow>(c.bx);
+        const double ddx_by = lane_shift<kAbove>(c.by) - lane_shift<kBelow>(c.by);
+        const double ddx_bz = lane_shift<kAbove>(c.bz) - lane_shift<kBelow>(c.bz);
+        const double ddx_p = lane_shift<kAbove>(c.p) - lane_shift<kBelow>(c.p);
         if (!side && k < nz - 1) {
             const Nb &q = nb;
             // z-derivatives: central, or one-sided at the base
@@ -1623,10 +1646,10 @@ __global__ __launch_bounds__(kThreads) void k_diag(const DiagItem it)
                 dzbz = (-3.0 * c.bz + 4.0 * u.bz - w.bz) / tdz;
                 dzp = (-3.0 * c.p + 4.0 * u.p - w.p) / tdz;
             }
-            const double dxbx = (q.bx_xp - q.bx_xm) / tdx, dybx = (q.bx_yp - q.bx_ym) / tdy;
-            const double dxby = (q.by_xp - q.by_xm) / tdx, dyby = (q.by_yp - q.by_ym) / tdy;
-            const double dxbz = (q.bz_xp - q.bz_xm) / tdx, dybz = (q.bz_yp - q.bz_ym) / tdy;
-            const double dxp = (q.p_xp - q.p_xm) / tdx, dyp = (q.p_yp - q.p_ym) / tdy;
+            const double dxbx = ddx_bx / tdx, dybx = (q.bx_yp - q.bx_ym) / tdy;
+            const double dxby = ddx_by / tdx, dyby = (q.by_yp - q.by_ym) / tdy;
+            const double dxbz = ddx_bz / tdx, dybz = (q.bz_yp - q.bz_ym) / tdy;
+            const double dxp = ddx_p / tdx, dyp = (q.p_yp - q.p_ym) / tdy;
             jx = (dybz - dzby) / it.mu0;
             jy = (dzbx - dxbz) / it.mu0;
             jz = (dxby - dybx) / it.mu0;
@@ -1637,11 +1660,11 @@ __global__ __launch_bounds__(kThreads) void k_diag(const DiagItem it)
             dv = dxbx + dyby + dzbz;
         }
         const size_t pl = sxy * (size_t)k;
-        bstore(jx, plane_rsrc(ojx + pl, plane_bytes), bc);
-        bstore(jy, plane_rsrc(ojy + pl, plane_bytes), bc);
-        bstore(jz, plane_rsrc(ojz + pl, plane_bytes), bc);
-        bstore(fr, plane_rsrc(ofr + pl, plane_bytes), bc);
-        bstore(dv, plane_rsrc(odv + pl, plane_bytes), bc);
+        bstore(jx, plane_rsrc(ojx + pl, plane_bytes), out);
+        bstore(jy, plane_rsrc(ojy + pl, plane_bytes), out);
+        bstore(jz, plane_rsrc(ojz + pl, plane_bytes), out);
+        bstore(fr, plane_rsrc(ofr + pl, plane_bytes), out);
+        bstore(dv, plane_rsrc(odv + pl, plane_bytes), out);
         m = c;
         c = u;
         u = u2;
@@ -2086,9 +2109,8 @@ hipError_t launch_fields(const FieldsItem *items, int nitems, int ntiles, hipStr
 
 hipError_t launch_diag(const DiagItem &item, hipStream_t s)
 {
-    const dim3 grid((unsigned)((item.nx + kDX - 1) / kDX), (unsigned)((item.ny + kDY - 1) / kDY),
-                    (unsigned)((item.nz + item.kz - 1) / item.kz));
-    hipLaunchKernelGGL(k_diag, grid, dim3(kThreads), 0, s, item);
+    const unsigned nxy = (unsigned)((item.nx * item.ny + kDiagCols - 1) / kDiagCols);
+    hipLaunchKernelGGL(k_diag, dim3(nxy * (unsigned)((item.nz + item.kz - 1) / item.kz)), dim3(kThreads), 0, s, item);
     return hipGetLastError();
 }
 

@@ -163,6 +163,14 @@ def test_gpu_diagnostics_match_oracle(shape, lengths, seed):
         assert np.all(gt[walls(gt.shape)] == 0.0), name
 
 
+# fewer columns than a workgroup has, rows shorter and longer than a wave, one
+# chunk of planes and several
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(5, 5, 9), (9, 5, 5), (17, 65, 9), (257, 9, 65), (65, 9, 257)])
+def test_gpu_diagnostics_on_small_and_thin_grids(shape):
+    test_gpu_diagnostics_match_oracle(shape, (1.0, 0.7, 1.1), sum(shape))
+
+
 @pytest.mark.gpu
 def test_gpu_diagnostics_of_a_solved_equilibrium():
     """The 129^3 workload through the whole GPU path, then the diagnostics:
