@@ -772,7 +772,7 @@ void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, co
     it.u_in = uin;
     it.u_out = uout;
     it.f = f;
-    it.ec = ec;
+    it.ec = fc ? fc : ec;
     it.state = state;
     it.partials = partials;
     // levels >= 1 have no reductions: their z-chunking does not change a
@@ -793,7 +793,6 @@ void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, co
         it.nty = pt.nt[1];
         it.ntz = pt.nt[2];
         it.kz = pt.kz;
-        if (fc) it.r_out = fc;
     }
     it.tile_base = 0;
     const LevelItem *d = st.put(it);
@@ -803,9 +802,8 @@ void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, co
     }
     Launch L{};
     L.kind = h.planar ? Launch::kSweep2 : pair3 ? Launch::kPair3 : Launch::kSweep3;
-    L.flags = flags | (f ? kHasF : 0);
+    L.flags = flags | (f ? kHasF : 0) | (fc ? kPairRestrict : 0);
     if (pair3) {
-        if (fc) L.flags |= kPairRestrict;
         if (((flags & kProlong) || fc) && lv.keepz) L.flags |= kPairKeepZ;
         L.flags |= pt.var << kPairVariantShift;
     }
@@ -998,11 +996,11 @@ void *add_cycle(Program &pg, Staging &st, const Hierarchy &h, int path, void *a0
         }
     };
     // the coarse right-hand side of level l, if the last two pre-smoothing
-    // sweeps write it as well (in 3D with a right-hand side, where a pair of
-    // sweeps comes last and the step halves x and y), else the restriction does
+    // sweeps write it as well (with a right-hand side, where a pair of sweeps
+    // comes last and the step halves x and y), else the restriction does
     auto fused = [&](int l, const void *f) -> void * {
         const Level &lv = h.lv[l];
-        return !h.planar && f && nu1 % 2 == 0 && !lv.keepxy ? h.lv[l + 1].f[path] : nullptr;
+        return f && nu1 % 2 == 0 && !lv.keepxy ? h.lv[l + 1].f[path] : nullptr;
     };
     // the first sweep (flags) and the second with it
     auto pair_first = [&](int n) { return n >= 2 ? kTwoSweeps : 0; };
@@ -1010,7 +1008,7 @@ void *add_cycle(Program &pg, Staging &st, const Hierarchy &h, int path, void *a0
         int flags = pair_first(nu1);
         if (first_zero) flags |= kZeroIn;
         if (first_norm) flags |= kNorm;
-        void *fc = first_norm ? nullptr : fused(0, f0);
+        void *fc = first_norm && !h.planar ? nullptr : fused(0, f0); // (no such variant in 3D)
         add_sweep(pg, st, h, 0, path, cur, oth, f0, nullptr, flags, state, h.partials, nu1 == 2 ? fc : nullptr);
         std::swap(cur, oth);
         if (first_norm) add_finalize(pg, st, h.partials, pg.ok ? pg.launches.back().ntiles : 0, state);
@@ -1597,6 +1595,7 @@ int mhs_plan_create(const mhs_grid *grid, int32_t precisions, void *d_ws, size_t
     p->ws_bytes = ws_bytes;
     carve_plan(p, p->ws, precisions);
     tile_pairs(p->h3, precisions & 3, true);
+    gen_tile_pairs(p);
     if (hipHostMalloc((void **)&p->stage.host, kStagingBytes, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&p->h_states, 4 * sizeof(SolveState), hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&p->stage.inflight, hipEventDisableTiming) != hipSuccess) {

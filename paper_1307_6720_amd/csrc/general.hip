@@ -427,10 +427,8 @@ void carve_gen(GenHier &g, Carver &cv, bool face)
         g.f[l] = cv.take<double>(N);
         g.beta[l] = cv.take<double>(N);
         if (l < h.b && h.lv[l].keepxy) g.r[l] = cv.take<double>(N);
-        if (l < h.b && !h.planar) {
-            g.pair[l][0] = pair_tiling(h.lv[l].n, kF64, l == 0 ? kPairDataFaces : kPairF, false);
-            g.pair[l][1] = pair_tiling(h.lv[l].n, kF64, l == 0 ? kPairDataFaces : kPairF, false, kPairGenWaves);
-        }
+        if (l == 0 && h.b > 0 && !h.planar) // (its partial sums are part of the workspace)
+            g.pair[0][0] = pair_tiling(h.lv[0].n, kF64, kPairDataFaces, false);
     }
     const int m = std::min(h.m, kGenMaxCoarse); // (larger coarsest grids are refused)
     g.minv = cv.take<double>((size_t)m * m);
@@ -561,18 +559,19 @@ struct GenCycle {
         pg.launches.push_back(L);
     }
     // one launch of one or (kTwoSweeps) two sweeps, uin -> uout
-    void sweep(int l, const double *uin, double *uout, const double *ec, int flags)
+    // (fc: on a face, the restriction of the residual as well)
+    void sweep(int l, const double *uin, double *uout, const double *ec, int flags, double *fc = nullptr)
     {
         const Hierarchy &h = g.geo;
         const Level &lv = h.lv[l];
         LevelItem it = item(l);
         it.u_in = uin;
         it.u_out = uout;
-        it.ec = ec;
+        it.ec = fc ? fc : ec;
         double words = 4.0 - ((flags & kZeroIn) ? 1.0 : 0.0);
         double bytes = 8.0 * words * (double)lv.N;
         if (ec) bytes += 8.0 * (double)h.lv[l + 1].N;
-        flags |= kHasF | kPairGen;
+        flags |= kHasF | kPairGen | (fc ? kPairRestrict : 0);
         if (h.planar) {
             it.ntx = lv.st[0];
             it.nty = lv.st[1];
@@ -604,14 +603,15 @@ struct GenCycle {
     }
     // n sweeps of level l from cur (first: kZeroIn, kNorm or kProlong with
     // ec), ping-pong with oth; the norm's finalize follows its launch
-    void sweeps(int l, double *&cur, double *&oth, int n, int first, const double *ec)
+    // (fc: the last two also write the coarse right-hand side)
+    void sweeps(int l, double *&cur, double *&oth, int n, int first, const double *ec, double *fc = nullptr)
     {
         const Hierarchy &h = g.geo;
         const Level &lv = h.lv[l];
         int s = 0;
         if (h.planar || (n >= 2 && !(lv.keepxy && ec))) {
             const int two = n >= 2 ? kTwoSweeps : 0;
-            sweep(l, (first & kZeroIn) ? nullptr : cur, oth, ec, first | two);
+            sweep(l, (first & kZeroIn) ? nullptr : cur, oth, ec, first | two, n == 2 ? fc : nullptr);
             if (first & kNorm) finalize(pg.launches.back().ntiles);
             std::swap(cur, oth);
             s = two ? 2 : 1;
@@ -637,7 +637,7 @@ struct GenCycle {
         while (s < n) {
             if (h.planar || n - s >= 2) {
                 const int two = n - s >= 2 ? kTwoSweeps : 0;
-                sweep(l, cur, oth, nullptr, two);
+                sweep(l, cur, oth, nullptr, two, s + 2 == n ? fc : nullptr);
                 std::swap(cur, oth);
                 s += two ? 2 : 1;
             } else {
@@ -703,8 +703,9 @@ struct GenCycle {
         for (int l = 0; l < h.b; ++l) {
             cur[l] = l == 0 ? u0 : g.u[l];
             oth[l] = g.t[l];
-            sweeps(l, cur[l], oth[l], nu1, l == 0 ? kNorm : kZeroIn, nullptr);
-            restriction(l, cur[l]);
+            double *fc = h.planar && nu1 % 2 == 0 ? g.f[l + 1] : nullptr;
+            sweeps(l, cur[l], oth[l], nu1, l == 0 ? kNorm : kZeroIn, nullptr, fc);
+            if (!fc) restriction(l, cur[l]);
         }
         bottom(nu1, nu2);
         const double *ec = g.u[h.b];
@@ -812,6 +813,18 @@ int gen_check(mhs_plan *p, const mhs_opts *o)
 }
 
 } // namespace
+
+// Tilings of the two-sweep launches of the box, without and with a correction.
+void gen_tile_pairs(mhs_plan *p)
+{
+    if (!p->gen) return;
+    GenHier &g = p->gen->h[0];
+    for (int l = 0; g.ok && l < g.geo.b; ++l) {
+        const int kind = l == 0 ? kPairDataFaces : kPairF;
+        if (l > 0) g.pair[l][0] = pair_tiling(g.geo.lv[l].n, kF64, kind, false);
+        g.pair[l][1] = pair_tiling(g.geo.lv[l].n, kF64, kind, false, kPairGenWaves);
+    }
+}
 
 void gen_create(mhs_plan *p, Carver &cv)
 {

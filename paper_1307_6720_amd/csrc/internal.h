@@ -103,9 +103,10 @@ struct LevelItem {
     const void *u_in;   // iterate read by the stage
     void *u_out;        // iterate written (smoother, refinement) / coarse rhs (restriction)
     const void *f;      // right-hand side, nullptr = 0
-    const void *ec;     // coarse correction added before smoothing, or FP32 e (refinement)
+    const void *ec;     // coarse correction added before smoothing, or FP32 e (refinement), or
+                        // (kPairRestrict) the coarse right-hand side, written
     union {
-        void *r_out;      // refinement: FP32 residual output; pair kernel: coarse right-hand side
+        void *r_out;      // refinement: FP32 residual output
         const void *beta; // general operator: b/a per node
     };
     const void *coef;   // per-plane {cx, cy, d, 1/d} in the stage's arithmetic type
@@ -233,7 +234,7 @@ enum SweepFlags : int {
     kPairKeepZ = 32, // two sweeps in 3D: the step to the coarse level keeps z
     kPairGen = 64,   // two sweeps in 3D, or 2D sweeps: the general operator (a diagonal per node)
     kPairEdge = 128, // two sweeps in 3D: boundary nodes carry data although there is a right-hand side
-    kPairRestrict = 256, // two sweeps in 3D: the result's residual goes, restricted, to r_out
+    kPairRestrict = 256, // two sweeps: the result's residual is restricted as well
     // launch flags of the 3D two-sweep kernel carry its variant from this bit on
     kPairVariantShift = 9,
     kPairVariantBit = 1 << kPairVariantShift,

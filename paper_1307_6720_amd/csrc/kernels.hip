@@ -632,10 +632,18 @@ __global__ __launch_bounds__(kSThreads) MHS_SWEEP_ATTR void k_sweep3(const Level
 // tile's last black update reads is then final, as in the sweeps done one
 // launch at a time, and a ring node computed by two workgroups gets the
 // same value in both.  Two sweeps per launch cost one launch instead of two
-// on these small, launch-bound planes.
+// on these small, launch-bound planes.  kPairRestrict: the launch that ends a
+// level's pre-smoothing also restricts its residual, from rings two nodes
+// wider, which saves the launch that read u and f again; a tile's coarse nodes
+// are those of a workgroup of k_restrict2.  These launches wait for memory, not
+// for bytes: the window of u, f, b/a and the coarse values are loaded together
+// first, where each half-sweep read its f and each corner of a correction waited
+// for its branch.  257 x 257: 7.9 + 5.1 -> 8.7 us with the norm and the
+// restriction, 8.7 -> 6.8 with the correction (129 x 129: 10.1 -> 7.0).
 // ============================================================================
 constexpr int kOwn2 = kTY2 * kTX / kThreads;
 static_assert(kTY2 * kTX % kThreads == 0, "tile must be a multiple of the block");
+static_assert(kTX == 2 * kCX && kTY2 == 2 * kCY && kCX * kCY == kThreads, "a tile's coarse nodes are one per thread");
 
 template <typename T, int FLAGS>
 __global__ __launch_bounds__(kThreads) void k_sweep2(const LevelItem *__restrict__ items, int nitems)
@@ -645,10 +653,16 @@ __global__ __launch_bounds__(kThreads) void k_sweep2(const LevelItem *__restrict
     constexpr bool NORM = (FLAGS & kNorm) != 0;
     constexpr bool PROLONG = (FLAGS & kProlong) != 0;
     constexpr bool GEN = (FLAGS & kPairGen) != 0; // the general operator: d + b/a per node
+    constexpr bool REST = (FLAGS & kPairRestrict) != 0; // and the restriction of the residual
     constexpr int NS = (FLAGS & kTwoSweeps) ? 2 : 1;
-    constexpr int H = 2 * NS; // halo
+    constexpr int XR = REST ? 2 : 0; // rings that the restriction needs final
+    constexpr int H = 2 * NS + XR;   // halo
     constexpr int WX = kTX + 2 * H, WY = kTY2 + 2 * H;
+    static_assert(!REST || (HAS_F && !PROLONG), "the last pre-smoothing sweeps of a correction");
     __shared__ T S[WY][WX];
+    __shared__ T FS[HAS_F ? WY : 1][HAS_F ? WX : 1];
+    __shared__ T BS[GEN ? WY : 1][GEN ? WX : 1];
+    __shared__ T RS[REST ? kTY2 + 1 : 1][REST ? kTX + 1 : 1];
     __shared__ double red[kThreads / 64];
 
     const int tile = launch_tile(items, nitems);
@@ -668,18 +682,43 @@ __global__ __launch_bounds__(kThreads) void k_sweep2(const LevelItem *__restrict
     const int tid = threadIdx.x;
     const T cx = coef[0], cy = coef[1], d = coef[2], invd = coef[3];
 
-    // window cell (w, c) is node (i0 - H + c, j0 - H + w)
-    for (int e = tid; e < WY * WX; e += kThreads) {
+    // window cell (w, c) is node (i0 - H + c, j0 - H + w).  All its loads are
+    // issued before the first is used (the sweeps then read LDS only)
+    constexpr int kPer = (WY * WX + kThreads - 1) / kThreads;
+    T uv[kPer], fv_[kPer], bv[kPer], e00[kPer], e01[kPer], e10[kPer], e11[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int e = min(tid + q * kThreads, WY * WX - 1);
+        const int w = e / WX, c = e - w * WX;
+        const int i = min(max(i0 - H + c, 0), nx - 1), j = min(max(j0 - H + w, 0), ny - 1);
+        const size_t o = (size_t)i + (size_t)nx * j;
+        if constexpr (!ZERO_IN) uv[q] = uin[o];
+        if constexpr (HAS_F) fv_[q] = f[o];
+        if constexpr (GEN) bv[q] = be[o];
+        if constexpr (PROLONG) {
+            // (a boundary node, which gets no correction, reads a node inside)
+            const MHS_GLOBAL T *p =
+                ec + (size_t)(min(i, nx - 2) >> 1) + (size_t)ncx * (size_t)(min(j, ny - 2) >> 1);
+            e00[q] = p[0], e01[q] = p[1], e10[q] = p[ncx], e11[q] = p[ncx + 1];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int e = min(tid + q * kThreads, WY * WX - 1);
         const int w = e / WX, c = e - w * WX;
         const int i = i0 - H + c, j = j0 - H + w;
+        const bool in = i >= 0 && i < nx && j >= 0 && j < ny;
         T v = (T)0;
-        if (i >= 0 && i < nx && j >= 0 && j < ny) {
-            if constexpr (!ZERO_IN) v = uin[(size_t)i + (size_t)nx * j];
-            if constexpr (PROLONG) {
-                if (i >= 1 && i <= nx - 2 && j >= 1 && j <= ny - 2) v += interp2<T>(ec, ncx, i, j);
-            }
+        if constexpr (!ZERO_IN) v = in ? uv[q] : (T)0;
+        if constexpr (PROLONG) {
+            const T h = (T)0.5;
+            const T x0 = (i & 1) ? h * (e00[q] + e01[q]) : e00[q], x1 = (i & 1) ? h * (e10[q] + e11[q]) : e10[q];
+            const T cv = (j & 1) ? h * (x0 + x1) : x0;
+            if (i >= 1 && i <= nx - 2 && j >= 1 && j <= ny - 2) v += cv;
         }
         S[w][c] = v;
+        if constexpr (HAS_F) FS[w][c] = fv_[q];
+        if constexpr (GEN) BS[w][c] = bv[q];
     }
     lds_barrier();
     double acc = 0.0;
@@ -691,9 +730,9 @@ __global__ __launch_bounds__(kThreads) void k_sweep2(const LevelItem *__restrict
             const int i = i0 + c - H, j = j0 + w - H;
             if (i <= nx - 2 && j <= ny - 2) {
                 T fv = (T)0;
-                if constexpr (HAS_F) fv = f[(size_t)i + (size_t)nx * j];
+                if constexpr (HAS_F) fv = FS[w][c];
                 T dv = d;
-                if constexpr (GEN) dv += be[(size_t)i + (size_t)nx * j];
+                if constexpr (GEN) dv += BS[w][c];
                 const T r = fv - (cx * (S[w][c + 1] + S[w][c - 1]) + cy * (S[w + 1][c] + S[w - 1][c]) + dv * S[w][c]);
                 acc += (double)r * (double)r;
             }
@@ -714,10 +753,10 @@ __global__ __launch_bounds__(kThreads) void k_sweep2(const LevelItem *__restrict
             const int i = i0 - H + c;
             if (i >= 1 && i <= nx - 2 && j >= 1 && j <= ny - 2) {
                 T fv = (T)0;
-                if constexpr (HAS_F) fv = f[(size_t)i + (size_t)nx * j];
+                if constexpr (HAS_F) fv = FS[w][c];
                 const T n = fv - (cx * (S[w][c + 1] + S[w][c - 1]) + cy * (S[w + 1][c] + S[w - 1][c]));
                 if constexpr (GEN)
-                    S[w][c] = n / (be[(size_t)i + (size_t)nx * j] + d);
+                    S[w][c] = n / (BS[w][c] + d);
                 else
                     S[w][c] = n * invd;
             }
@@ -725,15 +764,41 @@ __global__ __launch_bounds__(kThreads) void k_sweep2(const LevelItem *__restrict
     };
 #pragma unroll
     for (int sw = 0; sw < NS; ++sw) {
-        colour(0, 2 * (NS - sw) - 1);
+        colour(0, 2 * (NS - sw) - 1 + XR);
         lds_barrier();
-        colour(1, 2 * (NS - sw) - 2);
+        colour(1, 2 * (NS - sw) - 2 + XR);
         lds_barrier();
     }
     for (int e = tid; e < kTY2 * kTX; e += kThreads) {
         const int w = H + e / kTX, c = H + e % kTX;
         const int i = i0 + c - H, j = j0 + w - H;
         if (i <= nx - 2 && j <= ny - 2) uout[(size_t)i + (size_t)nx * j] = S[w][c];
+    }
+    if constexpr (REST) {
+        // the residual of nodes i0 .. i0 + kTX (and so in y), then full
+        // weighting onto the tile's coarse nodes, one per thread (k_restrict2's
+        // expressions)
+        for (int e = tid; e < (kTY2 + 1) * (kTX + 1); e += kThreads) {
+            const int w = H + e / (kTX + 1), c = H + e % (kTX + 1);
+            const int i = i0 + c - H, j = j0 + w - H;
+            T r = (T)0;
+            if (i <= nx - 2 && j <= ny - 2) {
+                T dv = d;
+                if constexpr (GEN) dv += BS[w][c];
+                r = FS[w][c] - (cx * (S[w][c + 1] + S[w][c - 1]) + cy * (S[w + 1][c] + S[w - 1][c]) + dv * S[w][c]);
+            }
+            RS[w - H][c - H] = r;
+        }
+        lds_barrier();
+        const int tI = tid % kCX, tJ = tid / kCX;
+        const int I = 1 + tx * kCX + tI, J = 1 + ty * kCY + tJ;
+        if (I <= ncx - 2 && J <= it->ncy - 2) {
+            const T q4 = (T)0.25, h2 = (T)0.5;
+            const int cw = 2 * tJ + 1, cc = 2 * tI + 1;
+            auto row = [&](int w) { return q4 * RS[w][cc - 1] + h2 * RS[w][cc] + q4 * RS[w][cc + 1]; };
+            MHS_GLOBAL T *fc = gout<T>(const_cast<void *>(it->ec));
+            fc[(size_t)I + (size_t)ncx * J] = q4 * row(cw - 1) + h2 * row(cw) + q4 * row(cw + 1);
+        }
     }
     if constexpr (NORM) {
         const double tot = block_sum<kThreads>(acc, red);
@@ -1978,6 +2043,10 @@ hipError_t sweep2_dispatch(const LevelItem *items, int nitems, int ntiles, int f
         // the general operator on a face
         MHS_CASE(kPairGen | 1) MHS_CASE(kPairGen | 3) MHS_CASE(kPairGen | 5) MHS_CASE(kPairGen | 9)
         MHS_CASE(kPairGen | 17) MHS_CASE(kPairGen | 19) MHS_CASE(kPairGen | 21) MHS_CASE(kPairGen | 25)
+        // two sweeps and the restriction of their residual
+        MHS_CASE(kPairRestrict | 17) MHS_CASE(kPairRestrict | 19) MHS_CASE(kPairRestrict | 21)
+        MHS_CASE(kPairRestrict | kPairGen | 17) MHS_CASE(kPairRestrict | kPairGen | 19)
+        MHS_CASE(kPairRestrict | kPairGen | 21)
 #undef MHS_CASE
     default:
         return hipErrorInvalidValue;

@@ -248,7 +248,7 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     const MHS_GLOBAL T *__restrict__ fin = gin<T>(it->f);
     const MHS_GLOBAL T *__restrict__ ec = gin<T>(it->ec);
     const MHS_GLOBAL T *__restrict__ bin = gin<T>(it->beta);
-    MHS_GLOBAL T *__restrict__ fco = gout<T>(it->r_out);
+    MHS_GLOBAL T *__restrict__ fco = gout<T>(const_cast<void *>(it->ec));
     const MHS_CONST T *__restrict__ coef = gconst<T>(it->coef);
     const T cz = (T)it->cz;
     const int nx = it->nx, ny = it->ny, nz = it->nz;

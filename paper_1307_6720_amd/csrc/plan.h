@@ -276,6 +276,7 @@ struct GenPlan;
 // Geometry of the general problems' hierarchies (3D and the three face
 // orientations) and their buffers; base == nullptr only counts bytes.
 void gen_create(mhs_plan *p, Carver &cv);
+void gen_tile_pairs(mhs_plan *p);
 struct GenPlanDeleter {
     void operator()(GenPlan *g) const;
 };

@@ -80,3 +80,35 @@ def test_correction_cycles_in_fp32(S, dims, lengths, cycles):
     plan.solve_interior(model, u, S.make_opts(rtol=0.0, max_cycles=cycles), raise_on_error=False)
     diff = (P - u).abs().max().item()
     assert diff <= tol(dims, 2.0**-24) * u.abs().max().item()
+
+
+# one tile and several, remainders in x and y, the largest with two levels above
+# the bottom
+@pytest.mark.parametrize("dims,lengths", [((65, 129, 9), (1.0, 2.0, 1.0)), ((129, 129, 9), (1.0, 1.0, 1.0)),
+                                          ((257, 65, 9), (4.0, 1.0, 1.0)), ((257, 257, 9), (1.0, 1.0, 1.0))])
+def test_a_cycle_of_the_boundary_problem_equals_its_stages(S, dims, lengths):
+    g = synth.make_grid(*dims, *lengths)
+    plan = S.Plan(g, 1)
+    nx, ny, _ = dims
+    rng = np.random.default_rng(12)
+    bz0 = torch.from_numpy(rng.standard_normal((ny, nx))).cuda()
+    P = torch.zeros(plan.shape, dtype=torch.float64, device="cuda")
+    plan.solve_boundary(bz0, P, S.make_opts(rtol=0.0, max_cycles=1), raise_on_error=False)
+    # equation (11): the Laplacian of P on the base is -Bz0 (P = 0 on its edges)
+    bottom = plan.bottom_level(2)
+
+    def down(u, f, level):
+        if level == bottom:
+            plan.stage_bottom(None, 2, u, f)
+            return
+        plan.stage_smooth(None, 2, level, u, f, 2, zero_guess=level > 0)
+        fc = torch.zeros(plan.level_shape(2, level + 1), dtype=torch.float64, device="cuda")
+        plan.stage_restrict(None, 2, level, u, f, fc)
+        ec = torch.zeros_like(fc)
+        down(ec, fc, level + 1)
+        plan.stage_correct_smooth(None, 2, level, u, f, ec, nsweeps=2)
+
+    u = torch.zeros((ny, nx), dtype=torch.float64, device="cuda")
+    down(u, -bz0, 0)
+    diff = (P[0] - u).abs().max().item()
+    assert u.abs().max().item() > 0 and diff <= tol((nx, ny), 2.0**-53) * u.abs().max().item()
