@@ -32,7 +32,7 @@ METRIC = "V-cycle GB/s & solves/s at 257^3 to 1e-8 (FP64 vs mixed); p50/p99 late
 HBM_PEAK_GBPS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "smooth_l0_traffic_mhs257.txt")
 # the kernel source and what sets its launch shape and ring depth
-KERNEL_SRCS = [os.path.join(ROOT, "paper_1307_6720_amd", "csrc", f) for f in ("kernels.hip", "internal.h", "api.cpp")]
+KERNEL_SRCS = [os.path.join(ROOT, "paper_1307_6720_amd", "csrc", f) for f in ("kernels.hip", "pair.hip", "bottom.hip", "device.h", "internal.h", "api.cpp")]
 
 
 def kernels_digest():
@@ -120,16 +120,29 @@ def _short_kernel(name):
     return re.sub(r"\(.*\)$", "", n)
 
 
-# level-0 FP32 smoother variants and their compulsory bytes per fine node:
-# the zero-guess sweep (read f, write u; the first sweep of a refinement
-# step), sweeps with f (read u, f; write u) and the prolongation sweep
-# (+ coarse correction, N/8 floats); per FP32 V(2,2) cycle one prolongation
-# sweep and two or three with f
-SMOOTH_L0_MIX = {"k_sweep3<float, 3>": 8.0, "k_sweep3<float, 1>": 12.0, "k_sweep3<float, 9>": 12.5}
+# level-0 FP32 smoother variants (flags of k_pair3, two sweeps per launch) with
+# their compulsory bytes read and written per fine node: pre-smoothing from a
+# zero guess (read f; the first cycle of a refinement step) or with u and f,
+# both with the restricted residual written (N/8 floats), and post-smoothing
+# with the coarse correction (N/8 floats read); one of each kind per FP32
+# V(2,2) cycle
+SMOOTH_L0_MIX = {259: (4.0, 4.5), 257: (8.0, 4.5), 9: (8.5, 4.0)}
+# their workgroups at 257^3: of a one-request launch, and per request of a
+# merged one
+SMOOTH_L0_GROUPS_257 = {259: (250, 120), 257: (250, 120), 9: (240, 128)}
 COPY_BYTES = 1 << 30
-# workgroups of a one-request level-0 smoother launch at 257^3: 4 x 16 tiles
-# of 64 x 16 nodes per plane, 8 chunks of 32 planes
-SMOOTH_L0_GROUPS_257 = 512
+
+
+def smooth_l0_launch(kn, g):
+    """(flags, requests) of a launch of `g` workgroups of kernel `kn` that can
+    be one of the level-0 FP32 smoother on the 257^3 workload, else None."""
+    m = re.match(r"k_pair3<float, .*, (\d+)>$", kn)
+    if not m or int(m.group(1)) not in SMOOTH_L0_MIX:
+        return None
+    one, per = SMOOTH_L0_GROUPS_257[int(m.group(1))]
+    if g == one:
+        return int(m.group(1)), 1
+    return (int(m.group(1)), g // per) if g % per == 0 and g > per else None
 
 
 def counter_probe(batch=12, requests=24):
@@ -174,12 +187,12 @@ def counter_probe(batch=12, requests=24):
     print("counter probe done", flush=True)
 
 
-def summarize_counters(fetch_csv, write_csv, one_groups=SMOOTH_L0_GROUPS_257):
+def summarize_counters(fetch_csv, write_csv):
     """HBM traffic of the level-0 FP32 smoother from the two counter runs of
     counter_probe, each counter scaled by what it reads for the calibration
-    copy.  A launch of the smoother covering k requests of the 257^3
-    workload has k * one_groups workgroups; level-0 launches read about
-    8x what level-1 launches of the same k read, and launches issued after
+    copy.  Requests per launch follow from the workgroups
+    (SMOOTH_L0_GROUPS_257); level-0 launches read about 8x what level-1
+    launches of as many requests read, and launches issued after
     a solve converged read nothing.  Prints the summary kept under
     profiles/: the ratio of measured to compulsory bytes over the
     one-request (k = 1) and over the merged (k > 1) launches, weighted by
@@ -212,10 +225,10 @@ def summarize_counters(fetch_csv, write_csv, one_groups=SMOOTH_L0_GROUPS_257):
     def level0(rows, scale, min_bytes_per_req):
         out = collections.defaultdict(list)  # (kernel, k) -> bytes
         for n, g, v in rows:
-            kn = _short_kernel(n)
-            if kn not in SMOOTH_L0_MIX or g % one_groups:
+            hit = smooth_l0_launch(_short_kernel(n), g)
+            if hit is None:
                 continue
-            k = g // one_groups
+            kn, k = hit
             if v / scale > k * min_bytes_per_req:
                 out[(kn, k)].append(v / scale)
         return out
@@ -239,9 +252,10 @@ def summarize_counters(fetch_csv, write_csv, one_groups=SMOOTH_L0_GROUPS_257):
         kn, k = key
         fk, wk = full(F[key], k), full(W[key], k)
         fb, wb = sum(fk) / len(fk) / k, sum(wk) / len(wk) / k
-        c = SMOOTH_L0_MIX[kn]
-        print(f"  {kn:22s} k={k:2d}  launches {len(fk):3d} of {len(F[key]):3d}  read {fb / N:5.2f} B/node "
-              f"(compulsory {c - 4:.2f})  write {wb / N:5.2f} B/node (compulsory 4.00)")
+        cr, cw_ = SMOOTH_L0_MIX[kn]
+        c = cr + cw_
+        print(f"  k_pair3<float, .., {kn:3d}> k={k:2d}  launches {len(fk):3d} of {len(F[key]):3d}  read {fb / N:5.2f} "
+              f"B/node (compulsory {cr:.2f})  write {wb / N:5.2f} B/node (compulsory {cw_:.2f})")
         if k > 1:
             meas += (fb + wb) * k * len(fk)
             alg += k * c * N * len(fk)
@@ -255,26 +269,26 @@ def summarize_counters(fetch_csv, write_csv, one_groups=SMOOTH_L0_GROUPS_257):
     print(f"merged_traffic_ratio: {meas / alg:.4f}")
 
 
-def _level0_split(launches, one_groups):
+def _level0_split(launches):
     """Pick the level-0 launches among launches of the smoother: (start,
-    end, kernel, groups) tuples.  Within one kernel variant and workgroup
-    count (equal requests per launch), level-0 launches take several times
+    end, flags, requests) tuples.  Within one kernel variant and number of
+    requests per launch, level-0 launches take several times
     longer than level-1 launches and launches whose items all exited at once
-    take a few microseconds (about 1 us per 1024 workgroups): the level-0
-    launches are those above the largest duration ratio between neighbours
-    among the launches longer than 3 us per 1024 workgroups (at least 5 us).
+    take a few microseconds: the level-0 launches are those above the largest
+    duration ratio between neighbours among the launches longer than 5 us and
+    2 us per request.
     Where the durations form one cluster (merged launches, whose level-1
     launches have other workgroup counts), the cluster is level 0 if its
-    median takes at least 15 us per request (a level-0 FP32 sweep of one
-    257^3 request takes 25-55 us, a level-1 sweep under 10 us)."""
+    median takes at least 15 us per request (a level-0 FP32 launch takes
+    25-60 us per 257^3 request, a level-1 launch under 10)."""
     import collections
 
     by = collections.defaultdict(list)
     for x in launches:
         by[(x[2], x[3])].append(x)
     out = []
-    for (_, g), v in by.items():
-        floor = max(5000.0, 3000.0 * g / 1024)
+    for (_, k), v in by.items():
+        floor = max(5000.0, 2000.0 * k)
         v = sorted((x for x in v if (x[1] - x[0]) > floor), key=lambda x: x[1] - x[0])
         if not v:
             continue
@@ -282,7 +296,7 @@ def _level0_split(launches, one_groups):
         gaps = [d[i + 1] / d[i] for i in range(len(d) - 1)]
         if not gaps or max(gaps) < 1.8:
             # one cluster: no level-0 / level-1 split to make
-            if d[len(d) // 2] >= 15000.0 * max(1, g // one_groups):
+            if d[len(d) // 2] >= 15000.0 * k:
                 out.extend(v)
             continue
         cut = gaps.index(max(gaps)) + 1
@@ -290,13 +304,12 @@ def _level0_split(launches, one_groups):
     return sorted(out)
 
 
-def summarize_trace(stats_csv, trace_csv, marker_csv=None, one_groups=SMOOTH_L0_GROUPS_257, top=24):
+def summarize_trace(stats_csv, trace_csv, marker_csv=None, top=24):
     """Kernel-time summary of a rocprofv3 --kernel-trace --stats (and
     --marker-trace) run of bench.py: the stats table; the launches that ran
     (> 5 us; launches issued after a solve converged exit at once) by
-    kernel and workgroup count; and the level-0 FP32 smoother launches (a
-    launch covering k requests of the 257^3 workload has k * one_groups
-    workgroups) with their average duration, over the run and inside each
+    kernel and workgroup count; and the level-0 FP32 smoother launches (their
+    requests by SMOOTH_L0_GROUPS_257) with their average duration, over the run and inside each
     ROCTx range of bench.py (the passes whose HIP-event timings give the
     roofline)."""
     import collections
@@ -313,14 +326,15 @@ def summarize_trace(stats_csv, trace_csv, marker_csv=None, one_groups=SMOOTH_L0_
     with open(trace_csv) as fh:
         rows = list(csv.DictReader(fh))
     agg = collections.defaultdict(list)
-    sm = []  # (start, end, kernel, groups) of the FP32 smoother variants
+    sm = []  # (start, end, flags, requests) of the FP32 smoother variants
     for r in rows:
         kn = _short_kernel(r["Kernel_Name"])
         g = int(r["Grid_Size_X"]) // max(1, int(r["Workgroup_Size_X"]))
         t0, t1 = int(r["Start_Timestamp"]), int(r["End_Timestamp"])
         agg[(kn, g)].append((t1 - t0) / 1e3)
-        if kn in SMOOTH_L0_MIX and g % one_groups == 0:
-            sm.append((t0, t1, kn, g))
+        hit = smooth_l0_launch(kn, g)
+        if hit is not None:
+            sm.append((t0, t1, *hit))
     print()
     print("## launches that ran (> 5 us), by kernel and workgroup count")
     print(f"{'kernel':40s} {'groups':>7s} {'ran':>5s} {'avg_us':>8s} {'med_us':>8s} {'skip':>5s} {'ran_ms':>8s}")
@@ -335,12 +349,12 @@ def summarize_trace(stats_csv, trace_csv, marker_csv=None, one_groups=SMOOTH_L0_
     def table(sel, title):
         print()
         print(title)
-        l0 = _level0_split(sel, one_groups)
+        l0 = _level0_split(sel)
         by = collections.defaultdict(list)
-        for t0, t1, kn, g in l0:
-            by[(kn, g // one_groups)].append((t1 - t0) / 1e3)
+        for t0, t1, kn, k in l0:
+            by[(kn, k)].append((t1 - t0) / 1e3)
         for (kn, k), v in sorted(by.items()):
-            print(f"  {kn:22s} k={k}  launches {len(v):4d}  avg_us {statistics.mean(v):8.2f}  "
+            print(f"  k_pair3<float, .., {kn:3d}> k={k}  launches {len(v):4d}  avg_us {statistics.mean(v):8.2f}  "
                   f"median_us {statistics.median(v):8.2f}")
         ds = [(t1 - t0) / 1e3 for t0, t1, _, _ in l0]
         if ds:
@@ -647,10 +661,10 @@ def level0_kz(grid):
 
 
 def pattern_reference(torch, dev, grid, nreq):
-    """Rates of mhs_probe_smoother_pattern: the level-0 smoother's memory
-    traffic (12 B per interior node) in its own order with no LDS, barrier
-    or arithmetic, for one request and for `nreq` requests per launch as in
-    the merged launches; with the smoother's tile and z-chunk, and with a
+    """Rates of mhs_probe_smoother_pattern: a level-0 sweep's memory traffic
+    (12 B per interior node) in the order of the single-sweep kernel, with no
+    LDS, barrier or arithmetic, for one request and for `nreq` requests per launch as in
+    the merged launches; with that kernel's tile and z-chunk, and with a
     row-wide 256 x 8 tile (the headroom of another tiling).  HIP events on
     the stream of the launches, median of 9."""
     import ctypes as C
@@ -686,7 +700,7 @@ def pattern_reference(torch, dev, grid, nreq):
             ms = sorted(ts)[len(ts) // 2]
             rates[name] = 12.0 * interior * k / (ms * 1e-3) / 1e9
         rates["pattern_note"] = (f"mhs_probe_smoother_pattern, {k} request(s) of {grid.nx}x{grid.ny}x{grid.nz} "
-                                 f"per launch; smoother tile 64x16, {kz} planes per group; wide tile 256x8, 8 planes")
+                                 f"per launch; single-sweep tile 64x16, {kz} planes per group; wide tile 256x8, 8 planes")
         out[label] = rates
         del u, f, o
     return out
@@ -861,7 +875,8 @@ def main():
         ms, n, b = prof["smooth_l0"]
         achieved = b / (ms * 1e-3) / 1e9
         return {"bound": "hbm",
-                "kernel": "level-0 FP32 red-black smoother k_sweep3<float, 3|1|9> (zero guess, with f, with prolongation)",
+                "kernel": ("level-0 FP32 red-black smoother, two sweeps per launch: k_pair3<float, .., 259|257|9> (zero guess "
+                           "and u, f with the restricted residual; with prolongation)"),
                 "launches_timed": where,
                 "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBPS, "traffic": None,

@@ -236,7 +236,7 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     constexpr int kSet = (128 * NW + 128) * H;
     // and the residual of the row above each coarse row, for the thread above
     constexpr int kSetC = REST ? (64 * NW + 64) * H : 0;
-    static_assert(R == 2 || R == 4, "the correction's rows come in pairs");
+    static_assert(R == 2, "a thread has one coarse row");
     __shared__ __attribute__((aligned(16))) T S[2 * kSets * kSet + 2 * kSetC];
     __shared__ double red[NW];
 
