@@ -129,7 +129,7 @@ def _short_kernel(name):
 SMOOTH_L0_MIX = {259: (4.0, 4.5), 257: (8.0, 4.5), 9: (8.5, 4.0)}
 # their workgroups at 257^3: of a one-request launch, and per request of a
 # merged one
-SMOOTH_L0_GROUPS_257 = {259: (250, 120), 257: (250, 120), 9: (240, 128)}
+SMOOTH_L0_GROUPS_257 = {259: (250, 60), 257: (250, 63), 9: (240, 64)}
 COPY_BYTES = 1 << 30
 
 

@@ -86,10 +86,14 @@ int chunk(int planes, int xy_tiles, int cap, int target = kTargetGroups)
 // Tiling of a two-sweep launch over an n[0] x n[1] x n[2] level, among the
 // variants of at most max_waves waves: the one with the smallest estimate of
 // its time.  The constants are fitted to the measured times of every variant
-// and chunk length on levels from 33^3 to 513 x 513 x 257, alone and eight or
-// twelve together, in FP32 and FP64 (91 cases): its choices are within 5 % of
-// the best one measured, except for batches of another number of requests than
-// the eight it assumes.
+// and chunk length on levels from 33^3 to 513 x 513 x 257, alone and four to
+// twelve together, in FP32 and FP64 (91 cases): for a launch alone its choices
+// are within 6 % of the best one measured; a batch of another number of
+// requests than the eight it assumes can lose more on levels of one round of
+// workgroups.  Large launches take long chunks: a chunk's first and last planes
+// are read again, by then from memory (513 x 513 x 257, chunks of 36 -> 90
+// planes: two FP32 sweeps 224 -> 185 us; twelve 257^3 with the restriction
+// 755 -> 689 us).
 PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max_waves)
 {
     const int V = path == kF64 ? kPairV64 : kPairV32;
@@ -108,9 +112,13 @@ PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max
     struct Cost {
         double step, wave, group, rate, z, y, x, rest;
     };
-    constexpr Cost kPlain{0.125, 0.235, 1.0, 8.9, 0.64, 0.33, 0.36, 0.74};
-    constexpr Cost kRest{0.45, 0.30, 1.6, 6.5, 0.87, 0.07, 0.10, 0.45};
+    constexpr Cost kPlain{0.05, 0.124, 0.63, 4.55, 0.08, 0.05, 0.60, 0.83};
+    constexpr Cost kRest{0.40, 0.34, 1.9, 6.8, 0.56, 0.28, 0.38, 0.15};
     const Cost &c = rest ? kRest : kPlain;
+    // chunk lengths tried: whole rounds, the long ones more coarsely
+    auto next = [](int kz, int round) {
+        return kz + (round == 2 ? (kz < 10 ? 2 : kz < 18 ? 4 : 8) : kz < 36 ? round : 3 * round);
+    };
     PairTiling best;
     double tbest = 0.0;
     for (int q = 0; q < kPairNVariants; ++q) {
@@ -132,7 +140,7 @@ PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max
         const int resident = rest && pv.waves == 8 ? 1 : std::max(1, (512 / regs) * 4 / pv.waves);
         const double y = 1.0 + c.y * ((double)nty * wy / my - 1.0);
         const double x = 1.0 + c.x * (ntx * (wx * es + 112.0) / (mx * es) - 1.0);
-        for (int kz = pv.depth == 1 ? 6 : 2; kz <= kPairMaxKz; kz += round == 2 ? (kz < 10 ? 2 : kz < 18 ? 4 : 8) : round) {
+        for (int kz = pv.depth == 1 ? 6 : 2; kz <= pair_max_kz(pv.waves, pv.row); kz = next(kz, round)) {
             const int planes = std::min(kz, n[2] - 2);
             const int ntz = ceil_div(n[2] - 2, kz);
             const double nwg = (double)ntx * nty * ntz * copies;
@@ -142,8 +150,7 @@ PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max
             const double comp = rounds * (steps * (c.step + c.wave * per_cu * pv.waves / 4.0) + c.group);
             const double again = (1.0 + c.z * halo / planes) * y * x;
             const double mem = (double)n[0] * n[1] * n[2] * es * (reads * again + writes) * copies / (c.rate * 1e6);
-            // (whole rows unless the others gain more than the fit's error)
-            const double tm = (std::max(comp, mem) + c.rest * std::min(comp, mem)) * (pv.row ? 1.087 : 1.0);
+            const double tm = std::max(comp, mem) + c.rest * std::min(comp, mem);
             if (best.var < 0 || tm < tbest) {
                 tbest = tm;
                 best.var = q;

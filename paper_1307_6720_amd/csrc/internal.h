@@ -264,7 +264,11 @@ constexpr int kPairNVariants = 6;
 constexpr int kPairGenWaves = 8;
 // nodes that neighbouring windows overlap by, without and with the restriction
 constexpr int kPairOver = 8, kPairOverRest = 12;
-constexpr int kPairMaxKz = 44; // planes per workgroup (their coefficients sit one plane per lane)
+// Planes per workgroup.  One plane's coefficients sit in one lane, 64 planes of
+// them; the variants that large launches take load them again on the way (which
+// costs the small levels' variants 1 %).
+constexpr int kPairTablePlanes = 44;
+constexpr int pair_max_kz(int waves, bool row) { return waves == 12 || (waves == 8 && row) ? 128 : kPairTablePlanes; }
 hipError_t launch_pair3(const LevelItem *items, int nitems, int ntiles, int flags, bool dbl, int variant,
                         hipStream_t s);
 hipError_t launch_sweep2(const LevelItem *items, int nitems, int ntiles, int flags, bool dbl,

@@ -316,7 +316,7 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         }
     }
 
-    // planes s0-4 .. (at most 64): cx, cy, 1/d
+    // cx, cy, 1/d of 64 planes from s0-4
     const int s0 = max(kb - (REST ? 4 : 3), 0) & ~1;
     // (the general operator's are the same on every plane)
     PlaneTab<T> tcx, tcy, tid_, tdd;
@@ -325,12 +325,17 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         gcx = coef[0];
         gcy = coef[1];
         gdd = coef[2];
-    } else {
-        tcx.load(coef, s0 - 4, 0, nz);
-        tcy.load(coef, s0 - 4, 1, nz);
-        tid_.load(coef, s0 - 4, 3, nz);
-        if constexpr (NORM || REST) tdd.load(coef, s0 - 4, 2, nz);
     }
+    // planes b .. b + 63
+    auto table = [&](int b) {
+        if constexpr (!GEN) {
+            tcx.load(coef, b, 0, nz);
+            tcy.load(coef, b, 1, nz);
+            tid_.load(coef, b, 3, nz);
+            if constexpr (NORM || REST) tdd.load(coef, b, 2, nz);
+        }
+    };
+    table(s0 - 4);
 
     T u[NS][R][V], f[NS][R][V], be[GEN ? NS : 1][R][V];
     T dr[R][H]; // red nodes of plane s-4
@@ -754,6 +759,8 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
     // ke - 1 or (ke - 1) / 2
     const int send = REST ? ke + (KEEPZ ? 4 : 5) : ke + 2;
     for (int s = s0; s <= send; s += NS) {
+        if constexpr (!GEN && pair_max_kz(NW, ROW) > kPairTablePlanes)
+            if (s + NS - 1 > tcx.base + 63) table(s - 4); // a long march's next planes
         step(s, std::integral_constant<int, 0>{});
         step(s + 1, std::integral_constant<int, 1>{});
         if (REST && D == 3 && s + 2 > send) break;

@@ -61,8 +61,9 @@ def test_two_sweeps_with_boundary_data_equal_two_launches(S, dims):
 
 
 # windows of sixteen lanes per row, several of them in x and in y, of four,
-# eight and twelve waves
-@pytest.mark.parametrize("dims", [(257, 129, 65), (129, 65, 65), (513, 65, 33), (257, 257, 129), (513, 257, 65)])
+# eight and twelve waves; the last marches through more planes than a wave has lanes
+@pytest.mark.parametrize("dims", [(257, 129, 65), (129, 65, 65), (513, 65, 33), (257, 257, 129), (513, 257, 65),
+                                  (513, 513, 257)])
 @pytest.mark.parametrize("precision", [1, 2])
 def test_two_sweeps_in_windows_of_sixteen_lanes(S, dims, precision):
     lengths = [n - 1.0 for n in dims]
