@@ -649,8 +649,8 @@ def general_leg(torch, dev, n=257, reps=3, rtol=1e-10):
     return {"grid": f"{n}^3", "rtol": rtol, "ms_per_solve": 1e3 * sum(ts) / reps, "cycles": info.cycles,
             "rel_residual": info.rel_residual, "kernel_ms": ms, "launches": nl,
             "kernel_gbps": by / (ms * 1e-3) / 1e9 if ms > 0 else None,
-            "note": "FP64 V(2,2); one-thread-per-node kernels; GB/s from algorithmic bytes (sweep 32 B/node, "
-                    "residual 32, restriction 8 + 8/8, prolongation 16 + 8/8) over summed HIP-event durations"}
+            "note": "FP64 V(2,2); GB/s from algorithmic bytes (two sweeps per launch 32 B/node, 24 from a zero guess, "
+                    "restriction 24 + 8/8, correction 8/8) over summed HIP-event durations"}
 
 
 def level0_kz(grid):
