@@ -14,11 +14,12 @@
 // which axes a step halves) is the one of (8), so the grid transfers are the
 // same full weighting and linear interpolation, applied per axis.
 //
-// Measured on a 257^3 unit box to rtol 1e-10 (9 cycles): 5.9 ms, against
-// 17.2 ms with a launch per colour and per stage (each of the two colour
+// Measured on a 257^3 unit box to rtol 1e-10 (9 cycles): 5.3 ms, against
+// 17.3 ms with a launch per colour and per stage (each of the two colour
 // launches of a sweep touched every line of u, b/a and the right-hand side);
-// a 129 x 65 face 0.41 against 1.33 ms.  Level 0 is bound by memory: a pair of
-// sweeps moves 32 bytes per node in 173 us (198 with the prolongation).
+// a 129 x 65 face 0.35 against 1.32 ms.  Level 0 is bound by memory: a pair of
+// sweeps moves 32 bytes per node in about 150 us (175 with the prolongation),
+// a copy of as many 125.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

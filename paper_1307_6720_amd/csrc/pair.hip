@@ -176,18 +176,18 @@ __device__ __forceinline__ double lane_above(double v)
 // windows of k_sweep3 carried (per node and sweep 1 LDS read and 1 write
 // instead of 7 and 2, one barrier per plane for both sweeps instead of four).
 // Measured on the two post-smoothing sweeps of a 257^3 level in FP32: 46
-// against 95 us for one request; twelve 257^3 equilibria served together take
-// 26.4 against 42.4 ms.  Merged it is bound by memory, alone by its
-// instructions: a window's halo and a march's first and last planes are
-// computed twice.
+// against 95 us for one request, 581 against 1072 us for twelve merged; twelve
+// 257^3 equilibria served together take 26.1 against 46.1 ms with all that is
+// described here.  Merged it is bound by memory (1.09 times the compulsory
+// bytes at the rate of a copy), alone by its instructions and the planes that
+// short chunks read again.
 //
 // Level 0 of the FP64 path has no right-hand side but Dirichlet data on its
 // boundary nodes: those keep their values, and where the side faces carry data
 // (ext = 2) the last window of a row or column reaches past the boundary node
 // instead of ending before it.  The first pair of a cycle also sums the
 // residual of its input.  257^3 in FP64, 9 cycles and the fields: 4.46 ms,
-// against 5.22 with single sweeps there (4.0 with the bottom solver and the
-// windows of 16 lanes).
+// against 5.22 with single sweeps there (3.73 with the later steps).
 //
 // kPairRestrict: the launch that ends a level's pre-smoothing also restricts
 // its residual (full weighting, as k_restrict3, whose expressions and order of
@@ -198,7 +198,7 @@ __device__ __forceinline__ double lane_above(double v)
 // further than a smoothed one, so windows overlap by twelve nodes and a march
 // is five steps longer.  It saves reading u and f again (8 of 20.5 bytes per
 // node in FP32) and a launch per level: level 0 of 513 x 513 x 257 mixed 198 +
-// 149 -> 255 us, of 257^3 46 + 35 -> 58 us, its 65^3 level 6.9 + 6.4 -> 12.7;
+// 149 -> 226 us, of 257^3 46 + 35 -> 57 us, its 65^3 level 6.9 + 6.4 -> 12.7;
 // 257^3 mixed in all 3.28 -> 3.06 ms.  With the restriction among the updates
 // twelve waves spill, so there it comes after them.
 // ============================================================================
