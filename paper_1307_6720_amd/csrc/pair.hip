@@ -454,16 +454,24 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
         return y;
     };
     // one colour (0 red, 1 black) of plane p: k its coefficients, uc its columns, uu and ud those
-    // above and below, S rows at rd; par the plane's parity
+    // above and below, S rows at rd; par the plane's parity.  What the second
+    // sweep (last) leaves in column 0 is stored with the row: it has to be zero
+    // also where a neighbour has overflowed and the product with 1/d = 0 is a
+    // NaN, for single sweeps read that column, which they do not write, in a
+    // later solve.  (Selects at every node and in both sweeps: 33^3 mixed 1 %
+    // slower.  In both sweeps at column 0 in FP64 with the restriction, whose
+    // registers then suffice: up to 88 spilled with one.)
+    constexpr bool kSelectBoth = sizeof(T) == 8 && REST && !ZERO_IN;
     auto colour = [&](int p, const Coef &k, int par, int col, T(&uc)[R][V], const T(&uu)[R][V], const T(&dn)[R][V], const T(&fp)[R][V],
-                      const T(&bp)[R][V], const Rows &y) {
+                      const T(&bp)[R][V], const Rows &y, auto last) {
         const T cx = k.cx, cy = k.cy, invd = k.inv;
         const bool in = p >= 1 && p <= nz - 2;
+        constexpr bool SELECT = decltype(last)::value || kSelectBoth;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int v0 = (r + par + col) & 1;
             const bool in1 = upd[r][1] && in, in0 = upd[r][0] && in;
-            const T inv1 = KEEP ? invd : upd[r][1] ? invd : (T)0, inv0 = KEEP || v0 ? inv1 : upd[r][0] ? invd : (T)0;
+            const T inv1 = KEEP ? invd : upd[r][1] ? invd : (T)0, inv0 = KEEP || SELECT || v0 ? inv1 : upd[r][0] ? invd : (T)0;
 #pragma unroll
             for (int m = 0; m < H; ++m) {
                 const int v = v0 + 2 * m;
@@ -474,7 +482,10 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
                 const T fv = HAS_F ? fp[r][v] : (T)0;
                 const T n = fv - (cx * (e + w) + cy * (yn + ys_) + cz * (uu[r][v] + dn[r][v]));
                 const T a = GEN ? n / (bp[r][v] + invd) : n * (v ? inv1 : inv0);
-                uc[r][v] = KEEP ? keep_or(v ? in1 : in0, a, uc[r][v]) : a;
+                if constexpr (KEEP)
+                    uc[r][v] = keep_or(v ? in1 : in0, a, uc[r][v]);
+                else
+                    uc[r][v] = SELECT && !v ? keep_or(upd[r][0], a, (T)0) : a;
             }
         }
     };
@@ -609,15 +620,15 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
                 }
             }
         } else {
-            colour(s, q[c0], P, 0, u[c0], u[cp1], u[cm1], f[c0], be[GEN ? c0 : 0], y0);
+            colour(s, q[c0], P, 0, u[c0], u[cp1], u[cm1], f[c0], be[GEN ? c0 : 0], y0, std::false_type{});
         }
         calm();
         if constexpr (LATE) y1 = outer(rb + kSet, ra + kSet);
-        colour(s - 1, q[cm1], Q, 1, u[cm1], u[c0], u[cm2], f[cm1], be[GEN ? cm1 : 0], y1);
+        colour(s - 1, q[cm1], Q, 1, u[cm1], u[c0], u[cm2], f[cm1], be[GEN ? cm1 : 0], y1, std::false_type{});
         // second sweep
         calm();
         if constexpr (LATE) y2 = outer(rb + 2 * kSet, ra + 2 * kSet);
-        colour(s - 2, q[cm2], P, 0, u[cm2], u[cm1], u[cm3], f[cm2], be[GEN ? cm2 : 0], y2);
+        colour(s - 2, q[cm2], P, 0, u[cm2], u[cm1], u[cm3], f[cm2], be[GEN ? cm2 : 0], y2, std::true_type{});
         {
             // below plane s-3 only its red nodes are needed, kept in dr
             T dn[R][V];
@@ -633,7 +644,7 @@ __global__ __launch_bounds__(64 * NW) void k_pair3(const LevelItem *__restrict__
                 }
             calm();
             if constexpr (LATE) y3 = outer(rb + 3 * kSet, ra + 3 * kSet);
-            colour(s - 3, q[cm3], Q, 1, u[cm3], u[cm2], dn, f[cm3], be[GEN ? cm3 : 0], y3);
+            colour(s - 3, q[cm3], Q, 1, u[cm3], u[cm2], dn, f[cm3], be[GEN ? cm3 : 0], y3, std::true_type{});
             if constexpr (CALM) {
                 __builtin_amdgcn_sched_barrier(0);
                 read_rest();
