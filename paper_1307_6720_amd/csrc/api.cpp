@@ -2203,7 +2203,23 @@ int mhs_stage_smooth(mhs_plan *p, const mhs_model *model, int32_t space, int32_t
         // the kernel takes the boundary values as zero, which a caller
         // guarantees from a zero guess only)
         const bool pair = (h->planar || zero || (!d_f && path == kF64)) && q + 1 < nsweeps;
-        add_sweep(pg, p->stage, *h, level, path, zero ? nullptr : cur, oth, d_f, nullptr,
+        const void *f = d_f;
+        if (pair && zero && !h->planar) {
+            // and so it does those of f, which a caller does not guarantee:
+            // f's interior goes to u, whose own is not read and whose boundary
+            // values are zero
+            const Level &lv = h->lv[level];
+            const size_t row = (size_t)lv.n[0] * es;
+            hipMemcpy3DParms c{};
+            c.srcPtr = make_hipPitchedPtr(const_cast<void *>(d_f), row, row, (size_t)lv.n[1]);
+            c.dstPtr = make_hipPitchedPtr(d_u, row, row, (size_t)lv.n[1]);
+            c.srcPos = c.dstPos = make_hipPos(es, 1, 1);
+            c.extent = make_hipExtent(row - 2 * es, (size_t)lv.n[1] - 2, (size_t)lv.n[2] - 2);
+            c.kind = hipMemcpyDeviceToDevice;
+            HIPCHK(hipMemcpy3DAsync(&c, s));
+            f = d_u;
+        }
+        add_sweep(pg, p->stage, *h, level, path, zero ? nullptr : cur, oth, f, nullptr,
                   (zero ? kZeroIn : 0) | (pair ? kTwoSweeps : 0), nullptr, nullptr);
         std::swap(cur, oth);
         q += pair ? 2 : 1;
