@@ -293,7 +293,11 @@ int mhs_solve_face(mhs_plan *plan, int32_t face, const double *d_a, const double
  * the level's shape; boundary nodes of u are its Dirichlet values.  For
  * space 3 the model supplies xi and alpha; for space 2 it may be NULL.
  * The coarse coefficients use xi sampled at the coarse nodes.  These run
- * the same kernels as the solves. */
+ * the solves' kernels: the 3D calls those of one sweep, one restriction and so
+ * on, which take boundary values as data everywhere, except that
+ * mhs_stage_smooth takes two sweeps per launch from a zero guess, and in FP64
+ * without f.  The cycles' launches of two sweeps, with or without a correction
+ * before or a restriction after, are those of mhs_stage_two_sweeps. */
 
 /* u <- nsweeps red-black Gauss-Seidel sweeps on A u = f (f may be NULL:
  * zero).  Red = (i+j+k) even, updated first.  zero_guess = 1: the first
@@ -313,10 +317,35 @@ int mhs_stage_restrict(mhs_plan *plan, const mhs_model *model, int32_t space, in
 
 /* u <- nsweeps (>= 1) red-black sweeps applied to u + I(e_c), where I is
  * trilinear (bilinear in 2D) interpolation from level+1, added on interior
- * nodes only (the first sweep fused with it, as in the cycle). */
+ * nodes only (in 2D two sweeps per launch, in 3D single ones; the first
+ * launch fused with the interpolation). */
 int mhs_stage_correct_smooth(mhs_plan *plan, const mhs_model *model, int32_t space,
                              int32_t level, int32_t precision, void *d_u, const void *d_f,
                              const void *d_ec, int32_t nsweeps, void *stream);
+
+/* out <- two red-black sweeps on A u = f from u + I(e_c), in the one launch
+ * that the cycles take for them on 3D level `level` (above the bottom level).
+ *   u     NULL: the zero guess (needs f, no e_c).
+ *   f     NULL: zero, in FP64 only; u's boundary values are then data, on the
+ *         side faces too if faces is MHS_FACES_GIVEN (MHS_FACES_ZERO: they are
+ *         zero there).  With f, the boundary values of u and f must be 0.
+ *   e_c   correction on level+1, or NULL; its boundary values must be 0.
+ *   f_c   NULL, or receives the full weighting of out's residual (needs f, no
+ *         e_c).  e_c and f_c need a step to level+1 that halves x and y.
+ *   norm  NULL, or receives ||A u||_2 (no f, no e_c; synchronous).
+ * variant is an index of the kernel's tilings (waves per workgroup, planes in
+ * flight, lanes per row), or -1 for the one that a solve of this grid takes;
+ * kz the planes per workgroup, or 0 for the chosen ones.  The results do not
+ * depend on either (the norm but for its rounding).  out must not overlap u.
+ * It is written on interior nodes, and on the column i = 0 with u's values (0
+ * with f).
+ * Errors: MHS_ERR_UNSUPPORTED for a variant whose windows do not fit the
+ * level, a precision the plan has not, or a level of the bottom solver;
+ * MHS_ERR_INVALID_ARG for any other combination than the above and for
+ * kz out of the variant's range (odd with f_c included). */
+int mhs_stage_two_sweeps(mhs_plan *plan, const mhs_model *model, int32_t level, int32_t precision,
+                         const void *d_u, const void *d_f, const void *d_ec, void *d_out, void *d_fc,
+                         int32_t faces, int32_t variant, int32_t kz, double *norm, void *stream);
 
 /* u <- one V(nu1,nu2) cycle, starting from u = 0, on A u = f over the
  * plan's bottom levels (from level mhs_plan_bottom_level() to the coarsest,

@@ -109,6 +109,7 @@ def lib():
         "mhs_stage_smooth": (C.c_int, [vp, P(Model), i32, i32, i32, vp, vp, i32, i32, vp]),
         "mhs_stage_restrict": (C.c_int, [vp, P(Model), i32, i32, i32, vp, vp, vp, vp]),
         "mhs_stage_correct_smooth": (C.c_int, [vp, P(Model), i32, i32, i32, vp, vp, vp, i32, vp]),
+        "mhs_stage_two_sweeps": (C.c_int, [vp, P(Model), i32, i32, vp, vp, vp, vp, vp, i32, i32, i32, P(dbl), vp]),
         "mhs_stage_bottom": (C.c_int, [vp, P(Model), i32, i32, vp, vp, i32, i32, P(i32), vp]),
         "mhs_stage_residual_norm": (C.c_int, [vp, P(Model), i32, i32, i32, vp, vp, P(dbl), vp]),
         "mhs_diagnostics": (C.c_int, [vp, P(Model)] + [vp] * 10 + [vp]),

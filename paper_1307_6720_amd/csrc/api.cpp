@@ -94,7 +94,7 @@ int chunk(int planes, int xy_tiles, int cap, int target = kTargetGroups)
 // are read again, by then from memory (513 x 513 x 257, chunks of 36 -> 90
 // planes: two FP32 sweeps 224 -> 185 us; twelve 257^3 with the restriction
 // 755 -> 689 us).
-PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max_waves)
+PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max_waves, int only)
 {
     const int V = path == kF64 ? kPairV64 : kPairV32;
     const double es = path == kF64 ? 8.0 : 4.0;
@@ -123,7 +123,7 @@ PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max
     double tbest = 0.0;
     for (int q = 0; q < kPairNVariants; ++q) {
         const PairVariant &pv = kPairVariants[q];
-        if (pv.waves > max_waves) continue;
+        if (pv.waves > max_waves || (only >= 0 && q != only)) continue;
         int lgx = 0;
         while (lgx < 6 && (V << lgx) < mx) ++lgx;
         if (pv.row) lgx = 4;
@@ -2266,7 +2266,8 @@ int mhs_stage_correct_smooth(mhs_plan *p, const mhs_model *model, int32_t space,
     if ((st = begin_staging(p))) return st;
     Program pg;
     void *cur = d_u, *oth = tw;
-    // as in the cycles: on the 2D hierarchy two sweeps per launch
+    // as in the cycles two sweeps per launch, but in 3D single ones (the
+    // launch of two takes the boundary values as zero)
     const bool pair0 = h->planar && nsweeps >= 2;
     add_correct_sweep(pg, p->stage, *h, level, path, cur, oth, d_f, d_ec, nullptr, pair0 ? kTwoSweeps : 0);
     std::swap(cur, oth);
@@ -2281,6 +2282,61 @@ int mhs_stage_correct_smooth(mhs_plan *p, const mhs_model *model, int32_t space,
     if ((st = run_program(p, pg, s))) return st;
     if (cur != d_u) HIPCHK(hipMemcpyAsync(d_u, cur, bytes, hipMemcpyDeviceToDevice, s));
     return release_twin(*h, level, path, s);
+}
+
+int mhs_stage_two_sweeps(mhs_plan *p, const mhs_model *model, int32_t level, int32_t precision, const void *d_u,
+                         const void *d_f, const void *d_ec, void *d_out, void *d_fc, int32_t faces, int32_t variant,
+                         int32_t kz, double *norm, void *stream)
+{
+    hipStream_t s = (hipStream_t)stream;
+    Hierarchy *h = nullptr;
+    int path = 0;
+    int st = stage_common(p, model, 3, level, precision, &h, &path, s);
+    if (st) return st;
+    if (level >= h->b) return fail(MHS_ERR_UNSUPPORTED, "level %d is handled by the bottom solver", level);
+    Level &lv = h->lv[level];
+    if (!d_out || d_out == d_u || (!d_u && (!d_f || d_ec)) || (!d_f && (path != kF64 || d_fc)) || (d_ec && d_fc) ||
+        ((d_ec || d_fc) && lv.keepxy) || (norm && (d_f || d_ec)) ||
+        (faces != MHS_FACES_ZERO && faces != MHS_FACES_GIVEN))
+        return fail(MHS_ERR_INVALID_ARG, "no such launch of two sweeps");
+    if (variant < -1 || variant >= kPairNVariants) return fail(MHS_ERR_INVALID_ARG, "no such variant");
+    const int kind = !d_f ? (faces == MHS_FACES_GIVEN ? kPairDataFaces : kPairData)
+                          : !d_u ? (d_fc ? kPairRestZero : kPairZero) : (d_fc ? kPairRestF : kPairF);
+    PairTiling &used = lv.pair[path][kind][0], pt = used;
+    if (variant >= 0) pt = pair_tiling(lv.n, path, kind, false, 12, variant);
+    if (pt.var < 0) return fail(MHS_ERR_UNSUPPORTED, "the variant's windows do not fit the level");
+    const PairVariant &pv = kPairVariants[pt.var];
+    if (kz < 0 || kz > pair_max_kz(pv.waves, pv.row) || (d_fc && (kz & 1)))
+        return fail(MHS_ERR_INVALID_ARG, "planes per workgroup out of range");
+    if (kz) {
+        pt.kz = kz;
+        pt.nt[2] = ceil_div(lv.n[2] - 2, kz);
+    }
+    if (norm && pt.tiles() > p->scratch_npart) return fail(MHS_ERR_WORKSPACE, "scratch too small");
+    if ((st = begin_staging(p))) return st;
+    Program pg;
+    SolveState *d_state = nullptr;
+    {
+        const PairTiling solves = used;
+        used = pt;
+        h->faces = faces == MHS_FACES_GIVEN;
+        add_sweep(pg, p->stage, *h, level, path, d_u, d_out, d_f, d_ec,
+                  kTwoSweeps | (d_u ? 0 : kZeroIn) | (d_ec ? kProlong : 0) | (norm ? kNorm : 0), nullptr,
+                  norm ? p->d_scratch_norm : nullptr, d_fc);
+        used = solves;
+    }
+    if (norm) {
+        d_state = (SolveState *)p->stage.put(initial_state(0.0, 0));
+        add_finalize(pg, p->stage, p->d_scratch_norm, pt.tiles(), d_state);
+    }
+    if (!pg.ok || (norm && !d_state)) return fail(MHS_ERR_WORKSPACE, "staging area exhausted");
+    if ((st = flush_staging(p, s))) return st;
+    if ((st = run_program(p, pg, s))) return st;
+    if (!norm) return MHS_OK;
+    SolveState ss{};
+    if ((st = read_state(p, d_state, &ss, s))) return st;
+    *norm = ss.rnorm;
+    return MHS_OK;
 }
 
 int mhs_stage_bottom(mhs_plan *p, const mhs_model *model, int32_t space, int32_t precision, void *d_u,

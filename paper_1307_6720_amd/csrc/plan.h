@@ -267,7 +267,8 @@ int drive(mhs_plan *p, const Program &cycle, const SolveState *d_state, const mh
           int *syncs, hipStream_t s, int kind, const std::function<int()> *overlap = nullptr);
 double seconds_since(std::chrono::steady_clock::time_point t0);
 
-PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max_waves = 12);
+// (only: among one variant's; var is -1 if its windows do not fit)
+PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max_waves = 12, int only = -1);
 // Shapes and step kinds of a multigrid hierarchy (api.cpp).
 int build_geometry(Hierarchy &h, const int n0[3], const double len[3], bool planar);
 

@@ -439,6 +439,22 @@ class Plan:
                                                       _stream(self.device)))
         return u
 
+    def stage_two_sweeps(self, model, level, u, f, out, ec=None, fc=None, precision=PREC_FP64, faces_given=False,
+                         variant=-1, kz=0, norm=False):
+        """Two sweeps on 3D level `level` from u + I(ec) (u None: from zero) in
+        the one launch that the cycles take for them; fc receives the
+        restriction of the residual.  Returns out, or with `norm` the residual
+        norm of u (see mhs_stage_two_sweeps)."""
+        self._check_stage(3, level, precision, ((u, 0, "u"), (f, 0, "f"), (ec, 1, "ec"), (fc, 1, "fc"), (out, 0, "out")))
+        m = _ModelArgs.of(model)
+        r = C.c_double()
+        with torch.cuda.device(self.device):
+            check(_lib.lib().mhs_stage_two_sweeps(self.h, C.byref(m.c) if m else None, level, precision, _ptr(u),
+                                                  _ptr(f), _ptr(ec), _ptr(out), _ptr(fc),
+                                                  _lib.FACES_GIVEN if faces_given else _lib.FACES_ZERO, variant, kz,
+                                                  C.byref(r) if norm else None, _stream(self.device)))
+        return r.value if norm else out
+
     def stage_bottom(self, model, space, u, f, nu1=2, nu2=2, precision=PREC_FP64):
         # the bottom level depends on the model (uploaded by the call), so
         # the shape is checked against every level the plan has
