@@ -166,6 +166,13 @@ PairTiling pair_tiling(const int n[3], int path, int kind, bool batched, int max
     return best;
 }
 
+const PairTiling &Level::tiling(int path, int kind, bool merged) const
+{
+    PairTiling &t = pair[path][kind][merged ? 1 : 0];
+    if (t.var < 0) t = pair_tiling(n, path, kind, merged);
+    return t;
+}
+
 bool valid_axis(int n)
 {
     if (n < 5) return false;
@@ -349,21 +356,6 @@ size_t carve_plan(mhs_plan *p, char *base, int precisions)
     p->stage.cap = kStagingBytes;
     if (precisions & MHS_PLAN_GENERAL) gen_create(p, cv);
     return cv.off + kAlign;
-}
-
-// Tilings of the two-sweep launches of the paths in `paths`, and of merged
-// launches (`merged`).
-void tile_pairs(Hierarchy &h, int paths, bool merged)
-{
-    for (int l = 0; l < h.L; ++l)
-        for (int path = 0; path < 2; ++path)
-            for (int k = 0; k < kPairKinds; ++k) {
-                const bool data = k == kPairData || k == kPairDataFaces;
-                if (!(paths & (1 << path)) || (data && path != kF64)) continue;
-                Level &lv = h.lv[l];
-                for (int bt = 0; bt < (merged ? 2 : 1); ++bt)
-                    if (lv.pair[path][k][bt].var < 0) lv.pair[path][k][bt] = pair_tiling(lv.n, path, k, bt != 0);
-            }
 }
 
 int geometry(mhs_plan *p, const mhs_grid *g)
@@ -792,8 +784,10 @@ void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, co
     // (the norm's partial sums depend on the tiling: the single request's)
     const int kind = !f ? (h.faces ? kPairDataFaces : kPairData)
                         : (flags & kZeroIn) ? (fc ? kPairRestZero : kPairZero) : (fc ? kPairRestF : kPairF);
-    const PairTiling &pt = lv.pair[path][kind][h.batched && !(flags & kNorm) ? 1 : 0];
+    int var = 0;
     if (pair3) {
+        const PairTiling &pt = lv.tiling(path, kind, h.batched && !(flags & kNorm));
+        var = pt.var;
         it.ext = kind == kPairDataFaces ? 2 : 0;
         it.lgx = pt.lgx;
         it.ntx = pt.nt[0];
@@ -812,7 +806,7 @@ void add_sweep(Program &pg, Staging &st, const Hierarchy &h, int l, int path, co
     L.flags = flags | (f ? kHasF : 0) | (fc ? kPairRestrict : 0);
     if (pair3) {
         if (((flags & kProlong) || fc) && lv.keepz) L.flags |= kPairKeepZ;
-        L.flags |= pt.var << kPairVariantShift;
+        L.flags |= var << kPairVariantShift;
     }
     L.dbl = path == kF64;
     L.items = d;
@@ -1601,7 +1595,6 @@ int mhs_plan_create(const mhs_grid *grid, int32_t precisions, void *d_ws, size_t
     p->ws = (char *)d_ws;
     p->ws_bytes = ws_bytes;
     carve_plan(p, p->ws, precisions);
-    tile_pairs(p->h3, precisions & 3, true);
     gen_tile_pairs(p);
     if (hipHostMalloc((void **)&p->stage.host, kStagingBytes, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&p->h_states, 4 * sizeof(SolveState), hipHostMallocDefault) != hipSuccess ||
@@ -2302,7 +2295,7 @@ int mhs_stage_two_sweeps(mhs_plan *p, const mhs_model *model, int32_t level, int
     if (variant < -1 || variant >= kPairNVariants) return fail(MHS_ERR_INVALID_ARG, "no such variant");
     const int kind = !d_f ? (faces == MHS_FACES_GIVEN ? kPairDataFaces : kPairData)
                           : !d_u ? (d_fc ? kPairRestZero : kPairZero) : (d_fc ? kPairRestF : kPairF);
-    PairTiling &used = lv.pair[path][kind][0], pt = used;
+    PairTiling &used = lv.pair[path][kind][0], pt = lv.tiling(path, kind, false);
     if (variant >= 0) pt = pair_tiling(lv.n, path, kind, false, 12, variant);
     if (pt.var < 0) return fail(MHS_ERR_UNSUPPORTED, "the variant's windows do not fit the level");
     const PairVariant &pv = kPairVariants[pt.var];
@@ -2451,7 +2444,6 @@ int mhs_solve_interior_noalloc(const mhs_grid *grid, const mhs_model *model, dou
     p.ws = slot.dev;
     p.ws_bytes = kScratchBytes;
     const size_t used = carve_plan(&p, p.ws, o->precision) - kAlign;
-    tile_pairs(p.h3, o->precision, false);
     p.stage.host = g_scratch_stage[dev];
     p.h_states = slot.states;
     hipStream_t s = (hipStream_t)stream;

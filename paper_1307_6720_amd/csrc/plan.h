@@ -73,8 +73,10 @@ struct Level {
     bool keepz = false;    // the step to level+1 halves x and y only
     bool keepxy = false;   // the step to level+1 halves z only
     // two-sweep launches, per path, kind (PairKind) and for a single request
-    // or a batch's merged launches
-    PairTiling pair[2][kPairKinds][2];
+    // or a batch's merged launches; found when a launch first takes one (a
+    // solve takes a tenth of them)
+    mutable PairTiling pair[2][kPairKinds][2];
+    const PairTiling &tiling(int path, int kind, bool merged) const;
     int ity = 0;           // refinement-step tiles in y (kTY rows; the smoother's are kSTY)
     int sweep_tiles() const { return st[0] * st[1] * st[2]; }
     int ir_tiles() const { return st[0] * ity * st[2]; }
