@@ -161,30 +161,5 @@ struct PlaneTab {
     __device__ __forceinline__ T operator()(int p) const { return lane_bcast(v, p - base); }
 };
 
-// Trilinear interpolation of the coarse correction at fine node (i, j, k):
-// coincident nodes copy, edge/face/cell midpoints average 2/4/8 values.
-template <typename T, typename Ptr>
-__device__ __forceinline__ T interp3(Ptr ec, int ncx, int ncy, int i, int j, int k)
-{
-    const size_t sy = (size_t)ncx, sz = (size_t)ncx * ncy;
-    const Ptr p = ec + (size_t)(i >> 1) + sy * (size_t)(j >> 1) + sz * (size_t)(k >> 1);
-    const int oi = i & 1, oj = j & 1, ok = k & 1;
-    const T h = (T)0.5;
-    auto X = [&](Ptr q) -> T { return oi ? h * (q[0] + q[1]) : (T)q[0]; };
-    auto Y = [&](Ptr q) -> T { return oj ? h * (X(q) + X(q + sy)) : X(q); };
-    return ok ? h * (Y(p) + Y(p + sz)) : Y(p);
-}
-
-template <typename T, typename Ptr>
-__device__ __forceinline__ T interp2(Ptr ec, int ncx, int i, int j)
-{
-    const size_t sy = (size_t)ncx;
-    const Ptr p = ec + (size_t)(i >> 1) + sy * (size_t)(j >> 1);
-    const int oi = i & 1, oj = j & 1;
-    const T h = (T)0.5;
-    auto X = [&](Ptr q) -> T { return oi ? h * (q[0] + q[1]) : (T)q[0]; };
-    return oj ? h * (X(p) + X(p + sy)) : X(p);
-}
-
 } // namespace
 } // namespace mhs

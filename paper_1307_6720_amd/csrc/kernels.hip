@@ -43,10 +43,6 @@ namespace {
 constexpr int kWX = kTX + 4;
 constexpr int kWY = kSTY + 4;
 constexpr int kWCells = kWX * kWY;
-// LDS rows store even columns first, then odd columns, so the colour phases
-// (which touch every other column) read consecutive doubles: no bank conflicts
-constexpr int kHalf = kWX / 2;
-__device__ __forceinline__ int sx(int c) { return (c & 1) * kHalf + (c >> 1); }
 static_assert(kWX % 2 == 0, "window width must be even");
 constexpr int kWPer = (kWCells + kSThreads - 1) / kSThreads;
 constexpr int kRedPerRow = kTX / 2 + 1;
