@@ -654,7 +654,7 @@ def general_leg(torch, dev, n=257, reps=3, rtol=1e-10):
 
 
 def level0_kz(grid):
-    """Planes per workgroup of the level-0 smoother: the library's rule
+    """Planes per workgroup of a single level-0 sweep: the library's rule
     (about 1024 groups of 64 x 8 node units per request, at most 32 planes)."""
     units = -(-(grid.nx - 2) // 64) * -(-(grid.ny - 2) // 8)
     return max(1, min(32, -(-(grid.nz - 2) * units // 1024)))
@@ -922,11 +922,9 @@ def main():
         if "copy_reference_gbps" not in r:
             r["copy_reference_gbps"] = copy_reference(r["algorithmic_bytes_per_launch"])
             r["frac_of_copy_reference"] = r["achieved"] / r["copy_reference_gbps"]
+    # (the traffic of one sweep per launch: not what a roofline launch, of two
+    # sweeps and a transfer, moves)
     pattern = pattern_reference(torch, dev, grid, a.batch if batched is not None else 1)
-    roofline.update(pattern["merged" if batched is not None else "single"])
-    roofline["frac_of_pattern_reference"] = roofline["achieved"] / roofline["pattern_reference_gbps"]
-    roof_single.update(pattern["single"])
-    roof_single["frac_of_pattern_reference"] = roof_single["achieved"] / roof_single["pattern_reference_gbps"]
 
     # diagnostics of (1)-(3) on the last equilibrium's fields (off the
     # solve's path): j, |force residual|, div B; 80 B per node (read 5, write 5)
@@ -1026,6 +1024,7 @@ def main():
         "kernels_note": "per-class HIP-event timings from a separate pass with every class timed",
         "roofline": roofline,
         "roofline_single_request": roof_single,
+        "single_sweep_pattern": pattern,
         "diagnostics": diagnostics,
         "field_lines": field_lines,
         "serving": serving,

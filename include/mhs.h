@@ -526,9 +526,10 @@ int mhs_batch_profile_read(mhs_batch *batch, int32_t klass, double *total_ms, in
                            double *bytes, int32_t reset);
 
 /* ---- access-pattern reference (a measurement aid, not part of a solve) -- *
- * Moves the compulsory bytes of a level-0 FP32 smoother launch (read u_in
- * and f, write u_out: 12 bytes per interior node) in the smoother's memory
- * order, with no LDS, barrier or arithmetic worth the name, so that its
+ * Moves the compulsory bytes of one level-0 FP32 sweep in a launch of its own
+ * (read u_in and f, write u_out: 12 bytes per interior node) in the memory
+ * order of that kernel (odd sweep counts; a launch of two sweeps has others),
+ * with no LDS, barrier or arithmetic worth the name, so that its
  * rate is the ceiling the z-marching tile pattern itself allows: per
  * workgroup an x-y tile of interior nodes of one request marching kz planes
  * (from two planes below the chunk to one above it), reading the tile plus
@@ -536,7 +537,7 @@ int mhs_batch_profile_read(mhs_batch *batch, int32_t klass, double *total_ms, in
  * tile's nodes of the chunk's planes, and writing u_out at those nodes.
  * d_u, d_f, d_out: nreq device arrays of nx*ny*nz floats each, x-fastest,
  * request r at element offset r*nx*ny*nz (caller-owned, distinct).  tile 0
- * is the smoother's tile (64 x 16 nodes, 512 threads), tile 1 a row-wide
+ * is that kernel's tile (64 x 16 nodes, 512 threads), tile 1 a row-wide
  * tile (256 x 8 nodes, 1024 threads); kz >= 1.  Overwrites the interior
  * nodes of d_out with f plus 1e-30 times a sum of loaded values (finite
  * inputs stay finite) and nothing else.  Asynchronous on `stream`.  Errors:

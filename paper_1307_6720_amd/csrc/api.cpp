@@ -87,10 +87,11 @@ int chunk(int planes, int xy_tiles, int cap, int target = kTargetGroups)
 // variants of at most max_waves waves: the one with the smallest estimate of
 // its time.  The constants are fitted to the measured times of every variant
 // and chunk length on levels from 33^3 to 513 x 513 x 257, alone and four to
-// twelve together, in FP32 and FP64 (91 cases): for a launch alone its choices
-// are within 6 % of the best one measured; a batch of another number of
-// requests than the eight it assumes can lose more on levels of one round of
-// workgroups.  Large launches take long chunks: a chunk's first and last planes
+// twelve together, in FP32 and FP64 (92 cases; all the times are in
+// profiles/pair_tilings.txt): for a launch alone its choices are within 6 % of
+// the best one measured; a batch of another number of requests than the eight it
+// assumes can lose more on levels of one round of workgroups (twelve 129^3: up
+// to 38 %).  Large launches take long chunks: a chunk's first and last planes
 // are read again, by then from memory (513 x 513 x 257, chunks of 36 -> 90
 // planes: two FP32 sweeps 224 -> 185 us; twelve 257^3 with the restriction
 // 755 -> 689 us).

@@ -1754,8 +1754,8 @@ __global__ __launch_bounds__(kThreads) void k_diag(const DiagItem it)
 // for its four tangents), and the cell that the line is heading for is touched
 // kTraceAhead steps before, so that its lines are in the cache by then (a
 // tenth of the time; one to four steps ahead are alike).  16384 lines of up to
-// 1024 steps of half a cell in 257^3: 6.4 -> 1.3 ms, repeated on warm caches 0.8,
-// which is 0.2 us per tangent of the longest line.
+// 1024 steps of half a cell in 257^3: 6.4 -> 1.3 to 1.5 ms, repeated on warm
+// caches 0.8, which is 0.2 us per tangent of the longest line.
 // ============================================================================
 constexpr int kTraceThreads = 64;
 constexpr double kTraceAhead = 2.0;

@@ -159,9 +159,12 @@ __device__ __forceinline__ double lane_above(double v)
 // shift brings in past the wave's end, by the next row's first node, which is
 // one too (LX = 2^lgx lanes, a single window of 2^lgx * V + 1 nodes with it),
 // or by the zero past a row of 16 lanes (ROW).  ROW takes any number of
-// windows in x: long rows of narrow windows have a shorter rim, a 513-node row
-// in nine windows of 64 by 96 nodes computes 1.27 times its nodes, in three of
-// 256 by 24 2.25 times (257^3 in FP64, level 0: 94 -> 76 us with the norm).
+// windows in x: nearly square windows have a shorter rim, a plane of 513^2
+// in windows of 64 by 64 nodes (FP32, eight waves) computes 1.27 times its
+// nodes, in windows of 256 by 24 (twelve waves) 2.25 times.  513 x 513 x 257 in
+// FP32 with the correction 191 us, in the longest rows 235; with the restriction
+// (64 by 96) 226 against 350; 257^3 with the restriction (64 by 64) 52 against
+// 65, without it longer rows are as fast.
 // In z a march starts three planes below the planes it writes and ends three
 // above.
 //

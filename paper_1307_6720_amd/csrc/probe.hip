@@ -1,9 +1,8 @@
-// Access-pattern reference for the roofline of the level-0 smoother: a
-// kernel that moves the smoother's compulsory bytes in the smoother's own
-// memory order, with no LDS, barrier or arithmetic worth the name.  Its
-// rate is the ceiling the z-marching tile pattern itself allows on this
-// memory system; the smoother's rate is judged against it and against a
-// plain copy.  Measurement aid only: no solve uses it.
+// Access-pattern reference for a single level-0 sweep (k_sweep3): a kernel
+// that moves that sweep's compulsory bytes in its own memory order, with no
+// LDS, barrier or arithmetic worth the name.  Its rate is the ceiling the
+// z-marching tile pattern itself allows on this memory system.  Measurement aid
+// only: no solve uses it.
 #include "internal.h"
 #include "plan.h"
 
